@@ -5,32 +5,43 @@
 // squared distance, summed directly in fp32 in channel order, lowest index among equals.  The
 // matrix cores only tell which centroids can possibly be that one:
 //   score(c) = sigma (x . c - |c|^2 / 2)      (largest score <=> smallest distance)
-// for the 64 tokens of a tile against the 256 centroids of a sub-space, as
-// v_mfma_f32_32x32x16_f16 products: rows = 32 centroids, columns = 32 tokens, and along k
+// for the 64 tokens of a tile against 32 centroids at a time, as v_mfma_f32_32x32x16_f16 products:
+// rows = 32 centroids, columns = 32 tokens, and along k
 //   [ c          | c          | -sigma |c|^2 / 2 as two fp16 parts ]   (A)
 //   [ hi(sigma x)| lo(sigma x)| 1 1                               ]   (B)
 // (hi + lo: sigma x to 22 bits; the centroids are fp16 already; sigma, a power of two per
-// sub-space, keeps the low parts out of the fp16 denormal range).  The screen's error is bounded
-// (below), so every centroid that can win or tie has a score within `margin` of the best one.
-// A lane keeps, of the 128 scores it sees per token, only their maxima over the 16 registers of
-// each MFMA (8 "blocks") and over the 8 MFMAs for each register (16 "groups"): a score within the
-// margin marks its block and its group, so the (few, normally one) marked pairs are a superset
-// of the centroids that matter, and only those get the exact distance.
+// sub-space, keeps the low parts out of the fp16 denormal range).  At d = 8 that is 18 of 16 places:
+// the low parts of the last two channels are left out, which costs a wider margin instead of a
+// second MFMA.  The screen's error is bounded (below), so every centroid that can win or tie has a
+// score within `margin` of the best one.
+// A lane keeps, of the 128 scores it sees per token, only the maximum of each accumulator register
+// over the 8 blocks of 32 centroids (16 "groups" of 8 centroids): one v_max3_f32 per two scores,
+// which is the least that looks at every score.  A score within the margin marks its group, and the
+// centroids of the marked groups (normally one group) get the exact distance.  (Keeping the
+// maximum of every block as well, so that a mark names one centroid, costs as many v_max3_f32 again;
+// going over the 8 centroids of a group costs half of that.)
+//
+// What bounds it: vector-ALU instructions.  Per wavefront, sub-space and tile 128 + 16 for the maxima,
+// 64 for the marks, about 110 per round of exact distances, 50 for operands and the rest.
+// 65536 tokens x 8 heads, d = 4, keys / values: 459 / 398 us with block maxima, 338 / 276 us without;
+// 10007 tokens x 8 heads, d = 8, 12-bit codes: 511 / 498 us, 236 / 203 us (one MFMA per block, marks
+// once per search instead of once per 256 centroids).
 //
 // Error bound, in score units (T = sum_j |x_j| max|c_j| + max|c|^2 / 2 bounds the sum of the
-// magnitudes of a score's terms):
-//   split of sigma x          <= 2^-22 sigma T        fp32 |c|^2 and its two parts   <= 2^-20.2 sigma T
-//   fp32 accumulation of <= 18 products, every addition taken as truncating (2^-23): <= 2^-18.8 sigma T
-//   (10 products and 2^-19.7 at d = 4; a matrix core that rounds once per instruction is far below this)
+// magnitudes of a score's terms), per score:
+//   split of sigma x                                                        <= 2^-22 sigma T
+//   fp32 |c|^2 (d roundings) and its two parts                  <= (d 2^-24 + 2^-22) sigma T
+//   fp32 accumulation of n products (n = 2 d + 2, 16 at d = 8), every addition
+//   taken as truncating                                                 <= n 2^-23 sigma T
 //   fp16 parts below 2^-14 taken as flushed to zero: <= 2^-14 (d max|c_j| + 3), whatever sigma
-//   two scores compared: twice the sum, 2^-17.25 sigma T + 2^-13 (d max|c_j| + 3) < the margin's first terms
-//   the exact distances themselves carry (d + 2) 2^-24 relative rounding each; a centroid is
-//   safely worse when its true distance exceeds the best's by 2^-18.9 times the best distance
-//   (<= 2 (|x|^2 + max|c|^2)), i.e. by 2^-18 sigma (|x|^2 + max|c|^2) in score units.
-// margin = sigma (2^-17 T + 2^-18 (|x|^2 + max|c|^2)) + 2^-13 (d max|c_j| + 3).
+//   d = 8: the low parts left out,                     <= (|lo_6| + |lo_7|) max|c_j|
+// Two scores are compared, so twice that.  The exact distances themselves carry (d + 2) 2^-24
+// relative rounding each: a centroid is safely worse when its true distance exceeds the best's, D, by
+// 2 (d + 2) 2^-24 D, i.e. its score lies (d + 2) 2^-24 sigma D below; sigma D = sigma |x|^2 - 2 best.
+// (5 % are added to cover the margin's own rounding and what the screen's error does to D.)
 // A token whose scaled sub-vector leaves the fp16 range (or holds an infinity or a NaN) has no
-// finite best score, a sub-space whose |c|^2 does not fit gets a NaN sigma: either way the
-// wavefront falls back to the plain search for that tile.
+// finite best score; a codebook whose |c|^2 does not fit, or that holds an infinity or a NaN, gets
+// a NaN sigma: either way the wavefront falls back to the plain search for that tile.
 #pragma once
 #include "common.h"
 
@@ -43,16 +54,20 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// LDS tables of one codebook of C centroids: plane 0 = the fp16 centroids as MFMA A operands want
-// them (d = 2: each twice, d = 4: 8 bytes, d = 8: 16 bytes), plane 1 = -sigma |c|^2 / 2 as {hi, lo};
-// 16 spare bytes, so that an 8-byte read of the last plane-1 entry stays inside.
+// LDS table of one codebook of C centroids: one entry per centroid with everything the MFMA's A operand
+// needs of it, so that a lane fetches its operand with one 16-byte read and no register moves:
+//   d = 2:  8 bytes  [ c0 c1 | n n' ]                 d = 4: 12 bytes  [ c0 .. c3 | n n' ]
+//   d = 8: 20 bytes  [ n n' | c0 .. c7 ]
+// (c: the fp16 centroid, n n': -sigma |c|^2 / 2 in two fp16 parts).  A 16-byte read of the last entries
+// runs into the 16 spare bytes at the end.
 // C = 256: the codebook of one sub-space (8-bit codes); C = 2^b: the one codebook a KV head's
-// sub-spaces share (10- / 12-bit codes), searched 256 centroids ("chunk") at a time.
+// sub-spaces share (10- / 12-bit codes).
 template <int d, int C = kCentroids>
 struct ScreenTab {
-    static constexpr int kCenBytes = d == 8 ? 16 : 8;
-    static constexpr int kPlane0 = C * kCenBytes;
-    static constexpr int kBytes = kPlane0 + C * 4 + 16;
+    static constexpr int kEntry = d == 8 ? 20 : (d == 4 ? 12 : 8);
+    static constexpr int kCen = d == 8 ? 4 : 0;             // offset of the centroid in its entry
+    static constexpr int kNorm = d == 8 ? 0 : 2 * d;        // offset of its norm
+    static constexpr int kBytes = C * kEntry + 16;
 };
 
 struct ScreenConsts {
@@ -67,8 +82,9 @@ __device__ __forceinline__ float wave_max(float v)
 }
 
 // sigma: the power of two that brings max |c|^2 / 2 to about 2^10 (within 2^-14 .. 2^14).
-// Centroids too large for the fp16 parts of -sigma |c|^2 / 2 (or not finite): no screen for this
-// codebook; a NaN sigma makes every margin NaN, which sends every tile to the plain search.
+// Centroids too large for the fp16 parts of -sigma |c|^2 / 2 (or not finite: nm is then infinite): no
+// screen for this codebook; a NaN sigma makes every margin NaN, which sends every tile to the plain
+// search.
 __device__ __forceinline__ float screen_sigma(float nm)
 {
     int e = 9 - ilogbf(fmaxf(0.5f * nm, 1e-30f));
@@ -78,15 +94,15 @@ __device__ __forceinline__ float screen_sigma(float nm)
 }
 
 template <int d>
-__device__ __forceinline__ void screen_store_norm(unsigned char *plane1, int c, float sigma, float n)
+__device__ __forceinline__ void screen_store_norm(unsigned char *tab, int c, float sigma, float n)
 {
     const float v = -0.5f * sigma * n;
     const _Float16 hi = (_Float16)v;
     const f16x2 h = {hi, (_Float16)(v - (float)hi)};
-    *reinterpret_cast<f16x2 *>(plane1 + c * 4) = h;
+    *reinterpret_cast<f16x2 *>(tab + c * ScreenTab<d>::kEntry + ScreenTab<d>::kNorm) = h;
 }
 
-// Plane-0 entry of centroid c from its fp16 values; returns |c|^2 (fp32) and folds max |c_j| into cm.
+// The fp16 values of centroid c -> its entry; returns |c|^2 (fp32) and folds max |c_j| into cm.
 template <int d>
 __device__ __forceinline__ float screen_store_centroid(const __half *src, unsigned char *tab, int c, float &cm)
 {
@@ -99,12 +115,11 @@ __device__ __forceinline__ float screen_store_centroid(const __half *src, unsign
         s = fmaf(v, v, s);
         cm = fmaxf(cm, fabsf(v));
     }
-    if constexpr (d == 2) {
-        const f16x4 h = {raw[0], raw[1], raw[0], raw[1]};
-        *reinterpret_cast<f16x4 *>(tab + c * 8) = h;
-    } else {
-        *reinterpret_cast<f16xd *>(tab + c * (2 * d)) = raw;
-    }
+    unsigned w[d / 2];
+    __builtin_memcpy(w, &raw, 2 * d);
+#pragma unroll
+    for (int j = 0; j < d / 2; ++j)
+        *reinterpret_cast<unsigned *>(tab + c * ScreenTab<d>::kEntry + ScreenTab<d>::kCen + 4 * j) = w[j];
     return s;
 }
 
@@ -117,13 +132,13 @@ __device__ __forceinline__ ScreenConsts screen_prepare(const __half *src, unsign
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         n[i] = screen_store_centroid<d>(src, tab, lane + 64 * i, cm);
-        nm = fmaxf(nm, n[i]);
+        nm = fmaxf(nm, n[i] < INFINITY ? n[i] : INFINITY);
     }
     cm = wave_max(cm);
     nm = wave_max(nm);
     const float sigma = screen_sigma(nm);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) screen_store_norm<d>(tab + ScreenTab<d>::kPlane0, lane + 64 * i, sigma, n[i]);
+    for (int i = 0; i < 4; ++i) screen_store_norm<d>(tab, lane + 64 * i, sigma, n[i]);
     if (lane < 4) *reinterpret_cast<unsigned *>(tab + ScreenTab<d>::kBytes - 16 + 4 * lane) = 0u;   // the spare bytes
     return ScreenConsts{sigma, cm, nm};
 }
@@ -140,7 +155,7 @@ __device__ __forceinline__ ScreenConsts screen_prepare_shared(const __half *src,
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         n[i] = screen_store_centroid<d>(src, tab, tid + BLOCK * i, cm);
-        nm = fmaxf(nm, n[i]);
+        nm = fmaxf(nm, n[i] < INFINITY ? n[i] : INFINITY);
     }
     cm = wave_max(cm);
     nm = wave_max(nm);
@@ -156,26 +171,52 @@ __device__ __forceinline__ ScreenConsts screen_prepare_shared(const __half *src,
     }
     const float sigma = screen_sigma(nm);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) screen_store_norm<d>(tab + ScreenTab<d, C>::kPlane0, tid + BLOCK * i, sigma, n[i]);
+    for (int i = 0; i < PER; ++i) screen_store_norm<d>(tab, tid + BLOCK * i, sigma, n[i]);
     if (tid < 4) *reinterpret_cast<unsigned *>(tab + ScreenTab<d, C>::kBytes - 16 + 4 * tid) = 0u;        // the spare bytes
     __syncthreads();
     return ScreenConsts{sigma, cm, nm};
 }
 
-// Bits of the squared distance of x to centroid c of the codebook whose tables are `tab`: the
-// fp16 centroid widened (exact), differences squared and summed in channel order in fp32.
+// The fp16 centroid at p (4-byte aligned).
 template <int d>
-__device__ __forceinline__ unsigned screen_dist_bits(const float (&x)[d], const unsigned char *tab, int c)
+__device__ __forceinline__ void screen_load_centroid(const unsigned char *p, _Float16 (&cen)[d])
 {
-    typedef _Float16 f16xd __attribute__((ext_vector_type(d)));
-    const f16xd cen = *reinterpret_cast<const f16xd *>(tab + c * ScreenTab<d>::kCenBytes);
+    unsigned w[d / 2];
+#pragma unroll
+    for (int j = 0; j < d / 2; ++j) w[j] = *reinterpret_cast<const unsigned *>(p + 4 * j);
+    __builtin_memcpy(cen, w, 2 * d);
+}
+
+// A constant in a scalar register that the compiler does not see through.
+__device__ __forceinline__ float opaque(float v)
+{
+    asm("" : "+s"(v));
+    return v;
+}
+
+// Bits of the squared distance of x to a centroid: the fp16 centroid widened (exact), differences
+// squared and summed in channel order in fp32.  The difference is a fused multiply-add by -1, which
+// rounds the same value once and takes the fp16 operand as it is (v_fma_mix_f32 in place of a
+// conversion and a subtraction).
+template <int d>
+__device__ __forceinline__ unsigned dist_bits(const float (&x)[d], const _Float16 (&cen)[d])
+{
+    const float minus1 = opaque(-1.0f);
     float dist = 0.f;
 #pragma unroll
     for (int j = 0; j < d; ++j) {
-        const float t = x[j] - (float)cen[j];
+        const float t = fmaf((float)cen[j], minus1, x[j]);
         dist = fmaf(t, t, dist);
     }
     return __float_as_uint(dist);
+}
+
+template <int d>
+__device__ __forceinline__ unsigned screen_dist_bits(const float (&x)[d], const unsigned char *tab, int c)
+{
+    _Float16 cen[d];
+    screen_load_centroid<d>(tab + c * ScreenTab<d>::kEntry + ScreenTab<d>::kCen, cen);
+    return dist_bits<d>(x, cen);
 }
 
 // The plain search of one token's sub-vector x over the C centroids (the same address in every
@@ -208,297 +249,339 @@ __device__ __forceinline__ void plain_search(const float (&x)[d], const unsigned
     best_out = best;
 }
 
-// B operands and margins of tokens col (cb = 0) and 32 + col (cb = 1) of the tile.
+// What a search needs of the tile's tokens: lane l holds token l's sub-vector and margin, and both
+// B operands (cb = 0: tokens 0 .. 31, cb = 1: tokens 32 .. 63; column = lane % 32) are made of the
+// lanes' own halves by exchanging 32-lane halves between two registers.
 template <int d>
-struct ScreenOperands {
-    f16x8 b1[2], b2[2];
-    float mg[2];
+struct ScreenTokens {
+    float x[d];
+    float mg;          // margin but for the part that depends on the best score
+    float sx2;         // sigma |x|^2
+    f16x8 b[2];
 };
 
-template <int d>
-__device__ __forceinline__ ScreenOperands<d> screen_operands(const float *x_s, int XS, int ch0, const ScreenConsts &k,
-                                                             int h, int col)
+__device__ __forceinline__ unsigned pack2(_Float16 a, _Float16 b)
 {
-    const _Float16 one = (_Float16)1.0f, zero = (_Float16)0.0f;
-    const f16x8 ones = {one, one, zero, zero, zero, zero, zero, zero};
-    const f16x8 zeros = {zero, zero, zero, zero, zero, zero, zero, zero};
-    ScreenOperands<d> o;
+    const f16x2 v = {a, b};
+    return __builtin_bit_cast(unsigned, v);
+}
+
+__device__ __forceinline__ f16x8 as_f16x8(unsigned a, unsigned b, unsigned c, unsigned e)
+{
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = {a, b, c, e};
+    return __builtin_bit_cast(f16x8, v);
+}
+
+// k-slots 0 .. 7 belong to lanes 0 .. 31, 8 .. 15 to lanes 32 .. 63:
+//   d = 2   [ hi0 hi1 1 1 0 0 0 0           | lo0 lo1 0 .. 0            ]
+//   d = 4   [ hi0 .. hi3 1 1 0 0            | lo0 .. lo3 0 .. 0         ]
+//   d = 8   [ hi0 .. hi7                    | 1 1 lo0 .. lo5            ]   (A: [ c0 .. c7 | n n' c0 .. c5 ])
+// v_permlane32_swap(a, b) exchanges the upper half of a with the lower half of b: with a = the lane's
+// word for k-slots 0 .. 7 and b = its word for 8 .. 15, a becomes the word of cb = 0 and b that of cb = 1.
+template <int d>
+__device__ __forceinline__ ScreenTokens<d> screen_tokens(const float *x_s, int XS, int ch0, const ScreenConsts &k, int lane)
+{
+    ScreenTokens<d> o;
+    float l1 = 0.f, l2 = 0.f, dropped = 0.f;
+    _Float16 hi[d], lo[d];
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-        float x[d], l1 = 0.f, l2 = 0.f;
-        _Float16 hi[d], lo[d];
-#pragma unroll
-        for (int j = 0; j < d; ++j) {
-            x[j] = x_s[(32 * cb + col) * XS + ch0 + j];
-            l1 += fabsf(x[j]);
-            l2 = fmaf(x[j], x[j], l2);
-            const float xs = x[j] * k.sigma;
-            hi[j] = (_Float16)xs;
-            lo[j] = (_Float16)(xs - (float)hi[j]);
-        }
-        o.mg[cb] = k.sigma * (0x1p-17f * (l1 * k.cmax + 0.5f * k.nmax) + 0x1p-18f * (l2 + k.nmax)) +
-                   0x1p-13f * ((float)d * k.cmax + 3.0f);
-        f16x8 v;
-        o.b2[cb] = zeros;
-        if constexpr (d == 8) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = h ? lo[j] : hi[j];
-            o.b2[cb] = h ? zeros : ones;
-        } else if constexpr (d == 4) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                v[j] = h ? ones[j] : hi[j];
-                v[4 + j] = h ? zero : lo[j];
-            }
-        } else {
-            v = zeros;
-            v[0] = h ? one : hi[0];
-            v[1] = h ? one : hi[1];
-            v[2] = h ? zero : lo[0];
-            v[3] = h ? zero : lo[1];
-        }
-        o.b1[cb] = v;
+    for (int j = 0; j < d; ++j) {
+        o.x[j] = x_s[lane * XS + ch0 + j];
+        l1 += fabsf(o.x[j]);
+        l2 = fmaf(o.x[j], o.x[j], l2);
+        const float xs = o.x[j] * k.sigma;
+        hi[j] = (_Float16)xs;
+        const float rest = xs - (float)hi[j];
+        lo[j] = (_Float16)rest;
+        if (d == 8 && j >= 6) dropped += fabsf(rest);
     }
+    constexpr float kT = 2.1f * (0x1p-22f + d * 0x1p-24f + 0x1p-22f + (d == 8 ? 16 : 2 * d + 2) * 0x1p-23f);
+    o.mg = k.sigma * kT * (l1 * k.cmax + 0.5f * k.nmax) + 0x1p-13f * ((float)d * k.cmax + 3.0f);
+    if (d == 8) o.mg += 2.1f * dropped * k.cmax;
+    o.sx2 = k.sigma * l2;
+    const unsigned ones = 0x3c003c00u;                      // 1.0, 1.0
+    unsigned a[4], b[4];
+    if constexpr (d == 8) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            a[j] = pack2(hi[2 * j], hi[2 * j + 1]);
+            b[j] = j == 0 ? ones : pack2(lo[2 * j - 2], lo[2 * j - 1]);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < d / 2; ++j) {
+            a[j] = pack2(hi[2 * j], hi[2 * j + 1]);
+            b[j] = pack2(lo[2 * j], lo[2 * j + 1]);
+        }
+    }
+    constexpr int kWords = d == 8 ? 4 : d / 2;              // words that are exchanged
+#pragma unroll
+    for (int j = 0; j < kWords; ++j) {
+        auto sw = __builtin_amdgcn_permlane32_swap(a[j], b[j], false, false);
+        a[j] = sw[0];
+        b[j] = sw[1];
+    }
+    if constexpr (d != 8) {
+        a[d / 2] = b[d / 2] = lane < 32 ? ones : 0u;        // the same in both operands
+#pragma unroll
+        for (int j = d / 2 + 1; j < 4; ++j) a[j] = b[j] = 0u;
+    }
+    o.b[0] = as_f16x8(a[0], a[1], a[2], a[3]);
+    o.b[1] = as_f16x8(b[0], b[1], b[2], b[3]);
     return o;
 }
 
-// Scores of the tile's 64 tokens against the 256 centroids row0 .. row0 + 255 of the codebook at
-// `tab` (plane 1 at tab + plane1), 2 x 32 centroids at a time; out: their maxima per block (MFMA)
-// and per group (accumulator register), for cb = 0, 1.
-// kRolled: the four pairs of blocks as iterations of a real loop (the block maxima move up two
-// places per iteration, so that no register is indexed by the loop counter).  Unrolled, the
-// compiler is free to issue all 16 MFMAs first; inside the chunk loop of a shared codebook it does,
-// and their 256 result registers spill (d8b12 cache fill 7.0 ms against 3.4 ms rolled); for a single
-// chunk (8-bit codes) the unrolled form is 2 - 5 % faster.
-template <int d, bool kRolled = false>
-__device__ __forceinline__ void screen_chunk(const unsigned char *tab, int plane1, int row0, int h, int col,
-                                             const ScreenOperands<d> &o, float (&bm)[2][8], float (&gm)[2][16])
+// A operand of the 32 centroids from `row0`: 16 bytes of the lane's entry.  What lies behind the
+// entry (the next one, or the zeroed spare bytes) meets zeros in the B operand and is finite.
+template <int d>
+__device__ __forceinline__ f16x8 screen_a(const unsigned char *lane_tab, int row0)
 {
-    const _Float16 zero = (_Float16)0.0f;
-    const f16x8 zeros = {zero, zero, zero, zero, zero, zero, zero, zero};
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+    const u32x4 w = *reinterpret_cast<const u32x4 *>(lane_tab + row0 * ScreenTab<d>::kEntry);
+    return __builtin_bit_cast(f16x8, (unsigned __attribute__((ext_vector_type(4))))w);
+}
+
+// This lane's base for screen_a.
+template <int d>
+__device__ __forceinline__ const unsigned char *screen_lane_tab(const unsigned char *tab, int lane)
+{
+    return tab + (lane & 31) * ScreenTab<d>::kEntry + (d == 8 && lane < 32 ? 4 : 0);
+}
+
+// Scores of the tile's 64 tokens against NB x 32 centroids from row0; gm: per accumulator register
+// ("group" of NB centroids) the maximum over the blocks of 32.  A step is two blocks for one of
+// the two operands: two MFMAs and 16 v_max3_f32, which take about as long; the MFMAs of a step are
+// issued ahead of the maxima of the step before, so that the matrix cores and the vector ALU
+// work side by side.  (The fences keep it at that: left alone the compiler issues many more
+// MFMAs first, whose results then spill.)
+template <int d, int NB>
+__device__ __forceinline__ void screen_groups(const unsigned char *lane_tab, int row0, const ScreenTokens<d> &o,
+                                              float (&gm)[2][16])
+{
     const f32x16 z16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // (as a third operand of the first maxima: a plain fmaxf of two MFMA results would quiet both first)
+    const float lowest = opaque(-INFINITY);
+    f32x16 v[2][2];
+    f16x8 a[2], next[2] = {screen_a<d>(lane_tab, row0), screen_a<d>(lane_tab, row0 + 32)};
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) gm[cb][r] = -INFINITY;
-    if constexpr (kRolled) {
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-            for (int r = 0; r < 8; ++r) bm[cb][r] = -INFINITY;
-    }
-    constexpr int kUnroll = kRolled ? 1 : 4;
-#pragma unroll kUnroll
-    for (int rp = 0; rp < 4; ++rp) {
-        f16x8 a1[2], a2[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int row = row0 + 32 * (2 * rp + u) + col;
-            a2[u] = zeros;
-            if constexpr (d == 8) {
-                a1[u] = *reinterpret_cast<const f16x8 *>(tab + row * 16);
-                const f16x2 nn = *reinterpret_cast<const f16x2 *>(tab + plane1 + row * 4);
-                a2[u][0] = nn[0];
-                a2[u][1] = nn[1];
-            } else {
-                // lanes 0-31: the centroid (8 bytes); lanes 32-63: the 4 bytes of plane 1, read as 8.
-                // What lanes 32-63 get beyond their two halves meets zeros in the B operand, and it
-                // is finite (entries of plane 1, or its zeroed spare bytes), so it adds nothing.
-                const f16x4 rd = *reinterpret_cast<const f16x4 *>(tab + (h ? plane1 + row * 4 : row * 8));
-                a1[u] = zeros;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) a1[u][j] = rd[j];
-                if constexpr (d == 4) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) a1[u][4 + j] = rd[j];
-                }
-            }
+    for (int t = 0; t <= NB; ++t) {
+        if (t % 2 == 0) {
+            a[0] = next[0];
+            a[1] = next[1];
+        } else if (t + 1 < NB) {                             // the next pair of blocks' operands, a step ahead
+            next[0] = screen_a<d>(lane_tab, row0 + 32 * (t + 1));
+            next[1] = screen_a<d>(lane_tab, row0 + 32 * (t + 2));
         }
+        if (t < NB) {
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            f32x16 v[2];
+            for (int u = 0; u < 2; ++u) v[t & 1][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u], o.b[t & 1], z16, 0, 0, 0);
+        }
+        if (t > 0) {
+            const int p = (t - 1) & 1;
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                gm[p][r] = fmaxf(fmaxf(t <= 2 ? lowest : gm[p][r], v[p][0][r]), v[p][1][r]);
+        }
+        if (t > 0 && t < NB) {
+            if (t % 2 == 1 && t + 1 < NB) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                v[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1[u], o.b1[cb], z16, 0, 0, 0);
-                if constexpr (d == 8) v[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2[u], o.b2[cb], v[u], 0, 0, 0);
-                float m = fmaxf(v[u][0], v[u][1]);
-#pragma unroll
-                for (int r = 2; r < 16; r += 2) m = fmaxf(fmaxf(m, v[u][r]), v[u][r + 1]);
-                if constexpr (kRolled) {
-                    if (u == 0) {
-#pragma unroll
-                        for (int r = 0; r < 6; ++r) bm[cb][r] = bm[cb][r + 2];
-                    }
-                    bm[cb][6 + u] = m;
-                } else {
-                    bm[cb][2 * rp + u] = m;
-                }
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
             }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) gm[cb][r] = fmaxf(fmaxf(gm[cb][r], v[0][r]), v[1][r]);
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-__device__ __forceinline__ float screen_max8(const float (&bm)[8])
+template <int n>
+__device__ __forceinline__ float max_of(const float (&v)[n])
 {
-    float best = fmaxf(bm[0], bm[1]);
+    float m = n > 1 ? fmaxf(v[0], v[1]) : v[0];
 #pragma unroll
-    for (int r = 2; r < 8; r += 2) best = fmaxf(fmaxf(best, bm[r]), bm[r + 1]);
-    return best;
-}
-
-// A maximum above thr marks its block / group: the sign bit of thr - maximum, shifted into the
-// mask (one subtraction and one v_alignbit each).  Bits 0-7: blocks, bits 8-23: groups.
-__device__ __forceinline__ unsigned screen_marks(const float (&bm)[8], const float (&gm)[16], float thr)
-{
-    unsigned m = 0;
-#pragma unroll
-    for (int r = 15; r >= 0; --r) m = __builtin_amdgcn_alignbit(m, __float_as_uint(thr - gm[r]), 31);
-#pragma unroll
-    for (int r = 7; r >= 0; --r) m = __builtin_amdgcn_alignbit(m, __float_as_uint(thr - bm[r]), 31);
+    for (int r = 2; r + 1 < n; r += 2) m = fmaxf(fmaxf(m, v[r]), v[r + 1]);
+    if (n > 2 && n % 2) m = fmaxf(m, v[n - 1]);
     return m;
 }
 
-// Exact distances of the centroids that `marks` (of the half hh of the wavefront, for the 256
-// centroids from row0) points at; (best, arg) keeps the smallest (distance bits, index).
-template <int d>
-__device__ __forceinline__ void screen_eval(const float (&x)[d], const unsigned char *tab, int row0, unsigned marks,
-                                            int hh, unsigned &best, int &arg)
+// Bit r set where v[r] > thr: the sign bit of thr - v[r], shifted into the mask (one subtraction and
+// one v_alignbit each).
+template <int n>
+__device__ __forceinline__ unsigned marks_above(const float (&v)[n], float thr, unsigned m = 0u)
 {
-    unsigned mb = marks & 0xffu;
-    const unsigned mgp = (marks >> 8) & 0xffffu;
-    while (mb) {
-        const int rb = __builtin_ctz(mb);
-        mb &= mb - 1;
-        unsigned gg = mgp;
-        while (gg) {
-            const int r = __builtin_ctz(gg);
-            gg &= gg - 1;
-            const int c = row0 + 32 * rb + 8 * (r >> 2) + 4 * hh + (r & 3);   // row of register r of block rb
-            const unsigned dist = screen_dist_bits<d>(x, tab, c);
-            if (dist < best || (dist == best && c < arg)) {
-                best = dist;
-                arg = c;
-            }
+#pragma unroll
+    for (int r = n - 1; r >= 0; --r) m = __builtin_amdgcn_alignbit(m, __float_as_uint(thr - v[r]), 31);
+    return m;
+}
+
+// Thresholds (best score - margin) of the two operands' tokens from the lanes' maxima `bm` of both;
+// returns the own token's.
+template <int d>
+__device__ __forceinline__ float screen_thresholds(const float (&bm)[2], const ScreenTokens<d> &o, float (&thr)[2])
+{
+    // own token: its best over the rows of lanes 0 .. 31 and over those of lanes 32 .. 63
+    auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(bm[0]), __float_as_uint(bm[1]), false, false);
+    const float best = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    constexpr float kD = 1.05f * (d + 2) * 0x1p-24f;
+    const float own = best - fmaf(kD, fmaxf(fmaf(-2.0f, best, o.sx2), 0.0f), o.mg);
+    auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(own), __float_as_uint(own), false, false);
+    thr[0] = __uint_as_float(both[0]);
+    thr[1] = __uint_as_float(both[1]);
+    return own;
+}
+
+// Exact distances of the N centroids row, row + 32, .. (row: this lane's): (best, arg) keeps the
+// smallest (distance bits, index).
+template <int d, int N>
+__device__ __forceinline__ void screen_eval(const float (&x)[d], const unsigned char *tab, int row, unsigned &best, int &arg)
+{
+    const unsigned char *const p = tab + row * ScreenTab<d>::kEntry + ScreenTab<d>::kCen;
+    // (channel by channel over all N: independent chains side by side)
+    const float minus1 = opaque(-1.0f);
+    _Float16 cen[N][d];
+    float dist[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        screen_load_centroid<d>(p + i * 32 * ScreenTab<d>::kEntry, cen[i]);
+        dist[i] = 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < d; ++j)
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const float t = fmaf((float)cen[i][j], minus1, x[j]);
+            dist[i] = fmaf(t, t, dist[i]);
         }
+    unsigned v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = __float_as_uint(dist[i]);
+    unsigned m = v[0];
+#pragma unroll
+    for (int i = 1; i < N; ++i) m = v[i] < m ? v[i] : m;
+    int at = N - 1;
+#pragma unroll
+    for (int i = N - 2; i >= 0; --i) at = v[i] == m ? i : at;
+    const int c = row + 32 * at;
+    if (m < best || (m == best && c < arg)) {
+        best = m;
+        arg = c;
     }
 }
 
+// Row (within a block of 32 centroids) of accumulator register r & 15 in lanes 32 (r >> 4) ..
+__device__ __forceinline__ int screen_row(unsigned r)
+{
+    return (int)(8u * ((r >> 2) & 3u) + 4u * ((r >> 4) & 1u) + (r & 3u));
+}
+
 // The wavefront's 64 tokens (rows of x_s, channels ch0 .. ch0 + d) against the sub-space whose
-// tables are `tab`.  Returns the code of token `lane` and the bits of its squared distance; false
-// if the screen marked nothing for some token of the wavefront (the caller then runs the plain
-// search; same for every lane).
+// table is `tab`.  Returns the code of token `lane` and the bits of its squared distance; false
+// if some token of the wavefront has no usable scores (the caller then runs the plain search; same for
+// every lane).
 template <int d>
 __device__ __forceinline__ bool screen_search(const float *x_s, int XS, int ch0, const unsigned char *tab,
                                               const ScreenConsts &k, int lane, int &arg_out, unsigned &best_out)
 {
-    const int h = lane >> 5, col = lane & 31;
-    const ScreenOperands<d> o = screen_operands<d>(x_s, XS, ch0, k, h, col);
-    float bm[2][8], gm[2][16];
-    screen_chunk<d>(tab, ScreenTab<d>::kPlane0, 0, h, col, o, bm, gm);
-    // ---- blocks and groups within the margin of the token's best score (both halves of the wavefront)
-    unsigned mask[2];
-    bool finite[2];                        // the token's scores are numbers: the marks mean something
-#pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-        float best = screen_max8(bm[cb]);
-        best = fmaxf(best, __shfl_xor(best, 32));
-        const float thr = best - o.mg[cb];
-        finite[cb] = fabsf(thr) < INFINITY;
-        mask[cb] = screen_marks(bm[cb], gm[cb], thr);
-    }
-    // token `lane`: the marks of its own half of the rows, and those of the other half
-    const unsigned mine = h ? mask[1] : mask[0];
-    const unsigned other = __shfl_xor(h ? mask[0] : mask[1], 32);
-    // ---- exact distances of the marked centroids
-    float x[d];
-#pragma unroll
-    for (int j = 0; j < d; ++j) x[j] = x_s[lane * XS + ch0 + j];
+    const ScreenTokens<d> o = screen_tokens<d>(x_s, XS, ch0, k, lane);
+    float gm[2][16];
+    screen_groups<d, kCentroids / 32>(screen_lane_tab<d>(tab, lane), 0, o, gm);
+    // ---- groups within the margin of the token's best score
+    const float bm[2] = {max_of(gm[0]), max_of(gm[1])};
+    float thr[2];
+    const float own_thr = screen_thresholds<d>(bm, o, thr);
+    auto sw = __builtin_amdgcn_permlane32_swap(marks_above(gm[0], thr[0]), marks_above(gm[1], thr[1]), false, false);
+    unsigned marks = sw[0] | sw[1] << 16;                   // own token: groups of lanes 0 .. 31, of lanes 32 .. 63
+    // ---- exact distances of the marked groups' centroids.  A lane that has run out of marks while
+    // another has not goes over group 31 (its real distances can only repeat what is known).
     unsigned best = 0x7f800000u;
     int arg = 0;
-    screen_eval<d>(x, tab, 0, mine, h, best, arg);
-    screen_eval<d>(x, tab, 0, other, h ^ 1, best, arg);
+    do {
+        const unsigned r = (unsigned)__builtin_ctz(marks | 0x80000000u);
+        marks &= marks - 1u;
+        screen_eval<d, kCentroids / 32>(o.x, tab, screen_row(r), best, arg);
+    } while (__any(marks != 0u));
     arg_out = arg;
     best_out = best;
     // no screen result for a token whose scaled operands left the fp16 range (infinite or NaN
     // scores), and none where nothing finite was found
-    const bool mine_ok = h ? finite[1] : finite[0];
-    return !__any(best == 0x7f800000u || !mine_ok);
+    return !__any(best >= 0x7f800000u || !(fabsf(own_thr) < INFINITY));
 }
 
-// The same for a codebook of C = 2^b centroids shared by the sub-spaces, 256 centroids (a chunk)
-// at a time.  Each half of the wavefront keeps, per token, the best score it has seen so far and
-// the marks of at most two chunks: a chunk whose best score beats the running best by more than
-// the margin replaces what was kept (nothing kept can still win), one within the margin of it is
-// kept beside it (its marks taken against the better of the two), a third such chunk gives up
-// (plain search for the tile; this needs three chunks within 2^-17 of each other).  Marks are
-// taken against a threshold that only rises, so what is kept is a superset of the centroids
-// within the margin of the final best; at the end a half whose best lies below the other
-// half's threshold drops out.
+// The same for a codebook of C = 2^b centroids shared by the sub-spaces: the centroids are gone through
+// in chunks, and a token keeps, in each half of the wavefront, the maxima of its 16 groups over the
+// whole codebook and the maximum of every chunk.  A score within the margin marks its group and
+// its chunk, so the marked (chunk, group) pairs - normally one - hold every centroid that can win or
+// tie.  (Per chunk of 512 centroids that is 48 vector-ALU instructions on top of the 256 of the maxima
+// themselves; marking groups chunk by chunk took 140 per 256 centroids.)
 template <int d, int C>
 __device__ __forceinline__ bool screen_search_shared(const float *x_s, int XS, int ch0, const unsigned char *tab,
                                                      const ScreenConsts &k, int lane, int &arg_out,
                                                      unsigned &best_out)
 {
-    constexpr int NCH = C / kCentroids;
-    static_assert(NCH >= 1 && NCH <= 64, "chunk index in 7 bits of a mark word");
-    const int h = lane >> 5, col = lane & 31;
-    const ScreenOperands<d> o = screen_operands<d>(x_s, XS, ch0, k, h, col);
-    float run[2] = {-INFINITY, -INFINITY};
-    unsigned s0[2] = {0u, 0u}, s1[2] = {0u, 0u};       // marks | chunk << 24; s1 bit 31: gave up
-#pragma unroll 1
-    for (int ch = 0; ch < NCH; ++ch) {
-        float bm[2][8], gm[2][16];
-        screen_chunk<d, true>(tab, ScreenTab<d, C>::kPlane0, ch * kCentroids, h, col, o, bm, gm);
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            // (the marks are taken for every chunk: in a wavefront of 64 lanes some lane's running
-            // best nearly always moves, and a branch here makes the compiler sink the group maxima
-            // into it, with all 16 MFMA results live until then)
-            const float cbst = screen_max8(bm[cb]);
-            const bool matters = cbst >= run[cb] - o.mg[cb];
-            const float nr = fmaxf(run[cb], cbst);
-            const unsigned m = screen_marks(bm[cb], gm[cb], nr - o.mg[cb]) | ((unsigned)ch << 24);
-            const bool replace = cbst > run[cb] + o.mg[cb];
-            if (matters) {
-                if (replace) {
-                    s0[cb] = m;
-                    s1[cb] = 0u;
-                } else if (s0[cb] == 0u) {
-                    s0[cb] = m;
-                } else if (s1[cb] == 0u) {
-                    s1[cb] = m;
-                } else {
-                    s1[cb] |= 0x80000000u;
-                }
-                run[cb] = nr;
-            }
-        }
-    }
-    bool ok[2];
+    constexpr int NCH = C >= 4096 ? 8 : 4, NB = C / 32 / NCH;     // chunks; blocks of 32 centroids per chunk
+    static_assert(NCH <= 8 && NB % 2 == 0 && NB * NCH * 32 == C, "whole chunks, chunk marks in 8 bits");
+    const ScreenTokens<d> o = screen_tokens<d>(x_s, XS, ch0, k, lane);
+    const unsigned char *const lane_tab = screen_lane_tab<d>(tab, lane);
+    float run[2][16], cm[2][NCH];
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
-        const float thr = fmaxf(run[cb], __shfl_xor(run[cb], 32)) - o.mg[cb];
-        ok[cb] = fabsf(thr) < INFINITY;
-        if (run[cb] < thr) s0[cb] = s1[cb] = 0u;      // nothing in this half's rows reaches the threshold
-    }
-    // token `lane`: what its own half of the rows kept, and what the other half kept
-    const unsigned mine0 = h ? s0[1] : s0[0], mine1 = h ? s1[1] : s1[0];
-    const unsigned other0 = __shfl_xor(h ? s0[0] : s0[1], 32), other1 = __shfl_xor(h ? s1[0] : s1[1], 32);
-    float x[d];
 #pragma unroll
-    for (int j = 0; j < d; ++j) x[j] = x_s[lane * XS + ch0 + j];
+        for (int r = 0; r < 16; ++r) run[cb][r] = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) cm[cb][i] = -INFINITY;
+    }
+#pragma unroll 1
+    for (int ch = 0; ch < NCH; ++ch) {
+        float gm[2][16];
+        screen_groups<d, NB>(lane_tab, ch * NB * 32, o, gm);
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+            // (the chunk maxima move up a place per iteration, so that no register is indexed by ch)
+#pragma unroll
+            for (int i = 0; i + 1 < NCH; ++i) cm[cb][i] = cm[cb][i + 1];
+            cm[cb][NCH - 1] = max_of(gm[cb]);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) run[cb][r] = fmaxf(run[cb][r], gm[cb][r]);
+        }
+    }
+    const float bm[2] = {max_of(cm[0]), max_of(cm[1])};
+    float thr[2];
+    const float own_thr = screen_thresholds<d>(bm, o, thr);
+    unsigned m[2];                                          // groups in bits 0 .. 15, chunks from bit 16
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) m[cb] = marks_above(run[cb], thr[cb], marks_above(cm[cb], thr[cb]));
+    auto sw = __builtin_amdgcn_permlane32_swap(m[0], m[1], false, false);
+    // own token: the marks of lanes 0 .. 31's rows, then those of lanes 32 .. 63's
+    unsigned cur = sw[0], next = sw[1];
+    unsigned half = 0u;
+    if (cur == 0u) {
+        cur = next;
+        next = 0u;
+        half = 16u;
+    }
+    unsigned groups = cur & 0xffffu, chunks = cur >> 16;
     unsigned best = 0x7f800000u;
     int arg = 0;
-    screen_eval<d>(x, tab, (int)((mine0 >> 24) & 0x7fu) * kCentroids, mine0, h, best, arg);
-    screen_eval<d>(x, tab, (int)((mine1 >> 24) & 0x7fu) * kCentroids, mine1, h, best, arg);
-    screen_eval<d>(x, tab, (int)((other0 >> 24) & 0x7fu) * kCentroids, other0, h ^ 1, best, arg);
-    screen_eval<d>(x, tab, (int)((other1 >> 24) & 0x7fu) * kCentroids, other1, h ^ 1, best, arg);
+    do {
+        // (a lane without marks left goes over some pair again: it can only repeat what is known)
+        const unsigned r = (unsigned)__builtin_ctz(groups | 0x8000u), ch = (unsigned)__builtin_ctz(chunks | 1u << (NCH - 1));
+        screen_eval<d, NB>(o.x, tab, (int)ch * NB * 32 + screen_row(r + half), best, arg);
+        groups &= groups - 1u;
+        if (groups == 0u) {
+            chunks &= chunks - 1u;
+            if (chunks == 0u && next != 0u) {
+                cur = next;
+                next = 0u;
+                half = 16u;
+                chunks = cur >> 16;
+            }
+            groups = chunks != 0u ? cur & 0xffffu : 0u;
+        }
+    } while (__any(groups != 0u));
     arg_out = arg;
     best_out = best;
-    const bool mine_ok = (h ? ok[1] : ok[0]) && ((mine1 | other1) & 0x80000000u) == 0u;
-    return !__any(best == 0x7f800000u || !mine_ok);
+    return !__any(best >= 0x7f800000u || !(fabsf(own_thr) < INFINITY));
 }
 
 // One wavefront, one sub-space, the 64 tokens of the tile in x_s: the screen and the exact

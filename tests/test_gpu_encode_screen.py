@@ -113,6 +113,28 @@ def test_keys_with_outliers_full_tile_mix():
     assert_indices_match(got, ref, gap, "keys with outliers")
 
 
+@pytest.mark.parametrize("d", [2, 4, 8])
+def test_many_groups_within_the_margin(d):
+    """Codebooks in which every group of the screen holds centroids at the smallest distance (all
+    centroids equal; 16 vectors repeated with a period that is no multiple of 32), and a NaN and an
+    infinite centroid (no screen for that sub-space, never the nearest): the lowest index must win."""
+    D = 128
+    g = synth.rng(5 + d)
+    M = D // d
+    cb = (g.integers(-6, 7, size=(M, 256, d)) / 2).astype(np.float16)
+    cb[0] = cb[0, :1]
+    cb[1] = cb[1, np.arange(256) % 15]
+    cb[2, 77] = np.float16("nan")
+    cb[2, 78, 0] = np.float16("inf")
+    x = cb[:, g.integers(0, 60, size=T)].transpose(1, 0, 2).astype(np.float32)
+    x = (x + g.integers(-1, 2, size=x.shape) / 4).astype(np.float16).reshape(T, D)
+    shape = synth.Shape(1, 1, 1, D, T, d, d)
+    got, = gpu_encode(shape, v=x[None, None], cb_v=cb[None])
+    with np.errstate(invalid="ignore"):
+        dist = ((x.reshape(T, M, 1, d).astype(np.float64) - cb[None].astype(np.float64)) ** 2).sum(-1)     # exact
+    np.testing.assert_array_equal(got[0, 0], np.nanargmin(dist, -1))
+
+
 # ------------------------------------------------------------------ shared codebooks (10- / 12-bit codes)
 
 def _wide_values_case(D, d, bits, x, cb):
@@ -126,9 +148,9 @@ def _wide_values_case(D, d, bits, x, cb):
 @pytest.mark.parametrize("D,d,bits", [(128, 8, 12), (128, 4, 12), (128, 4, 10), (64, 8, 12), (64, 4, 10)])
 def test_shared_codebook_exact_ties_across_chunks(D, d, bits):
     """A table of 2^b centroids that holds only 40 different vectors on a grid of halves: every
-    token's nearest centroid occurs about 2^b / 40 times, spread over all 256-centroid chunks of the
-    search, all at exactly the same distance.  More than two chunks tie, so the screen gives up and
-    the plain search must return the lowest index."""
+    token's nearest centroid occurs about 2^b / 40 times, spread over all chunks and groups of the
+    search, all at exactly the same distance: every marked (chunk, group) pair has to be gone over and
+    the lowest index returned."""
     g = synth.rng(D + d + bits)
     C = 1 << bits
     M = D // d
