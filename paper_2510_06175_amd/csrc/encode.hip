@@ -144,18 +144,22 @@ constexpr int kVqBlock = 512;
 
 // Sub-spaces per workgroup: all of them for the cache fill (32 at most: d = 2 at D = 128 takes two
 // workgroups per tile), 16 (d = 8: 8) for K-Means, whose sums need 256 (d + 1) floats per sub-space.
-template <int d, bool kAccumulate>
+// A cache fill of few tiles takes smaller groups, which leave fewer compute units idle (launch_typed):
+// kGroup = 8 or 16 instead of 32.
+constexpr int kVqAll = 32;
+
+template <int d, bool kAccumulate, int kGroup>
 constexpr int vq_group(int M)
 {
-    const int most = !kAccumulate ? 32 : (d == 8 ? 8 : 16);
+    const int most = !kAccumulate ? kGroup : (d == 8 ? 8 : 16);
     return M < most ? M : most;
 }
 
-template <int D, int d, bool kAccumulate>
+template <int D, int d, bool kAccumulate, int kGroup>
 constexpr size_t vq_smem_bytes()
 {
-    constexpr int MSW = vq_group<d, kAccumulate>(D / d);
-    constexpr int NCH = kAccumulate ? MSW * d : D;         // channels of the tile kept in LDS
+    constexpr int MSW = vq_group<d, kAccumulate, kGroup>(D / d);
+    constexpr int NCH = kAccumulate || kGroup != kVqAll ? MSW * d : D; // channels of the tile kept in LDS
     return (size_t)MSW * ScreenTab<d>::kBytes + sizeof(float) * kEncTokens * (NCH + 4) + (size_t)kEncTokens * MSW +
            (kAccumulate ? (sizeof(float) * (d + 1) + 1) * MSW * kCentroids : 0);
 }
@@ -167,16 +171,16 @@ struct KmeansState {
     int32_t pad;
 };
 
-template <int D, int d, bool kTransform, bool kAccumulate>
+template <int D, int d, bool kTransform, bool kAccumulate, int kGroup>
 __global__ __launch_bounds__(kVqBlock) void vq_tile_kernel(EncodeParams p, int tiles_per_wg, int iter, KmeansState *state)
 {
     constexpr int M = D / d;
-    constexpr int MSW = vq_group<d, kAccumulate>(M);       // sub-spaces of the workgroup
+    constexpr int MSW = vq_group<d, kAccumulate, kGroup>(M); // sub-spaces of the workgroup
     constexpr int NW = kVqBlock / 64;
     constexpr int SPW = (MSW + NW - 1) / NW;               // sub-spaces per wavefront: 1, 2 or 4
     static_assert(MSW % NW == 0 && M % MSW == 0, "whole groups, dealt evenly to the wavefronts");
-    // K-Means keeps only its group's channels of the tile (the sums need the room)
-    constexpr int NCH = kAccumulate ? MSW * d : D;
+    // K-Means (the sums need the room) and small groups keep only their channels of the tile
+    constexpr int NCH = kAccumulate || kGroup != kVqAll ? MSW * d : D;
     constexpr int XS = NCH + 4;                            // row stride of the transformed tile
     constexpr int TB = ScreenTab<d>::kBytes;
     extern __shared__ __align__(16) unsigned char vq_smem[];
@@ -192,6 +196,9 @@ __global__ __launch_bounds__(kVqBlock) void vq_tile_kernel(EncodeParams p, int t
     const int bg = blockIdx.z, g = bg % p.Hkv;
     const long long tile0 = (long long)blockIdx.x * tiles_per_wg;
 
+    const int win0 = NCH == D ? 0 : grp * MSW * d;         // first channel of the tile that is kept
+    TileRows<D, kVqBlock> rows;                            // (the first tile's rows travel while the tables are built)
+    if (tile0 * kEncTokens < p.T) tile_request<D, kTransform, kVqBlock, NCH>(p, rows, tile0 * kEncTokens, bg, win0);
     // ---- the search tables of this wavefront's sub-spaces (nobody else reads them)
     ScreenConsts sc[SPW];
 #pragma unroll
@@ -203,9 +210,6 @@ __global__ __launch_bounds__(kVqBlock) void vq_tile_kernel(EncodeParams p, int t
         for (int e = tid; e < MSW * kCentroids * (d + 1); e += kVqBlock) acc_s[e] = 0.f;
 
     float err = 0.f;
-    const int win0 = NCH == D ? 0 : grp * MSW * d;         // first channel of the tile that is kept
-    TileRows<D, kVqBlock> rows;
-    if (tile0 * kEncTokens < p.T) tile_request<D, kTransform, kVqBlock, NCH>(p, rows, tile0 * kEncTokens, bg, win0);
     for (int ti = 0; ti < tiles_per_wg; ++ti) {
         const long long t0 = (tile0 + ti) * kEncTokens;
         if (t0 >= p.T) break;
@@ -844,16 +848,16 @@ int launch_encode_wide(const EncodeParams &p, hipStream_t stream)
 // vq_tile_kernel over the T tokens of p: runs long enough that the tables are built a few times per
 // compute unit only (and, for K-Means, that a workgroup meets each centroid many times), short
 // enough that the grid still fills the chip several times over.
-template <int D, int d, bool kAccumulate>
+template <int D, int d, bool kAccumulate, int kGroup = kVqAll>
 int launch_vq_tiles(const EncodeParams &p, int iter, void *state, hipStream_t stream)
 {
-    constexpr int M = D / d, MSW = vq_group<d, kAccumulate>(M);
-    constexpr size_t smem = vq_smem_bytes<D, d, kAccumulate>();
+    constexpr int M = D / d, MSW = vq_group<d, kAccumulate, kGroup>(M);
+    constexpr size_t smem = vq_smem_bytes<D, d, kAccumulate, kGroup>();
     static_assert(smem <= 160 * 1024, "LDS of a compute unit");
     static const bool configured =
-        hipFuncSetAttribute(reinterpret_cast<const void *>(vq_tile_kernel<D, d, true, kAccumulate>),
+        hipFuncSetAttribute(reinterpret_cast<const void *>(vq_tile_kernel<D, d, true, kAccumulate, kGroup>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess &&
-        hipFuncSetAttribute(reinterpret_cast<const void *>(vq_tile_kernel<D, d, false, kAccumulate>),
+        hipFuncSetAttribute(reinterpret_cast<const void *>(vq_tile_kernel<D, d, false, kAccumulate, kGroup>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess;
     if (!configured) return -4;
     const long long tiles = (p.T + kEncTokens - 1) / kEncTokens;
@@ -865,10 +869,10 @@ int launch_vq_tiles(const EncodeParams &p, int iter, void *state, hipStream_t st
     if (per > 256) per = 256;
     dim3 grid((unsigned)((tiles + per - 1) / per), M / MSW, p.B * p.Hkv);
     if (p.lam)
-        hipLaunchKernelGGL((vq_tile_kernel<D, d, true, kAccumulate>), grid, dim3(kVqBlock), smem, stream, p, (int)per, iter,
+        hipLaunchKernelGGL((vq_tile_kernel<D, d, true, kAccumulate, kGroup>), grid, dim3(kVqBlock), smem, stream, p, (int)per, iter,
                            static_cast<KmeansState *>(state));
     else
-        hipLaunchKernelGGL((vq_tile_kernel<D, d, false, kAccumulate>), grid, dim3(kVqBlock), smem, stream, p, (int)per, iter,
+        hipLaunchKernelGGL((vq_tile_kernel<D, d, false, kAccumulate, kGroup>), grid, dim3(kVqBlock), smem, stream, p, (int)per, iter,
                            static_cast<KmeansState *>(state));
     return hipGetLastError() == hipSuccess ? 0 : -4;
 }
@@ -884,6 +888,19 @@ int launch_typed(const EncodeParams &p, hipStream_t stream)
             hipLaunchKernelGGL((encode_token_kernel<D, d, false>), tgrid, dim3(kCentroids), 0, stream, p);
         return hipGetLastError() == hipSuccess ? 0 : -4;
     }
+    // Few tiles (a residual window flushed into the cache, a short prompt): the smallest group of
+    // sub-spaces whose workgroups all run at once.  (A compute unit holds one at a time: two rounds of
+    // small groups take longer than one of large ones.)  D = 128, d = 4, keys / values, us per call:
+    //   tiles x heads    8 per workgroup     16 per workgroup    all 32
+    //        64            8.2 / 5.7               -            15.0 / 13.7
+    //       128           14.7 / 9.8           10.8 / 8.4       15.4 / 13.7
+    //       256           26.6 / 17.6              -            15.9 / 14.2
+    constexpr int M = D / d, all = M < kVqAll ? M : kVqAll;
+    const long long tiles = (p.T + kEncTokens - 1) / kEncTokens * p.B * p.Hkv;
+    if constexpr (all > 8)
+        if (tiles * (M / 8) <= num_cus()) return launch_vq_tiles<D, d, false, 8>(p, 0, nullptr, stream);
+    if constexpr (all > 16)
+        if (tiles * (M / 16) <= num_cus()) return launch_vq_tiles<D, d, false, 16>(p, 0, nullptr, stream);
     return launch_vq_tiles<D, d, false>(p, 0, nullptr, stream);
 }
 

@@ -135,6 +135,30 @@ def test_many_groups_within_the_margin(d):
     np.testing.assert_array_equal(got[0, 0], np.nanargmin(dist, -1))
 
 
+@pytest.mark.parametrize("tiles", [1, 2, 4, 5, 8, 9, 16, 17])
+@pytest.mark.parametrize("D,d,v_tiled", [(128, 4, 1), (128, 4, 0), (128, 2, 1), (128, 8, 1), (64, 4, 1), (64, 2, 0)])
+def test_few_tiles_small_groups(D, d, v_tiled, tiles):
+    """Calls of few tiles hand a workgroup 8 or 16 sub-spaces instead of all (at 8 KV heads and 256
+    compute units the lines lie at tiles = 4 .. 16): ragged lengths on both sides of each line, row
+    offset, keys and values, against the oracle and bit for bit against the same tokens as part of a
+    call that is past every line."""
+    shape = synth.Shape(1, 8, 8, D, 64 * tiles - 13, d, d)
+    e = synth.encode_inputs(shape, seed=D + d + tiles, n_outlier=2)
+    lam = np.stack([oracle.smoothing_factors(e["k"][:, h]) for h in range(shape.Hkv)]).astype(np.float32)
+    pos0, n_cap = 70, 64 * (tiles + 2)
+    big = (64 + tiles - 1) // tiles
+    call = lambda n: gpu_encode(synth.Shape(n, 8, 8, D, shape.N, d, d), k=e["k"].repeat(n, 0), lam=lam, cb_k=e["cb_k"],
+                                v=e["v"].repeat(n, 0), cb_v=e["cb_v"], pos0=pos0, n_cap=n_cap, v_tiled=v_tiled)
+    (k_few, v_few), (k_all, v_all) = call(1), call(big)
+    np.testing.assert_array_equal(k_few[0], k_all[0])       # (rows nobody wrote included)
+    np.testing.assert_array_equal(v_few[0], v_all[0])
+    ref, gap = oracle.encode_keys(e["k"], lam, e["cb_k"], want_gap=True)
+    assert_indices_match(k_few[:, :, pos0:pos0 + shape.N], ref, gap, f"keys D={D} d={d} tiles={tiles}")
+    if not v_tiled:
+        ref, gap = oracle.encode_values(e["v"], e["cb_v"], want_gap=True)
+        assert_indices_match(v_few[:, :, pos0:pos0 + shape.N], ref, gap, f"values D={D} d={d} tiles={tiles}")
+
+
 # ------------------------------------------------------------------ shared codebooks (10- / 12-bit codes)
 
 def _wide_values_case(D, d, bits, x, cb):
