@@ -155,6 +155,13 @@ constexpr int vq_group(int M)
     return M < most ? M : most;
 }
 
+// Wavefronts: 16 (four per SIMD, 128 registers) from 16 sub-spaces on, otherwise 8.
+template <int d, bool kAccumulate, int kGroup>
+constexpr int vq_block(int M)
+{
+    return vq_group<d, kAccumulate, kGroup>(M) >= 16 ? 2 * kVqBlock : kVqBlock;
+}
+
 template <int D, int d, bool kAccumulate, int kGroup>
 constexpr size_t vq_smem_bytes()
 {
@@ -172,17 +179,18 @@ struct KmeansState {
 };
 
 template <int D, int d, bool kTransform, bool kAccumulate, int kGroup>
-__global__ __launch_bounds__(kVqBlock) void vq_tile_kernel(EncodeParams p, int tiles_per_wg, int iter, KmeansState *state)
+__global__ __launch_bounds__((vq_block<d, kAccumulate, kGroup>(D / d))) __attribute__((amdgpu_waves_per_eu(kAccumulate && d == 8 ? 2 : 4))) void vq_tile_kernel(EncodeParams p, int tiles_per_wg, int iter, KmeansState *state)
 {
     constexpr int M = D / d;
     constexpr int MSW = vq_group<d, kAccumulate, kGroup>(M); // sub-spaces of the workgroup
-    constexpr int NW = kVqBlock / 64;
+    constexpr int BLOCK = vq_block<d, kAccumulate, kGroup>(M), NW = BLOCK / 64;
     constexpr int SPW = (MSW + NW - 1) / NW;               // sub-spaces per wavefront: 1, 2 or 4
     static_assert(MSW % NW == 0 && M % MSW == 0, "whole groups, dealt evenly to the wavefronts");
     // K-Means (the sums need the room) and small groups keep only their channels of the tile
     constexpr int NCH = kAccumulate || kGroup != kVqAll ? MSW * d : D;
     constexpr int XS = NCH + 4;                            // row stride of the transformed tile
     constexpr int TB = ScreenTab<d>::kBytes;
+    constexpr int DEPTH = kAccumulate && d == 8 ? 2 : 1;   // (K-Means at d = 8: one workgroup of 8 wavefronts fills the LDS)
     extern __shared__ __align__(16) unsigned char vq_smem[];
     unsigned char *const tab_s = vq_smem;                                          // [MSW] search tables
     float *const x_s = reinterpret_cast<float *>(tab_s + MSW * TB);                // [64][XS] transformed tile
@@ -197,8 +205,8 @@ __global__ __launch_bounds__(kVqBlock) void vq_tile_kernel(EncodeParams p, int t
     const long long tile0 = (long long)blockIdx.x * tiles_per_wg;
 
     const int win0 = NCH == D ? 0 : grp * MSW * d;         // first channel of the tile that is kept
-    TileRows<D, kVqBlock> rows;                            // (the first tile's rows travel while the tables are built)
-    if (tile0 * kEncTokens < p.T) tile_request<D, kTransform, kVqBlock, NCH>(p, rows, tile0 * kEncTokens, bg, win0);
+    TileRows<D, BLOCK> rows;                            // (the first tile's rows travel while the tables are built)
+    if (tile0 * kEncTokens < p.T) tile_request<D, kTransform, BLOCK, NCH>(p, rows, tile0 * kEncTokens, bg, win0);
     // ---- the search tables of this wavefront's sub-spaces (nobody else reads them)
     ScreenConsts sc[SPW];
 #pragma unroll
@@ -207,25 +215,25 @@ __global__ __launch_bounds__(kVqBlock) void vq_tile_kernel(EncodeParams p, int t
         sc[i] = screen_prepare<d>(p.cb + ((size_t)g * M + (size_t)grp * MSW + ms) * kCentroids * d, tab_s + ms * TB, lane);
     }
     if (kAccumulate)
-        for (int e = tid; e < MSW * kCentroids * (d + 1); e += kVqBlock) acc_s[e] = 0.f;
+        for (int e = tid; e < MSW * kCentroids * (d + 1); e += BLOCK) acc_s[e] = 0.f;
 
     float err = 0.f;
     for (int ti = 0; ti < tiles_per_wg; ++ti) {
         const long long t0 = (tile0 + ti) * kEncTokens;
         if (t0 >= p.T) break;
         __syncthreads();                       // previous tile's x_s and idx_s consumed (first tile: accumulators cleared)
-        tile_finish<D, kTransform, kVqBlock, NCH>(p, rows, x_s, g, win0);
+        tile_finish<D, kTransform, BLOCK, NCH>(p, rows, x_s, g, win0);
         __syncthreads();
         // the next tile's rows travel while this one is searched
         if (ti + 1 < tiles_per_wg && t0 + kEncTokens < p.T)
-            tile_request<D, kTransform, kVqBlock, NCH>(p, rows, t0 + kEncTokens, bg, win0);
+            tile_request<D, kTransform, BLOCK, NCH>(p, rows, t0 + kEncTokens, bg, win0);
 #pragma unroll
         for (int i = 0; i < SPW; ++i) {
             const int ms = wave + NW * i;
             const int ch0 = (NCH == D ? grp * MSW + ms : ms) * d;
             int arg;
             unsigned best;
-            search_tile<d>(x_s, XS, ch0, tab_s + ms * TB, sc[i], lane, arg, best);
+            search_tile<d, kCentroids, DEPTH>(x_s, XS, ch0, tab_s + ms * TB, sc[i], lane, arg, best);
             idx_s[lane * MSW + ms] = (uint8_t)arg;
             if (kAccumulate && t0 + lane < p.T) {
                 // The accumulators of a sub-space belong to this wavefront alone, and its LDS
@@ -255,7 +263,7 @@ __global__ __launch_bounds__(kVqBlock) void vq_tile_kernel(EncodeParams p, int t
         __syncthreads();
         // ---- the group's MSW code bytes of each token
         if (!kAccumulate && p.tiled) {
-            for (int e = tid; e < kEncTokens * MSW; e += kVqBlock) {
+            for (int e = tid; e < kEncTokens * MSW; e += BLOCK) {
                 const int tl = e / MSW, m = grp * MSW + (e - tl * MSW);
                 const long long t = t0 + tl;
                 if (t < p.T) p.idx[(size_t)bg * p.n_cap * M + v_tiled_offset(p.pos0 + t, m, M)] = idx_s[e];
@@ -275,7 +283,7 @@ __global__ __launch_bounds__(kVqBlock) void vq_tile_kernel(EncodeParams p, int t
     if constexpr (kAccumulate) {
         __syncthreads();
         // the run's partial sums -> memory
-        for (int e = tid; e < MSW * kCentroids; e += kVqBlock) {
+        for (int e = tid; e < MSW * kCentroids; e += BLOCK) {
             const float *a = acc_s + (size_t)e * (d + 1);
             const int n = (int)a[d];
             if (n > 0) {
@@ -795,6 +803,30 @@ int launch_append_wide(const EncodeParams &pk, const EncodeParams &pv, hipStream
     return -2;
 }
 
+// Tiles per workgroup of the tile kernels, for `tiles` tiles of each of `groups` (sequence, KV head,
+// sub-space group)s.  A compute unit holds one workgroup at a time, so what the launch takes is the
+// number of rounds of workgroups times a run, and a run is its tiles plus `setup`: the search tables
+// (and, for K-Means, the flush of the sums), in tiles.  The least of that over 1 .. 8 rounds.
+long long tile_run(long long tiles, long long groups, double setup)
+{
+    const long long cus = num_cus();
+    long long best_per = tiles < 256 ? tiles : 256;
+    double best = 1e300;
+    for (int r = 1; r <= 8; ++r) {
+        const long long runs = r * cus / groups;                // runs of a group that fit r rounds
+        if (runs < 1) continue;
+        long long per = (tiles + runs - 1) / runs;
+        if (per > 256) per = 256;
+        const long long rounds = ((tiles + per - 1) / per * groups + cus - 1) / cus;
+        const double cost = rounds * (per + setup);
+        if (cost < best) {
+            best = cost;
+            best_per = per;
+        }
+    }
+    return best_per;
+}
+
 template <int D, int d, int BITS>
 int launch_wide_typed(const EncodeParams &p, hipStream_t stream)
 {
@@ -816,11 +848,8 @@ int launch_wide_typed(const EncodeParams &p, hipStream_t stream)
         hipFuncSetAttribute(reinterpret_cast<const void *>(vq_tile_wide_kernel<D, d, BITS, false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess;
     if (!configured) return -4;
-    // runs: the tables are built a few times per compute unit only, the grid still fills the chip
     const long long tiles = (p.T + kEncTokens - 1) / kEncTokens;
-    long long per = tiles * p.B * p.Hkv / (4LL * num_cus());
-    if (per < 1) per = 1;
-    if (per > 256) per = 256;
+    const long long per = tile_run(tiles, (long long)p.B * p.Hkv, 0.1);
     dim3 grid((unsigned)((tiles + per - 1) / per), 1, p.B * p.Hkv);
     const size_t smem_now = p.km_sums ? smem : smem_fill;     // (the partial sums only where they are used)
     if (p.lam)
@@ -845,9 +874,7 @@ int launch_encode_wide(const EncodeParams &p, hipStream_t stream)
     }
 }
 
-// vq_tile_kernel over the T tokens of p: runs long enough that the tables are built a few times per
-// compute unit only (and, for K-Means, that a workgroup meets each centroid many times), short
-// enough that the grid still fills the chip several times over.
+// vq_tile_kernel over the T tokens of p.
 template <int D, int d, bool kAccumulate, int kGroup = kVqAll>
 int launch_vq_tiles(const EncodeParams &p, int iter, void *state, hipStream_t stream)
 {
@@ -861,18 +888,15 @@ int launch_vq_tiles(const EncodeParams &p, int iter, void *state, hipStream_t st
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess;
     if (!configured) return -4;
     const long long tiles = (p.T + kEncTokens - 1) / kEncTokens;
-    const long long groups = (long long)(M / MSW) * p.B * p.Hkv;
-    // (K-Means: one workgroup per compute unit where the input allows, so that the partial sums are
-    // flushed as rarely as possible: 21 M global atomics per iteration at 65536 x 8 tokens with four)
-    long long per = tiles * groups / ((kAccumulate ? 1LL : 4LL) * num_cus());
-    if (per < 1) per = 1;
-    if (per > 256) per = 256;
+    constexpr int block = vq_block<d, kAccumulate, kGroup>(M);
+    // (K-Means: a run ends with the partial sums' flush, and a long run meets each centroid many times)
+    const long long per = tile_run(tiles, (long long)(M / MSW) * p.B * p.Hkv, kAccumulate ? 2.0 : 0.5);
     dim3 grid((unsigned)((tiles + per - 1) / per), M / MSW, p.B * p.Hkv);
     if (p.lam)
-        hipLaunchKernelGGL((vq_tile_kernel<D, d, true, kAccumulate, kGroup>), grid, dim3(kVqBlock), smem, stream, p, (int)per, iter,
+        hipLaunchKernelGGL((vq_tile_kernel<D, d, true, kAccumulate, kGroup>), grid, dim3(block), smem, stream, p, (int)per, iter,
                            static_cast<KmeansState *>(state));
     else
-        hipLaunchKernelGGL((vq_tile_kernel<D, d, false, kAccumulate, kGroup>), grid, dim3(kVqBlock), smem, stream, p, (int)per, iter,
+        hipLaunchKernelGGL((vq_tile_kernel<D, d, false, kAccumulate, kGroup>), grid, dim3(block), smem, stream, p, (int)per, iter,
                            static_cast<KmeansState *>(state));
     return hipGetLastError() == hipSuccess ? 0 : -4;
 }

@@ -74,6 +74,12 @@ struct ScreenConsts {
     float sigma, cmax, nmax;
 };
 
+// A value that every lane holds, in a scalar register.
+__device__ __forceinline__ float uniform(float v)
+{
+    return __uint_as_float((unsigned)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v)));
+}
+
 __device__ __forceinline__ float wave_max(float v)
 {
 #pragma unroll
@@ -140,7 +146,7 @@ __device__ __forceinline__ ScreenConsts screen_prepare(const __half *src, unsign
 #pragma unroll
     for (int i = 0; i < 4; ++i) screen_store_norm<d>(tab, lane + 64 * i, sigma, n[i]);
     if (lane < 4) *reinterpret_cast<unsigned *>(tab + ScreenTab<d>::kBytes - 16 + 4 * lane) = 0u;   // the spare bytes
-    return ScreenConsts{sigma, cm, nm};
+    return ScreenConsts{uniform(sigma), uniform(cm), uniform(nm)};
 }
 
 // Tables of a shared codebook `src` [C][d] fp16, built by the whole workgroup of BLOCK threads
@@ -174,7 +180,7 @@ __device__ __forceinline__ ScreenConsts screen_prepare_shared(const __half *src,
     for (int i = 0; i < PER; ++i) screen_store_norm<d>(tab, tid + BLOCK * i, sigma, n[i]);
     if (tid < 4) *reinterpret_cast<unsigned *>(tab + ScreenTab<d, C>::kBytes - 16 + 4 * tid) = 0u;        // the spare bytes
     __syncthreads();
-    return ScreenConsts{sigma, cm, nm};
+    return ScreenConsts{uniform(sigma), uniform(cm), uniform(nm)};
 }
 
 // The fp16 centroid at p (4-byte aligned).
@@ -351,17 +357,39 @@ __device__ __forceinline__ const unsigned char *screen_lane_tab(const unsigned c
 
 // Scores of the tile's 64 tokens against NB x 32 centroids from row0; gm: per accumulator register
 // ("group" of NB centroids) the maximum over the blocks of 32.  A step is two blocks for one of
-// the two operands: two MFMAs and 16 v_max3_f32, which take about as long; the MFMAs of a step are
-// issued ahead of the maxima of the step before, so that the matrix cores and the vector ALU
-// work side by side.  (The fences keep it at that: left alone the compiler issues many more
-// MFMAs first, whose results then spill.)
-template <int d, int NB>
+// the two operands: two MFMAs and 16 v_max3_f32, which take about as long.
+// DEPTH = 2 (workgroups that leave a SIMD two wavefronts): the MFMAs of a step are issued ahead of the
+// maxima of the step before, so that the matrix cores and the vector ALU work side by side within
+// the wavefront.  DEPTH = 1 (four wavefronts per SIMD, which do that among themselves): one set of
+// results, 32 registers less, which is what lets the kernel stay within 128.
+// (The fences keep it at that: left alone the compiler issues many more MFMAs first, whose
+// results then spill.)
+template <int d, int NB, int DEPTH>
 __device__ __forceinline__ void screen_groups(const unsigned char *lane_tab, int row0, const ScreenTokens<d> &o,
                                               float (&gm)[2][16])
 {
     const f32x16 z16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     // (as a third operand of the first maxima: a plain fmaxf of two MFMA results would quiet both first)
     const float lowest = opaque(-INFINITY);
+    if constexpr (DEPTH == 1) {
+        f16x8 a[2] = {screen_a<d>(lane_tab, row0), screen_a<d>(lane_tab, row0 + 32)};
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            f32x16 v[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) v[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u], o.b[t & 1], z16, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (t % 2 == 1 && t + 1 < NB) {                  // the next pair of blocks' operands
+                a[0] = screen_a<d>(lane_tab, row0 + 32 * (t + 1));
+                a[1] = screen_a<d>(lane_tab, row0 + 32 * (t + 2));
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                gm[t & 1][r] = fmaxf(fmaxf(t < 2 ? lowest : gm[t & 1][r], v[0][r]), v[1][r]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return;
+    }
     f32x16 v[2][2];
     f16x8 a[2], next[2] = {screen_a<d>(lane_tab, row0), screen_a<d>(lane_tab, row0 + 32)};
 #pragma unroll
@@ -479,13 +507,13 @@ __device__ __forceinline__ int screen_row(unsigned r)
 // table is `tab`.  Returns the code of token `lane` and the bits of its squared distance; false
 // if some token of the wavefront has no usable scores (the caller then runs the plain search; same for
 // every lane).
-template <int d>
+template <int d, int DEPTH>
 __device__ __forceinline__ bool screen_search(const float *x_s, int XS, int ch0, const unsigned char *tab,
                                               const ScreenConsts &k, int lane, int &arg_out, unsigned &best_out)
 {
     const ScreenTokens<d> o = screen_tokens<d>(x_s, XS, ch0, k, lane);
     float gm[2][16];
-    screen_groups<d, kCentroids / 32>(screen_lane_tab<d>(tab, lane), 0, o, gm);
+    screen_groups<d, kCentroids / 32, DEPTH>(screen_lane_tab<d>(tab, lane), 0, o, gm);
     // ---- groups within the margin of the token's best score
     const float bm[2] = {max_of(gm[0]), max_of(gm[1])};
     float thr[2];
@@ -534,7 +562,7 @@ __device__ __forceinline__ bool screen_search_shared(const float *x_s, int XS, i
 #pragma unroll 1
     for (int ch = 0; ch < NCH; ++ch) {
         float gm[2][16];
-        screen_groups<d, NB>(lane_tab, ch * NB * 32, o, gm);
+        screen_groups<d, NB, 2>(lane_tab, ch * NB * 32, o, gm);
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
             // (the chunk maxima move up a place per iteration, so that no register is indexed by ch)
@@ -586,12 +614,12 @@ __device__ __forceinline__ bool screen_search_shared(const float *x_s, int XS, i
 
 // One wavefront, one sub-space, the 64 tokens of the tile in x_s: the screen and the exact
 // distances of what it marks; the plain search when the screen gives no answer.
-template <int d, int C = kCentroids>
+template <int d, int C = kCentroids, int DEPTH = 2>
 __device__ __forceinline__ void search_tile(const float *x_s, int XS, int ch0, const unsigned char *tab,
                                             const ScreenConsts &k, int lane, int &arg, unsigned &best)
 {
     if constexpr (C == kCentroids) {
-        if (screen_search<d>(x_s, XS, ch0, tab, k, lane, arg, best)) return;
+        if (screen_search<d, DEPTH>(x_s, XS, ch0, tab, k, lane, arg, best)) return;
     } else {
         if (screen_search_shared<d, C>(x_s, XS, ch0, tab, k, lane, arg, best)) return;
     }
