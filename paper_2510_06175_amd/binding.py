@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 from dataclasses import dataclass
+from functools import cached_property
 
 import torch
 
@@ -53,6 +54,34 @@ class Config:
     def c(self) -> _Cfg:
         return _Cfg(self.head_dim, self.num_q_heads, self.num_kv_heads, self.k_sub_dim,
                     self.v_sub_dim, self.k_bits, self.v_bits, self.v_tiled)
+
+    # What every call needs of a configuration, worked out once per (immutable) object.
+    @cached_property
+    def _c(self) -> _Cfg:
+        return self.c()
+
+    @cached_property
+    def _lam_shape(self) -> tuple:
+        return (self.num_kv_heads, self.head_dim)
+
+    @cached_property
+    def _cb_k(self) -> tuple:
+        return self.cb_shape(True)
+
+    @cached_property
+    def _cb_v(self) -> tuple:
+        return self.cb_shape(False)
+
+    @cached_property
+    def _row_k(self) -> int:
+        return self.row_bytes(True)
+
+    @cached_property
+    def _row_v(self) -> int:
+        return self.row_bytes(False)
+
+    def __getstate__(self):                 # (pickles and copies carry the fields alone)
+        return {f: self.__dict__[f] for f in self.__dataclass_fields__}
 
     def cb_shape(self, keys: bool) -> tuple:
         """Codebook tensor shape: one 256-entry table per (KV head, sub-space) for 8-bit codes, one
@@ -146,17 +175,21 @@ def _check(rc: int) -> None:
         raise VecInferError(rc)
 
 
+# The current stream's handle without a Stream object around it, where this torch offers that.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: torch.cuda.current_stream(dev).cuda_stream)
+
+
 def _dev(t: torch.Tensor, dtype, shape, name: str) -> int:
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and t.shape == shape and t.is_contiguous():
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name}: expected a tensor on the GPU")
-    if t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous():
-        raise ValueError(f"{name}: expected contiguous {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
-    return t.data_ptr()
+    raise ValueError(f"{name}: expected contiguous {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
 
 
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -165,10 +198,10 @@ def vecinfer_encode_keys(cfg: Config, k_f16, lam, cb_k, k_idx, pos0: int = 0, st
     B, Hkv, T, D = k_f16.shape
     n_cap = k_idx.shape[2]
     _check(lib().vecinfer_encode_keys(
-        C.byref(cfg.c()), _dev(k_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "k_f16"),
-        _dev(lam, torch.float32, (cfg.num_kv_heads, cfg.head_dim), "lambda"),
-        _dev(cb_k, torch.float16, cfg.cb_shape(True), "cb_k"),
-        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(True)), "k_idx"),
+        C.byref(cfg._c), _dev(k_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "k_f16"),
+        _dev(lam, torch.float32, cfg._lam_shape, "lambda"),
+        _dev(cb_k, torch.float16, cfg._cb_k, "cb_k"),
+        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_k), "k_idx"),
         B, T, pos0, n_cap, _stream(stream)))
 
 
@@ -177,9 +210,9 @@ def vecinfer_encode_values(cfg: Config, v_f16, cb_v, v_idx, pos0: int = 0, strea
     B, Hkv, T, D = v_f16.shape
     n_cap = v_idx.shape[2]
     _check(lib().vecinfer_encode_values(
-        C.byref(cfg.c()), _dev(v_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "v_f16"),
-        _dev(cb_v, torch.float16, cfg.cb_shape(False), "cb_v"),
-        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(False)), "v_idx"),
+        C.byref(cfg._c), _dev(v_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "v_f16"),
+        _dev(cb_v, torch.float16, cfg._cb_v, "cb_v"),
+        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_v), "v_idx"),
         B, T, pos0, n_cap, _stream(stream)))
 
 
@@ -188,22 +221,22 @@ def vecinfer_append_kv(cfg: Config, k_f16, v_f16, lam, cb_k, cb_v, k_idx, v_idx,
     B, Hkv, T, D = k_f16.shape
     n_cap = k_idx.shape[2]
     _check(lib().vecinfer_append_kv(
-        C.byref(cfg.c()), _dev(k_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "k_f16"),
+        C.byref(cfg._c), _dev(k_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "k_f16"),
         _dev(v_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "v_f16"),
-        _dev(lam, torch.float32, (cfg.num_kv_heads, cfg.head_dim), "lambda"),
-        _dev(cb_k, torch.float16, cfg.cb_shape(True), "cb_k"),
-        _dev(cb_v, torch.float16, cfg.cb_shape(False), "cb_v"),
-        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(True)), "k_idx"),
-        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(False)), "v_idx"),
+        _dev(lam, torch.float32, cfg._lam_shape, "lambda"),
+        _dev(cb_k, torch.float16, cfg._cb_k, "cb_k"),
+        _dev(cb_v, torch.float16, cfg._cb_v, "cb_v"),
+        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_k), "k_idx"),
+        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_v), "v_idx"),
         B, T, pos0, n_cap, _stream(stream)))
 
 
 def vecinfer_decode_auto_splits(cfg: Config, B: int, N: int) -> int:
-    return int(lib().vecinfer_decode_auto_splits(C.byref(cfg.c()), B, N))
+    return int(lib().vecinfer_decode_auto_splits(C.byref(cfg._c), B, N))
 
 
 def vecinfer_decode_workspace_bytes(cfg: Config, B: int, N: int, num_splits: int = 0) -> int:
-    return int(lib().vecinfer_decode_workspace_bytes(C.byref(cfg.c()), B, N, num_splits))
+    return int(lib().vecinfer_decode_workspace_bytes(C.byref(cfg._c), B, N, num_splits))
 
 
 def new_workspace(cfg: Config, B: int, N: int, num_splits: int = 0, device="cuda") -> torch.Tensor:
@@ -222,12 +255,12 @@ def vecinfer_decode_attention(cfg: Config, q_f16, lam, cb_k, cb_v, k_idx, v_idx,
     n_cap = k_idx.shape[2]
     N = n_cap if N is None else N
     _check(lib().vecinfer_decode_attention(
-        C.byref(cfg.c()), _dev(q_f16, torch.float16, (B, cfg.num_q_heads, cfg.head_dim), "q_f16"),
-        _dev(lam, torch.float32, (cfg.num_kv_heads, cfg.head_dim), "lambda"),
-        _dev(cb_k, torch.float16, cfg.cb_shape(True), "cb_k"),
-        _dev(cb_v, torch.float16, cfg.cb_shape(False), "cb_v"),
-        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(True)), "k_idx"),
-        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(False)), "v_idx"),
+        C.byref(cfg._c), _dev(q_f16, torch.float16, (B, cfg.num_q_heads, cfg.head_dim), "q_f16"),
+        _dev(lam, torch.float32, cfg._lam_shape, "lambda"),
+        _dev(cb_k, torch.float16, cfg._cb_k, "cb_k"),
+        _dev(cb_v, torch.float16, cfg._cb_v, "cb_v"),
+        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_k), "k_idx"),
+        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_v), "v_idx"),
         None if seq_lens is None else _dev(seq_lens, torch.int32, (B,), "seq_lens"),
         B, N, n_cap, num_splits, variant, workspace.data_ptr(), workspace.numel() * workspace.element_size(),
         _dev(out_f16, torch.float16, (B, cfg.num_q_heads, cfg.head_dim), "out_f16"),
@@ -247,12 +280,12 @@ def vecinfer_decode_attention_static(cfg: Config, q_f16, lam, cb_k, cb_v, k_idx,
     n_cap = k_idx.shape[2]
     N = n_cap if N is None else N
     _check(lib().vecinfer_decode_attention_static(
-        C.byref(cfg.c()), _dev(q_f16, torch.float16, (B, cfg.num_q_heads, cfg.head_dim), "q_f16"),
-        _dev(lam, torch.float32, (cfg.num_kv_heads, cfg.head_dim), "lambda"),
-        _dev(cb_k, torch.float16, cfg.cb_shape(True), "cb_k"),
-        _dev(cb_v, torch.float16, cfg.cb_shape(False), "cb_v"),
-        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(True)), "k_idx"),
-        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(False)), "v_idx"),
+        C.byref(cfg._c), _dev(q_f16, torch.float16, (B, cfg.num_q_heads, cfg.head_dim), "q_f16"),
+        _dev(lam, torch.float32, cfg._lam_shape, "lambda"),
+        _dev(cb_k, torch.float16, cfg._cb_k, "cb_k"),
+        _dev(cb_v, torch.float16, cfg._cb_v, "cb_v"),
+        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_k), "k_idx"),
+        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_v), "v_idx"),
         None if seq_lens is None else _dev(seq_lens, torch.int32, (B,), "seq_lens"),
         B, N, n_cap, num_splits, variant,
         _dev(out_f16, torch.float16, (B, cfg.num_q_heads, cfg.head_dim), "out_f16"),
@@ -271,12 +304,12 @@ def vecinfer_decode_attention_residual(cfg: Config, q_f16, lam, cb_k, cb_v, k_id
     r_cap = k_res.shape[2]
     R = r_cap if R is None else R
     _check(lib().vecinfer_decode_attention_residual(
-        C.byref(cfg.c()), _dev(q_f16, torch.float16, (B, cfg.num_q_heads, cfg.head_dim), "q_f16"),
-        _dev(lam, torch.float32, (cfg.num_kv_heads, cfg.head_dim), "lambda"),
-        _dev(cb_k, torch.float16, cfg.cb_shape(True), "cb_k"),
-        _dev(cb_v, torch.float16, cfg.cb_shape(False), "cb_v"),
-        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(True)), "k_idx"),
-        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(False)), "v_idx"),
+        C.byref(cfg._c), _dev(q_f16, torch.float16, (B, cfg.num_q_heads, cfg.head_dim), "q_f16"),
+        _dev(lam, torch.float32, cfg._lam_shape, "lambda"),
+        _dev(cb_k, torch.float16, cfg._cb_k, "cb_k"),
+        _dev(cb_v, torch.float16, cfg._cb_v, "cb_v"),
+        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_k), "k_idx"),
+        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_v), "v_idx"),
         None if seq_lens is None else _dev(seq_lens, torch.int32, (B,), "seq_lens"),
         B, N, n_cap,
         _dev(k_res, torch.float16, (B, cfg.num_kv_heads, r_cap, cfg.head_dim), "k_res"),
@@ -296,14 +329,14 @@ def vecinfer_decode_step(cfg: Config, q_f16, k_new, v_new, lam, cb_k, cb_v, k_id
     n_cap = k_idx.shape[2]
     N = n_cap if N is None else N
     _check(lib().vecinfer_decode_step(
-        C.byref(cfg.c()), _dev(q_f16, torch.float16, (B, cfg.num_q_heads, cfg.head_dim), "q_f16"),
+        C.byref(cfg._c), _dev(q_f16, torch.float16, (B, cfg.num_q_heads, cfg.head_dim), "q_f16"),
         _dev(k_new, torch.float16, (B, cfg.num_kv_heads, 1, cfg.head_dim), "k_new"),
         _dev(v_new, torch.float16, (B, cfg.num_kv_heads, 1, cfg.head_dim), "v_new"),
-        _dev(lam, torch.float32, (cfg.num_kv_heads, cfg.head_dim), "lambda"),
-        _dev(cb_k, torch.float16, cfg.cb_shape(True), "cb_k"),
-        _dev(cb_v, torch.float16, cfg.cb_shape(False), "cb_v"),
-        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(True)), "k_idx"),
-        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(False)), "v_idx"),
+        _dev(lam, torch.float32, cfg._lam_shape, "lambda"),
+        _dev(cb_k, torch.float16, cfg._cb_k, "cb_k"),
+        _dev(cb_v, torch.float16, cfg._cb_v, "cb_v"),
+        _dev(k_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_k), "k_idx"),
+        _dev(v_idx, torch.uint8, (B, cfg.num_kv_heads, n_cap, cfg._row_v), "v_idx"),
         None if seq_lens is None else _dev(seq_lens, torch.int32, (B,), "seq_lens"),
         B, N, n_cap, num_splits, variant, workspace.data_ptr(), workspace.numel() * workspace.element_size(),
         _dev(out_f16, torch.float16, (B, cfg.num_q_heads, cfg.head_dim), "out_f16"),
@@ -312,11 +345,11 @@ def vecinfer_decode_step(cfg: Config, q_f16, k_new, v_new, lam, cb_k, cb_v, k_id
 
 
 def vecinfer_index_row_bytes(cfg: Config, keys: bool) -> int:
-    return int(lib().vecinfer_index_row_bytes(C.byref(cfg.c()), 1 if keys else 0))
+    return int(lib().vecinfer_index_row_bytes(C.byref(cfg._c), 1 if keys else 0))
 
 
 def vecinfer_codebook_elems(cfg: Config, keys: bool) -> int:
-    return int(lib().vecinfer_codebook_elems(C.byref(cfg.c()), 1 if keys else 0))
+    return int(lib().vecinfer_codebook_elems(C.byref(cfg._c), 1 if keys else 0))
 
 
 LAMBDA_FLOOR = 1e-5
@@ -326,16 +359,16 @@ def vecinfer_calibrate_lambda(cfg: Config, k_f16, lam, stream=None) -> None:
     """Eq. 4: lam [Hkv, D] = sqrt(max |k|) over all tokens of k_f16 [B, Hkv, T, D], floored at LAMBDA_FLOOR."""
     B, Hkv, T, D = k_f16.shape
     _check(lib().vecinfer_calibrate_lambda(
-        C.byref(cfg.c()), _dev(k_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "k_f16"),
-        _dev(lam, torch.float32, (cfg.num_kv_heads, cfg.head_dim), "lambda"), B, T, _stream(stream)))
+        C.byref(cfg._c), _dev(k_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "k_f16"),
+        _dev(lam, torch.float32, cfg._lam_shape, "lambda"), B, T, _stream(stream)))
 
 
 def vecinfer_export_value_codes(cfg: Config, v_idx_tiled, v_idx_rows, N: int | None = None, stream=None) -> None:
     """Rows form [B, Hkv, n_cap, M_v] (rows 0 .. N-1) of a value code cache kept in the tiled layout."""
     B, n_cap = v_idx_rows.shape[0], v_idx_rows.shape[2]
-    shape = (B, cfg.num_kv_heads, n_cap, cfg.row_bytes(False))
+    shape = (B, cfg.num_kv_heads, n_cap, cfg._row_v)
     _check(lib().vecinfer_export_value_codes(
-        C.byref(cfg.c()), _dev(v_idx_tiled, torch.uint8, shape, "v_idx_tiled"),
+        C.byref(cfg._c), _dev(v_idx_tiled, torch.uint8, shape, "v_idx_tiled"),
         _dev(v_idx_rows, torch.uint8, shape, "v_idx_rows"), B, n_cap if N is None else N, n_cap, _stream(stream)))
 
 
@@ -348,7 +381,7 @@ def vecinfer_read_probe(src, sink, stream=None) -> None:
 
 
 def vecinfer_kmeans_workspace_bytes(cfg: Config, keys: bool) -> int:
-    return int(lib().vecinfer_kmeans_workspace_bytes(C.byref(cfg.c()), 1 if keys else 0))
+    return int(lib().vecinfer_kmeans_workspace_bytes(C.byref(cfg._c), 1 if keys else 0))
 
 
 def new_kmeans_workspace(cfg: Config, keys: bool, device="cuda") -> torch.Tensor:
@@ -364,8 +397,8 @@ def vecinfer_kmeans_step(cfg: Config, x_f16, lam, cb_in, cb_out, codes, workspac
     ws = workspace
     cb_shape = cfg.cb_shape(keys)
     _check(lib().vecinfer_kmeans_step(
-        C.byref(cfg.c()), _dev(x_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "x_f16"),
-        None if lam is None else _dev(lam, torch.float32, (cfg.num_kv_heads, cfg.head_dim), "lambda"),
+        C.byref(cfg._c), _dev(x_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "x_f16"),
+        None if lam is None else _dev(lam, torch.float32, cfg._lam_shape, "lambda"),
         _dev(cb_in, torch.float16, cb_shape, "cb_in"),
         _dev(cb_out, torch.float16, cb_shape, "cb_out"),
         _dev(codes, torch.uint8, (B, cfg.num_kv_heads, T, cfg.row_bytes(keys)), "codes"),
@@ -384,8 +417,8 @@ def vecinfer_kmeans_train(cfg: Config, x_f16, lam, cb, codes, workspace, counts=
     keys = lam is not None
     cb_shape = cfg.cb_shape(keys)
     _check(lib().vecinfer_kmeans_train(
-        C.byref(cfg.c()), _dev(x_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "x_f16"),
-        None if lam is None else _dev(lam, torch.float32, (cfg.num_kv_heads, cfg.head_dim), "lambda"),
+        C.byref(cfg._c), _dev(x_f16, torch.float16, (B, cfg.num_kv_heads, T, cfg.head_dim), "x_f16"),
+        None if lam is None else _dev(lam, torch.float32, cfg._lam_shape, "lambda"),
         _dev(cb, torch.float16, cb_shape, "cb"),
         _dev(codes, torch.uint8, (B, cfg.num_kv_heads, T, cfg.row_bytes(keys)), "codes"),
         None if counts is None else _dev(counts, torch.int32, cb_shape[:-1], "counts"),
