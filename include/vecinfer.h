@@ -247,8 +247,11 @@ int32_t vecinfer_decode_auto_splits(const vecinfer_cfg *cfg, int32_t B, int64_t 
 
 /*
  * Bytes of workspace vecinfer_decode_attention needs for batch B, up to N tokens and
- * `num_splits` splits (0 = whatever vecinfer_decode_auto_splits returns for (B, N)).
+ * `num_splits` splits (0 = what vecinfer_decode_auto_splits returns for (B, N), or the two or three
+ * splits that a short sequence with a residual window takes instead of one).
  * N = 0 (only meaningful for vecinfer_decode_attention_residual) gives the one-split size.
+ * With num_splits = 0 the decode calls also run in less than that, with fewer splits, down to splits
+ * of 1024 tokens.
  * Host-only.  Returns 0 for an invalid cfg or negative sizes.
  */
 size_t vecinfer_decode_workspace_bytes(const vecinfer_cfg *cfg, int32_t B, int64_t N,
@@ -294,7 +297,9 @@ int vecinfer_decode_attention(const vecinfer_cfg *cfg, const void *q_f16, const 
  * The call allocates and frees nothing, on the device or through any library; the first call
  * on a device looks the array's address up once (make that first call outside a capture).
  *   - A request whose workspace (vecinfer_decode_workspace_bytes for the same cfg, B, N,
- *     num_splits) exceeds VECINFER_STATIC_SCRATCH_BYTES returns EWORKSPACE; nothing is enqueued.
+ *     num_splits; num_splits = 0: with splits of 1024 tokens) exceeds VECINFER_STATIC_SCRATCH_BYTES
+ *     returns EWORKSPACE; nothing is enqueued.  (num_splits = 0: where the array is too small for the
+ *     splits vecinfer_decode_attention would take, fewer are taken.)
  *     (Llama-3.1-8B shapes: B = 1 with 32 splits needs 0.55 MiB; B x H_q x splits x (D + 2)
  *     floats in general.)
  *   - All calls on one GPU share that GPU's array.  It needs no clearing (every partial a merge

@@ -61,18 +61,40 @@ int num_cus()
 
 namespace {
 
-// Splits so that B * H_kv * S fills the compute units once, each split keeping enough
-// tokens to amortise staging the codebooks in LDS.
-int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N)
+// Splits of a sequence: as many as fill the compute units once and no more (a compute unit holds one
+// workgroup, so one split too many runs a second round: 3 sequences x 8 heads at 32000 tokens take
+// 33.7 us with 11 splits on 256 compute units, 21.4 with 10), down to one wavefront's tile of 64
+// tokens each (1000 tokens: 15.0 us whole, 12.3 in 8 splits, 11.9 in 16; 8000: 15.0 in 8, 12.7 in
+// 32), 32 tokens with codes wider than 8 bits, where the search for a fused new token is what the
+// workgroups share (d8b12, 1000 tokens: 34.8 us whole, 17.0 in 4, 13.6 in 8).
+// Two or three splits cost more in the merge launch than they gain on short sequences: 16 sequences at
+// 1000 / 8000 tokens 15.2 / 34.5 us whole, 17.0 / 28.3 in two (head dim 64, up to 3000 tokens: 14.8
+// whole, 13.3 in two); one at 300 / 1000 tokens 12.9 / 15.0 us whole, 14.1 / 14.4 in three.  With a
+// residual window the merge runs in any case (16 sequences at 1500 tokens: 17.8 us whole, 15.8 in two).
+int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, bool window = false)
 {
     const int64_t groups = (int64_t)B * c->num_kv_heads;
-    int64_t s = (num_cus() + groups - 1) / groups;
-    const int64_t min_tokens = 1024;
+    int64_t s = num_cus() / groups;
+    const int64_t min_tokens = wide(c) ? 32 : 64;
     const int64_t cap = (N + min_tokens - 1) / min_tokens;
     if (s > cap) s = cap;
     if (s > VECINFER_MAX_SPLITS) s = VECINFER_MAX_SPLITS;
+    if (!wide(c) && !window && ((s == 2 && N < (c->head_dim == 64 ? 1024 : 2048)) || (s == 3 && N < 768))) s = 1;
     if (s < 1) s = 1;
     return (int32_t)s;
+}
+
+// The fewest splits that an automatic choice falls back to where the scratch memory is too small for
+// auto_splits: at least 1024 tokens each.
+int32_t fewest_splits(const vecinfer_cfg *c, int32_t B, int64_t N, bool window = false)
+{
+    const int64_t groups = (int64_t)B * c->num_kv_heads;
+    int64_t s = (num_cus() + groups - 1) / groups;
+    const int64_t cap = (N + 1023) / 1024;
+    if (s > cap) s = cap;
+    if (s > VECINFER_MAX_SPLITS) s = VECINFER_MAX_SPLITS;
+    const int64_t most = auto_splits(c, B, N, window);
+    return (int32_t)(s < most ? s : most);
 }
 
 // Device address of `scratch` on the current device, resolved once per device.
@@ -201,8 +223,12 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     if (!aligned(q_f16, 16) || !aligned(lambda, 16) || !aligned(cb_k_f16, 16) || !aligned(cb_v_f16, 16) ||
         !aligned(k_idx, 16) || !aligned(v_idx, 16) || !aligned(out_f16, 16))
         return VECINFER_EINVAL;
-    const int32_t S = N == 0 ? 1 : (num_splits ? num_splits : auto_splits(cfg, B, N));
-    const WorkspaceLayout w = ws_layout(cfg, B, S);
+    int32_t S = N == 0 ? 1 : (num_splits ? num_splits : auto_splits(cfg, B, N, window));
+    WorkspaceLayout w = ws_layout(cfg, B, S);
+    if (N > 0 && num_splits == 0 && workspace_bytes < w.total) {
+        S = fewest_splits(cfg, B, N, window);
+        w = ws_layout(cfg, B, S);
+    }
     if (!workspace || !aligned(workspace, 256) || workspace_bytes < w.total) return VECINFER_EWORKSPACE;
 
     DecodeParams p;
@@ -412,7 +438,8 @@ int32_t vecinfer_decode_auto_splits(const vecinfer_cfg *cfg, int32_t B, int64_t 
 size_t vecinfer_decode_workspace_bytes(const vecinfer_cfg *cfg, int32_t B, int64_t N, int32_t num_splits)
 {
     if (!cfg_ok(cfg) || B < 1 || N < 0 || num_splits < 0 || num_splits > VECINFER_MAX_SPLITS) return 0;
-    const int32_t S = N == 0 ? 1 : (num_splits ? num_splits : auto_splits(cfg, B, N));
+    // (room for the splits of a call with a residual window too)
+    const int32_t S = N == 0 ? 1 : (num_splits ? num_splits : auto_splits(cfg, B, N, true));
     return ws_layout(cfg, B, S).total;
 }
 
@@ -437,7 +464,7 @@ int vecinfer_decode_attention_static(const vecinfer_cfg *cfg, const void *q_f16,
     if (!cfg) return VECINFER_EINVAL;
     if (!cfg_ok(cfg)) return VECINFER_EUNSUPPORTED;
     if (B < 1 || N < 1 || num_splits < 0 || num_splits > VECINFER_MAX_SPLITS) return VECINFER_EINVAL;
-    const int32_t S = num_splits ? num_splits : auto_splits(cfg, B, N);
+    const int32_t S = num_splits ? num_splits : fewest_splits(cfg, B, N);
     if (ws_layout(cfg, B, S).total > (size_t)VECINFER_STATIC_SCRATCH_BYTES) return VECINFER_EWORKSPACE;
     void *ws = nullptr;
     const int rc = static_scratch(&ws);
