@@ -19,6 +19,7 @@
 //   phase 3  the 64 x M code bytes go out through LDS as whole 32-bit words.
 #include "common.h"
 #include "encode_screen.h"
+#include "mfma_helpers.h"
 
 namespace vecinfer {
 
@@ -342,27 +343,55 @@ __global__ void kmeans_end_kernel(const float *sums, const int32_t *counts, __ha
         for (int j = 0; j < d; ++j) cb[c * d + j] = __float2half(sums[c * d + j] / (float)n);
 }
 
-// Decode-time append (Eq. 9) and other short inputs: one workgroup per (token, batch, KV head).
-// The token is transformed in LDS with the same butterfly order as the tiled kernel (so both
-// produce bit-identical k~).  Then, 32 sub-spaces at a time: thread c writes the distance of
-// every sub-vector to centroid c into LDS; eight threads per sub-space each scan 32 of its 256
-// distances in increasing centroid order (strict "<": lowest index wins) and combine through
-// 64-bit (distance bits, index) keys -- a non-negative fp32 orders like its bit pattern.
-constexpr int kTokRowStride = kCentroids + 1;    // padded LDS row: scanning threads hit distinct banks
-constexpr int kTokMaxPass = 32;                  // sub-spaces per pass
-constexpr int kTokDistFloats = kTokMaxPass * kTokRowStride;
+// Decode-time append (Eq. 9) and other short inputs: one wavefront per token and NS (4, or M / 4 if
+// that is less) sub-spaces, with no LDS and no barrier.  The wavefront requests the token's row and the
+// 256 NS centroids at once (a lane: centroids lane, lane + 64, ..), transforms the row in registers with
+// the butterfly order of the tiled kernel (so both produce bit-identical k~: distance 1, 2, .. 32
+// across lanes, 64 between a lane's two channels), reads the sub-vectors off the lanes that hold
+// them, and takes the wavefront's smallest (distance bits, index): lowest index wins ties.
+// Bound by latency: one trip to memory, 12 shuffles, then about 50 instructions per sub-space.  (One
+// workgroup of 256 threads per token, distances through LDS and a barrier per butterfly stage, took
+// 6.1 us where this takes 5.7: 32 sequences x 8 heads, D = 128, d = 4, keys and values; one sequence 5.2
+// and 3.3; d = 2 8.1 and 6.6; 8 sequences of 16 tokens 16.1 and 14.4.)
+constexpr int kTokWaves = 4;                     // wavefronts per workgroup
+
+template <int D, int d>
+constexpr int tok_subs()                         // sub-spaces per wavefront
+{
+    return D / d / kTokWaves < 4 ? D / d / kTokWaves : 4;
+}
+
+template <int D, int d>
+constexpr int tok_groups()                       // workgroups per token
+{
+    return D / d / (kTokWaves * tok_subs<D, d>());
+}
 
 template <int D, int d, bool kTransform>
-__device__ __forceinline__ void encode_token(const EncodeParams &p, float *x_s, float *dist_s)
+__device__ __forceinline__ void encode_token(const EncodeParams &p, int group)
 {
-    constexpr int M = D / d;
-    constexpr int MC = M < kTokMaxPass ? M : kTokMaxPass;   // sub-spaces per pass
-    constexpr int RS = kTokRowStride;
-
-    const int tid = threadIdx.x;
+    constexpr int M = D / d, NS = tok_subs<D, d>(), PER = kCentroids / 64;
+    static_assert(64 % (NS * d) == 0, "a wavefront's channels lie in one half of the row");
+    typedef _Float16 f16xd __attribute__((ext_vector_type(d)));
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const long long t = blockIdx.x;
     const int bg = blockIdx.z;
     const int g = bg % p.Hkv;
+    const int m0 = (group * kTokWaves + wave) * NS;             // first sub-space of the wavefront
+    const __half *const row = p.x + ((size_t)bg * p.T + t) * D;
+    const __half h0 = row[lane], h1 = row[(D == 128 ? 64 : 0) + lane];
+    float l0 = 1.f, l1 = 1.f;
+    if (kTransform) {
+        l0 = p.lam[(size_t)g * D + lane];
+        l1 = p.lam[(size_t)g * D + (D == 128 ? 64 : 0) + lane];
+    }
+    const __half *const cb = p.cb + ((size_t)g * M + m0) * kCentroids * d + (size_t)lane * d;
+    f16xd cen[NS][PER];
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+        for (int c = 0; c < PER; ++c)
+            cen[i][c] = *reinterpret_cast<const f16xd *>(cb + ((size_t)i * kCentroids + 64 * c) * d);
     long long pos = p.pos0 + t;
     if (p.seq_lens) {                          // per-sequence position: the last token of the sequence
         const long long v = p.seq_lens[bg / p.Hkv];
@@ -370,90 +399,74 @@ __device__ __forceinline__ void encode_token(const EncodeParams &p, float *x_s, 
         if (len == 0) return;                  // uniform over the workgroup
         pos = len - 1;
     }
-
-    if (tid < D) {
-        float v = __half2float(p.x[((size_t)bg * p.T + t) * D + tid]);
-        if (kTransform) v = v / p.lam[(size_t)g * D + tid];
-        x_s[tid] = v;
-    }
-    __syncthreads();
+    float x0 = __half2float(h0), x1 = __half2float(h1);
     if (kTransform) {
-        for (int st = 1; st < D; st <<= 1) {
-            float mine = 0.f, other = 0.f;
-            if (tid < D) {
-                mine = x_s[tid];
-                other = x_s[tid ^ st];
-            }
-            __syncthreads();
-            if (tid < D) x_s[tid] = (tid & st) ? (other - mine) : (mine + other);
-            __syncthreads();
+        x0 = x0 / l0;
+        x1 = x1 / l1;
+#pragma unroll
+        for (int st = 1; st < 64; st <<= 1) {
+            const float o0 = __shfl_xor(x0, st), o1 = D == 128 ? __shfl_xor(x1, st) : 0.f;
+            const bool up = (lane & st) != 0;
+            x0 = up ? (o0 - x0) : (x0 + o0);
+            x1 = up ? (o1 - x1) : (x1 + o1);
         }
         const float hs = 1.0f / sqrtf((float)D);
-        if (tid < D) x_s[tid] *= hs;
-        __syncthreads();
+        if (D == 128) {
+            const float a = x0 + x1, b = x0 - x1;
+            x0 = a * hs;
+            x1 = b * hs;
+        } else {
+            x0 *= hs;
+        }
     }
-
-    const __half *cb = p.cb + (size_t)g * M * kCentroids * d + (size_t)tid * d;
-    for (int m0 = 0; m0 < M; m0 += MC) {
-#pragma unroll 8
-        for (int mm = 0; mm < MC; ++mm) {
-            const int m = m0 + mm;
+    const unsigned half = __float_as_uint(D == 128 && m0 * d >= 64 ? x1 : x0);
+    const int ch0 = m0 * d & 63;
+    unsigned mine = 0u;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        float x[d];
+#pragma unroll
+        for (int j = 0; j < d; ++j) x[j] = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)half, ch0 + i * d + j));
+        unsigned best = 0x7f800000u, arg = 0u;              // +inf (a non-negative fp32 orders like its bit pattern)
+#pragma unroll
+        for (int c = 0; c < PER; ++c) {
             float dist = 0.f;
 #pragma unroll
             for (int j = 0; j < d; ++j) {
-                const float tdiff = x_s[m * d + j] - __half2float(cb[(size_t)m * kCentroids * d + j]);
+                const float tdiff = x[j] - (float)cen[i][c][j];
                 dist = fmaf(tdiff, tdiff, dist);
             }
-            dist_s[mm * RS + tid] = dist;
-        }
-        __syncthreads();
-        {
-            const int mm = tid >> 3, part = tid & 7;
-            float best = INFINITY;
-            unsigned arg = 0;
-            if (mm < MC) {
-#pragma unroll 8
-                for (int i = 0; i < kCentroids / 8; ++i) {
-                    const unsigned c = part + 8 * i;
-                    const float v = dist_s[mm * RS + c];
-                    if (v < best) {
-                        best = v;
-                        arg = c;
-                    }
-                }
+            if (__float_as_uint(dist) < best) {
+                best = __float_as_uint(dist);
+                arg = (unsigned)(lane + 64 * c);
             }
-            unsigned long long key = ((unsigned long long)__float_as_uint(best) << 32) | arg;
-#pragma unroll
-            for (int o = 4; o > 0; o >>= 1) {
-                const unsigned long long other = __shfl_xor(key, o);
-                key = other < key ? other : key;
-            }
-            if (part == 0 && mm < MC)
-                p.idx[(size_t)bg * p.n_cap * M + (p.tiled ? v_tiled_offset(pos, m0 + mm, M) : (size_t)pos * M + m0 + mm)] =
-                    (uint8_t)(key & 255u);
         }
-        __syncthreads();
+        const unsigned dmin = wave_umin(best);
+        const unsigned code = wave_umin(best == dmin ? arg : 0xffffffffu);
+        mine = lane == i ? code : mine;
+    }
+    if (lane < NS) {
+        const int m = m0 + lane;
+        p.idx[(size_t)bg * p.n_cap * M + (p.tiled ? v_tiled_offset(pos, m, M) : (size_t)pos * M + m)] = (uint8_t)mine;
     }
 }
 
 template <int D, int d, bool kTransform>
-__global__ __launch_bounds__(kCentroids) void encode_token_kernel(EncodeParams p)
+__global__ __launch_bounds__(64 * kTokWaves) void encode_token_kernel(EncodeParams p)
 {
-    __shared__ float x_s[D];
-    __shared__ float dist_s[kTokDistFloats];
-    encode_token<D, d, kTransform>(p, x_s, dist_s);
+    encode_token<D, d, kTransform>(p, (int)blockIdx.y);
 }
 
-// Eq. 9 in one launch: blockIdx.y = 0 appends the key codes (transform + VQ), 1 the value codes.
+// Eq. 9 in one launch: the first values of blockIdx.y append the key codes (transform + VQ), the others
+// the value codes.
 template <int D, int dk, int dv>
-__global__ __launch_bounds__(kCentroids) void append_kv_kernel(EncodeParams pk, EncodeParams pv)
+__global__ __launch_bounds__(64 * kTokWaves) void append_kv_kernel(EncodeParams pk, EncodeParams pv)
 {
-    __shared__ float x_s[D];
-    __shared__ float dist_s[kTokDistFloats];
-    if (blockIdx.y == 0)
-        encode_token<D, dk, true>(pk, x_s, dist_s);
+    constexpr int GK = tok_groups<D, dk>();
+    if (blockIdx.y < GK)
+        encode_token<D, dk, true>(pk, (int)blockIdx.y);
     else
-        encode_token<D, dv, false>(pv, x_s, dist_s);
+        encode_token<D, dv, false>(pv, (int)blockIdx.y - GK);
 }
 
 constexpr long long kTokenKernelMaxT = 16;     // below this many tokens per (b, g) the per-token kernel wins
@@ -905,11 +918,11 @@ template <int D, int d>
 int launch_typed(const EncodeParams &p, hipStream_t stream)
 {
     if (p.T <= kTokenKernelMaxT && !p.km_sums) {
-        dim3 tgrid((unsigned)p.T, 1, p.B * p.Hkv);
+        dim3 tgrid((unsigned)p.T, tok_groups<D, d>(), p.B * p.Hkv);
         if (p.lam)
-            hipLaunchKernelGGL((encode_token_kernel<D, d, true>), tgrid, dim3(kCentroids), 0, stream, p);
+            hipLaunchKernelGGL((encode_token_kernel<D, d, true>), tgrid, dim3(64 * kTokWaves), 0, stream, p);
         else
-            hipLaunchKernelGGL((encode_token_kernel<D, d, false>), tgrid, dim3(kCentroids), 0, stream, p);
+            hipLaunchKernelGGL((encode_token_kernel<D, d, false>), tgrid, dim3(64 * kTokWaves), 0, stream, p);
         return hipGetLastError() == hipSuccess ? 0 : -4;
     }
     // Few tiles (a residual window flushed into the cache, a short prompt): the smallest group of
@@ -931,13 +944,14 @@ int launch_typed(const EncodeParams &p, hipStream_t stream)
 template <int D, int dk>
 int launch_append_dv(const EncodeParams &pk, const EncodeParams &pv, hipStream_t stream)
 {
-    dim3 grid((unsigned)pk.T, 2, pk.B * pk.Hkv);
+    constexpr int block = 64 * kTokWaves;
+    auto grid = [&](int groups_v) { return dim3((unsigned)pk.T, tok_groups<D, dk>() + groups_v, pk.B * pk.Hkv); };
     if (pv.d == 2)
-        hipLaunchKernelGGL((append_kv_kernel<D, dk, 2>), grid, dim3(kCentroids), 0, stream, pk, pv);
+        hipLaunchKernelGGL((append_kv_kernel<D, dk, 2>), grid(tok_groups<D, 2>()), dim3(block), 0, stream, pk, pv);
     else if (pv.d == 4)
-        hipLaunchKernelGGL((append_kv_kernel<D, dk, 4>), grid, dim3(kCentroids), 0, stream, pk, pv);
+        hipLaunchKernelGGL((append_kv_kernel<D, dk, 4>), grid(tok_groups<D, 4>()), dim3(block), 0, stream, pk, pv);
     else if (pv.d == 8)
-        hipLaunchKernelGGL((append_kv_kernel<D, dk, 8>), grid, dim3(kCentroids), 0, stream, pk, pv);
+        hipLaunchKernelGGL((append_kv_kernel<D, dk, 8>), grid(tok_groups<D, 8>()), dim3(block), 0, stream, pk, pv);
     else
         return -2;
     return hipGetLastError() == hipSuccess ? 0 : -4;
