@@ -283,16 +283,17 @@ __global__ __launch_bounds__((vq_block<d, kAccumulate, kGroup>(D / d))) __attrib
     }
     if constexpr (kAccumulate) {
         __syncthreads();
-        // the run's partial sums -> memory
+        // The run's partial sums -> memory, element by element: a wavefront's 64 atomics cover 256 adjacent
+        // bytes.  (A lane per centroid, channel after channel, touched d times as many cache lines per
+        // instruction: an iteration at 8000 x 8 tokens took 157 us and takes 125 at d = 4, 200 and 102 at d = 8.)
+        const size_t cen0 = ((size_t)g * M + (size_t)grp * MSW) * kCentroids;
+        for (int e = tid; e < MSW * kCentroids * d; e += BLOCK) {
+            const float *a = acc_s + (size_t)(e / d) * (d + 1);
+            if (a[d] > 0.f) unsafeAtomicAdd(p.km_sums + cen0 * d + e, a[e % d]);
+        }
         for (int e = tid; e < MSW * kCentroids; e += BLOCK) {
-            const float *a = acc_s + (size_t)e * (d + 1);
-            const int n = (int)a[d];
-            if (n > 0) {
-                const size_t cen = ((size_t)g * M + (size_t)grp * MSW) * kCentroids + e;
-#pragma unroll
-                for (int j = 0; j < d; ++j) unsafeAtomicAdd(p.km_sums + cen * d + j, a[j]);
-                atomicAdd(p.km_counts + cen, n);
-            }
+            const int n = (int)acc_s[(size_t)e * (d + 1) + d];
+            if (n > 0) atomicAdd(p.km_counts + cen0 + e, n);
         }
         double e64 = (double)err;
 #pragma unroll
@@ -608,19 +609,24 @@ __global__ __launch_bounds__(kVqBlock) void vq_tile_wide_kernel(EncodeParams p, 
         __syncthreads();
         store_packed_rows<M, BITS>(p, idx_s, t0, kEncTokens, bg, kVqBlock);
         if (p.km_sums) {
-            for (int e = tid; e < kEncTokens * M; e += kVqBlock) {
-                const int tl = e / M, m = e - tl * M;
-                if (t0 + tl < p.T) {
-                    if constexpr (kLdsSums) {
+            if constexpr (kLdsSums) {
+                for (int e = tid; e < kEncTokens * M; e += kVqBlock) {
+                    const int tl = e / M, m = e - tl * M;
+                    if (t0 + tl < p.T) {
                         float *a = acc_s + (size_t)idx_s[tl * M + m] * (d + 1);
 #pragma unroll
                         for (int j = 0; j < d; ++j) atomicAdd(a + j, x_s[tl * XS + m * d + j]);
                         atomicAdd(a + d, 1.0f);        // (counts stay exact in fp32: far below 2^24 per run)
-                    } else {
+                    }
+                }
+            } else {
+                // d adjacent lanes per sub-vector: a wavefront's atomics touch 64 / d cache lines, not 64
+                for (int e = tid; e < kEncTokens * M * d; e += kVqBlock) {
+                    const int v = e / d, j = e % d, tl = v / M, m = v - tl * M;
+                    if (t0 + tl < p.T) {
                         const size_t cen = (size_t)g * C + idx_s[tl * M + m];
-#pragma unroll
-                        for (int j = 0; j < d; ++j) unsafeAtomicAdd(p.km_sums + cen * d + j, x_s[tl * XS + m * d + j]);
-                        atomicAdd(p.km_counts + cen, 1);
+                        unsafeAtomicAdd(p.km_sums + cen * d + j, x_s[tl * XS + m * d + j]);
+                        if (j == 0) atomicAdd(p.km_counts + cen, 1);
                     }
                 }
             }
@@ -629,16 +635,14 @@ __global__ __launch_bounds__(kVqBlock) void vq_tile_wide_kernel(EncodeParams p, 
     if (p.km_sums) {
         if constexpr (kLdsSums) {
             __syncthreads();
-            // the run's partial sums -> memory
+            // the run's partial sums -> memory, element by element as in vq_tile_kernel
+            for (int e = tid; e < C * d; e += kVqBlock) {
+                const float *a = acc_s + (size_t)(e / d) * (d + 1);
+                if (a[d] > 0.f) unsafeAtomicAdd(p.km_sums + (size_t)g * C * d + e, a[e % d]);
+            }
             for (int e = tid; e < C; e += kVqBlock) {
-                const float *a = acc_s + (size_t)e * (d + 1);
-                const int n = (int)a[d];
-                if (n > 0) {
-                    const size_t cen = (size_t)g * C + e;
-#pragma unroll
-                    for (int j = 0; j < d; ++j) unsafeAtomicAdd(p.km_sums + cen * d + j, a[j]);
-                    atomicAdd(p.km_counts + cen, n);
-                }
+                const int n = (int)acc_s[(size_t)e * (d + 1) + d];
+                if (n > 0) atomicAdd(p.km_counts + (size_t)g * C + e, n);
             }
         }
         double e64 = (double)err;
@@ -818,20 +822,21 @@ int launch_append_wide(const EncodeParams &pk, const EncodeParams &pv, hipStream
 
 // Tiles per workgroup of the tile kernels, for `tiles` tiles of each of `groups` (sequence, KV head,
 // sub-space group)s.  A compute unit holds one workgroup at a time, so what the launch takes is the
-// number of rounds of workgroups times a run, and a run is its tiles plus `setup`: the search tables
-// (and, for K-Means, the flush of the sums), in tiles.  The least of that over 1 .. 8 rounds.
-long long tile_run(long long tiles, long long groups, double setup)
+// number of rounds of workgroups times a run, and a run is its tiles plus `setup`, the search tables;
+// for K-Means every workgroup's flush of its sums comes on top (`flush`: atomics, which the memory takes
+// one workgroup after the other), both in tiles.  The least of that over a quarter to eight rounds.
+long long tile_run(long long tiles, long long groups, double setup, double flush = 0.0)
 {
     const long long cus = num_cus();
     long long best_per = tiles < 256 ? tiles : 256;
     double best = 1e300;
-    for (int r = 1; r <= 8; ++r) {
-        const long long runs = r * cus / groups;                // runs of a group that fit r rounds
+    for (int q = flush > 0.0 ? 1 : 4; q <= 32; q += q < 4 ? 1 : 4) {
+        const long long runs = q * cus / 4 / groups;            // runs of a group that fit q / 4 rounds
         if (runs < 1) continue;
         long long per = (tiles + runs - 1) / runs;
         if (per > 256) per = 256;
-        const long long rounds = ((tiles + per - 1) / per * groups + cus - 1) / cus;
-        const double cost = rounds * (per + setup);
+        const long long wgs = (tiles + per - 1) / per * groups;
+        const double cost = (wgs + cus - 1) / cus * (per + setup) + flush * wgs;
         if (cost < best) {
             best = cost;
             best_per = per;
@@ -902,8 +907,9 @@ int launch_vq_tiles(const EncodeParams &p, int iter, void *state, hipStream_t st
     if (!configured) return -4;
     const long long tiles = (p.T + kEncTokens - 1) / kEncTokens;
     constexpr int block = vq_block<d, kAccumulate, kGroup>(M);
-    // (K-Means: a run ends with the partial sums' flush, and a long run meets each centroid many times)
-    const long long per = tile_run(tiles, (long long)(M / MSW) * p.B * p.Hkv, kAccumulate ? 2.0 : 0.5);
+    // (K-Means: a flush of 256 (d + 1) atomics per sub-space at about 90 G/s against a tile of about 6 us)
+    const long long per = tile_run(tiles, (long long)(M / MSW) * p.B * p.Hkv, 0.5,
+                                   kAccumulate ? MSW * kCentroids * (d + 1) / (90e9 * 6e-6) : 0.0);
     dim3 grid((unsigned)((tiles + per - 1) / per), M / MSW, p.B * p.Hkv);
     if (p.lam)
         hipLaunchKernelGGL((vq_tile_kernel<D, d, true, kAccumulate, kGroup>), grid, dim3(block), smem, stream, p, (int)per, iter,
