@@ -71,6 +71,9 @@ namespace {
 // 1000 / 8000 tokens 15.2 / 34.5 us whole, 17.0 / 28.3 in two (head dim 64, up to 3000 tokens: 14.8
 // whole, 13.3 in two); one at 300 / 1000 tokens 12.9 / 15.0 us whole, 14.1 / 14.4 in three.  With a
 // residual window the merge runs in any case (16 sequences at 1500 tokens: 17.8 us whole, 15.8 in two).
+// The merge reads 32 partials in one go, more than 32 in a second dependent round: 28 / 4 heads, one
+// sequence of 2000 / 32000 tokens 17.3 / 21.0 us in 32 splits, 22.0 / 23.6 in 64; by these slopes
+// the lines cross near 67000 tokens.
 int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, bool window = false)
 {
     const int64_t groups = (int64_t)B * c->num_kv_heads;
@@ -79,6 +82,7 @@ int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, bool window = f
     const int64_t cap = (N + min_tokens - 1) / min_tokens;
     if (s > cap) s = cap;
     if (s > VECINFER_MAX_SPLITS) s = VECINFER_MAX_SPLITS;
+    if (s > 32 && N < 65536) s = 32;
     if (!wide(c) && !window && ((s == 2 && N < (c->head_dim == 64 ? 1024 : 2048)) || (s == 3 && N < 768))) s = 1;
     if (s < 1) s = 1;
     return (int32_t)s;
