@@ -1,22 +1,16 @@
 // Cache-fill kernels: key-side dual transform (Eq. 3, Eq. 6) and exhaustive nearest-centroid
 // vector quantization (Eq. 2, Eq. 8).
 //
-// One workgroup (4 wavefronts) handles 64 tokens of one (batch, KV head).  The sub-spaces are
-// searched four at a time (one per wavefront); the four codebooks are staged in LDS widened
-// to fp32, one group after the other.
+// Cache fill and K-Means assignment work on tiles of 64 tokens of one (batch, KV head):
 //   phase 1  transform: a lane owns 4 consecutive channels of one token; the first two
 //            butterfly stages run inside the lane, the others across lanes with wavefront
 //            shuffles.  The transformed tile is kept, as fp32, in LDS.
 //            (Values skip the transform: the lane just widens its fp16 inputs.)
-//   phase 2  search: a lane owns one token, a wavefront owns one sub-space at a time, so the
-//            centroid under test is the same for all 64 lanes and is read from LDS as a
-//            broadcast.  Squared distances are summed directly, in channel order, in fp32.
-//            Centroids are scanned in groups of 8: only the group minimum is compared with
-//            the running best (strict "<": the earliest group wins ties), and the winning
-//            group is re-evaluated at the end to find the lowest index that attains the
-//            minimum.  A non-negative fp32 orders like its bit pattern, so the minima are
-//            taken on the bits (integer min: no NaN canonicalisation on the way).
-//   phase 3  the 64 x M code bytes go out through LDS as whole 32-bit words.
+//   phase 2  search (encode_screen.h): a wavefront owns one sub-space at a time and a lane one
+//            token; the matrix cores shortlist, the exact fp32 distances decide.
+//   phase 3  the code bytes go out through LDS.
+// What bounds it: issue.  At 65536 x 8 tokens, d = 4, values, the vector ALU is busy for 201 us and the
+// matrix cores for 55 of the kernel's 286 us (352 for keys: 235 and 55), with four wavefronts per SIMD.
 #include "common.h"
 #include "encode_screen.h"
 #include "mfma_helpers.h"
@@ -938,6 +932,7 @@ int launch_typed(const EncodeParams &p, hipStream_t stream)
     //        64            8.2 / 5.7               -            15.0 / 13.7
     //       128           14.7 / 9.8           10.8 / 8.4       15.4 / 13.7
     //       256           26.6 / 17.6              -            15.9 / 14.2
+    // (before 16 wavefronts per workgroup, which take 10.0 / 7.0 at 128 with 16 and need the same order.)
     constexpr int M = D / d, all = M < kVqAll ? M : kVqAll;
     const long long tiles = (p.T + kEncTokens - 1) / kEncTokens * p.B * p.Hkv;
     if constexpr (all > 8)

@@ -24,6 +24,7 @@
 // What bounds it: vector-ALU instructions.  Per wavefront, sub-space and tile 128 + 16 for the maxima,
 // 64 for the marks, about 110 per round of exact distances, 50 for operands and the rest.
 // 65536 tokens x 8 heads, d = 4, keys / values: 459 / 398 us with block maxima, 338 / 276 us without;
+// both in turn 604 us, 540 us with four wavefronts per SIMD instead of two;
 // 10007 tokens x 8 heads, d = 8, 12-bit codes: 511 / 498 us, 236 / 203 us (one MFMA per block, marks
 // once per search instead of once per 256 centroids).
 //
