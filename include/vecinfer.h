@@ -241,17 +241,19 @@ int vecinfer_kmeans_train(const vecinfer_cfg *cfg, const void *x_f16, const floa
 
 /*
  * Number of sequence splits the library would pick for (B, N) when num_splits = 0
- * (grid axis "num_splits" of Sec. 3.3).  Host-only; returns >= 1, or a negative code.
+ * (grid axis "num_splits" of Sec. 3.3) and the workspace has room for them; a call with a residual
+ * window takes two or three for a short sequence where the others take one.  Host-only; returns >= 1,
+ * or a negative code.
  */
 int32_t vecinfer_decode_auto_splits(const vecinfer_cfg *cfg, int32_t B, int64_t N);
 
 /*
  * Bytes of workspace vecinfer_decode_attention needs for batch B, up to N tokens and
- * `num_splits` splits (0 = what vecinfer_decode_auto_splits returns for (B, N), or the two or three
- * splits that a short sequence with a residual window takes instead of one).
+ * `num_splits` splits (0 = as many as any of the decode calls takes for (B, N)).
  * N = 0 (only meaningful for vecinfer_decode_attention_residual) gives the one-split size.
- * With num_splits = 0 the decode calls also run in less than that, with fewer splits, down to splits
- * of 1024 tokens.
+ * A decode call with num_splits = 0 that is given less takes as many splits as there is room for, down
+ * to one; it returns EWORKSPACE only below the size for num_splits = 1.  So a workspace made for the
+ * largest batch serves the smaller ones too.
  * Host-only.  Returns 0 for an invalid cfg or negative sizes.
  */
 size_t vecinfer_decode_workspace_bytes(const vecinfer_cfg *cfg, int32_t B, int64_t N,
@@ -297,9 +299,9 @@ int vecinfer_decode_attention(const vecinfer_cfg *cfg, const void *q_f16, const 
  * The call allocates and frees nothing, on the device or through any library; the first call
  * on a device looks the array's address up once (make that first call outside a capture).
  *   - A request whose workspace (vecinfer_decode_workspace_bytes for the same cfg, B, N,
- *     num_splits; num_splits = 0: with splits of 1024 tokens) exceeds VECINFER_STATIC_SCRATCH_BYTES
- *     returns EWORKSPACE; nothing is enqueued.  (num_splits = 0: where the array is too small for the
- *     splits vecinfer_decode_attention would take, fewer are taken.)
+ *     num_splits; num_splits = 0: that for one split, the array always has room for the splits
+ *     vecinfer_decode_attention takes) exceeds VECINFER_STATIC_SCRATCH_BYTES returns EWORKSPACE;
+ *     nothing is enqueued.
  *     (Llama-3.1-8B shapes: B = 1 with 32 splits needs 0.55 MiB; B x H_q x splits x (D + 2)
  *     floats in general.)
  *   - All calls on one GPU share that GPU's array.  It needs no clearing (every partial a merge

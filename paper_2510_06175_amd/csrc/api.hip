@@ -88,17 +88,17 @@ int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, bool window = f
     return (int32_t)s;
 }
 
-// The fewest splits that an automatic choice falls back to where the scratch memory is too small for
-// auto_splits: at least 1024 tokens each.
-int32_t fewest_splits(const vecinfer_cfg *c, int32_t B, int64_t N, bool window = false)
+// As many as fill the compute units, rounded up, of at least 1024 tokens each: for some batches more than
+// auto_splits.  A workspace has room for the larger of the two, so that one made for the largest batch
+// of a program serves its smaller ones, whose B * S may be larger (8 KV heads: 24 x 1 split, 16 x 2).
+int32_t splits_of_1024(const vecinfer_cfg *c, int32_t B, int64_t N)
 {
     const int64_t groups = (int64_t)B * c->num_kv_heads;
     int64_t s = (num_cus() + groups - 1) / groups;
     const int64_t cap = (N + 1023) / 1024;
     if (s > cap) s = cap;
     if (s > VECINFER_MAX_SPLITS) s = VECINFER_MAX_SPLITS;
-    const int64_t most = auto_splits(c, B, N, window);
-    return (int32_t)(s < most ? s : most);
+    return (int32_t)s;
 }
 
 // Device address of `scratch` on the current device, resolved once per device.
@@ -229,10 +229,8 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
         return VECINFER_EINVAL;
     int32_t S = N == 0 ? 1 : (num_splits ? num_splits : auto_splits(cfg, B, N, window));
     WorkspaceLayout w = ws_layout(cfg, B, S);
-    if (N > 0 && num_splits == 0 && workspace_bytes < w.total) {
-        S = fewest_splits(cfg, B, N, window);
-        w = ws_layout(cfg, B, S);
-    }
+    if (num_splits == 0)                // fewer where the workspace has no room for that many
+        while (S > 1 && workspace_bytes < w.total) w = ws_layout(cfg, B, --S);
     if (!workspace || !aligned(workspace, 256) || workspace_bytes < w.total) return VECINFER_EWORKSPACE;
 
     DecodeParams p;
@@ -442,8 +440,11 @@ int32_t vecinfer_decode_auto_splits(const vecinfer_cfg *cfg, int32_t B, int64_t 
 size_t vecinfer_decode_workspace_bytes(const vecinfer_cfg *cfg, int32_t B, int64_t N, int32_t num_splits)
 {
     if (!cfg_ok(cfg) || B < 1 || N < 0 || num_splits < 0 || num_splits > VECINFER_MAX_SPLITS) return 0;
-    // (room for the splits of a call with a residual window too)
-    const int32_t S = N == 0 ? 1 : (num_splits ? num_splits : auto_splits(cfg, B, N, true));
+    int32_t S = num_splits;
+    if (S == 0) {                       // (room for the splits of a call with a residual window too)
+        const int32_t most = N == 0 ? 1 : auto_splits(cfg, B, N, true), other = N == 0 ? 1 : splits_of_1024(cfg, B, N);
+        S = most > other ? most : other;
+    }
     return ws_layout(cfg, B, S).total;
 }
 
@@ -468,7 +469,7 @@ int vecinfer_decode_attention_static(const vecinfer_cfg *cfg, const void *q_f16,
     if (!cfg) return VECINFER_EINVAL;
     if (!cfg_ok(cfg)) return VECINFER_EUNSUPPORTED;
     if (B < 1 || N < 1 || num_splits < 0 || num_splits > VECINFER_MAX_SPLITS) return VECINFER_EINVAL;
-    const int32_t S = num_splits ? num_splits : fewest_splits(cfg, B, N);
+    const int32_t S = num_splits ? num_splits : 1;     // (what auto_splits takes fits wherever one split does)
     if (ws_layout(cfg, B, S).total > (size_t)VECINFER_STATIC_SCRATCH_BYTES) return VECINFER_EWORKSPACE;
     void *ws = nullptr;
     const int rc = static_scratch(&ws);

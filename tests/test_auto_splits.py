@@ -50,3 +50,78 @@ def test_smaller_workspace_takes_fewer_splits(N):
         assert np.abs(l - ref_l).max() <= 1e-3
     with pytest.raises(vb.VecInferError):
         vb.vecinfer_decode_attention(cfg, t["q"], t["lam"], t["cb_k"], t["cb_v"], t["k_idx"], t["v_idx"], ws[:256], out, N=N)
+
+
+def _rounded_up(heads, B, N):
+    """ceil(compute units / groups) splits of at least 1024 tokens each."""
+    return min(-(-CUS // (B * heads[1])), -(-N // 1024))
+
+
+@pytest.mark.parametrize("heads", [(32, 8), (28, 4), (8, 8), (64, 16), (4, 1)])
+def test_a_workspace_has_room_for_smaller_batches(heads):
+    """The automatic size never falls below that of the rounded-up count, which grows with the batch
+    (to within a row of splits), and holds what a window call takes."""
+    cfg = vb.Config(128, *heads, 4, 4)
+    for B in (1, 2, 3, 5, 8, 12, 16, 17, 20, 24, 31, 32, 48):
+        for N in (100, 1500, 8192, 32768, 196608):
+            size = vb.vecinfer_decode_workspace_bytes(cfg, B, N, 0)
+            assert size >= vb.vecinfer_decode_workspace_bytes(cfg, B, N, _rounded_up(heads, B, N)), (B, N)
+            assert size >= vb.vecinfer_decode_workspace_bytes(cfg, B, N, vb.vecinfer_decode_auto_splits(cfg, B, N)), (B, N)
+            # (and the fixed array of the static entry point holds whatever is taken)
+            assert size <= vb.STATIC_SCRATCH_BYTES
+
+
+def _decode_state(cfg, B, N, seed, R=0):
+    """Random codes, codebooks and query of one layer on the GPU (the values do not matter here, only
+    that the calls run and agree)."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda")  # noqa: E731
+    code = lambda keys: torch.randint(0, 256, (B, cfg.num_kv_heads, N, cfg.row_bytes(keys)), generator=g, device="cuda",  # noqa: E731
+                                      dtype=torch.uint8)
+    return {"q": rn(B, cfg.num_q_heads, cfg.head_dim).half(), "lam": torch.exp(0.5 * rn(cfg.num_kv_heads, cfg.head_dim)),
+            "cb_k": rn(*cfg.cb_shape(True)).half(), "cb_v": rn(*cfg.cb_shape(False)).half(),
+            "k_idx": code(True), "v_idx": code(False), "k": rn(B, cfg.num_kv_heads, max(R, 1), cfg.head_dim).half(),
+            "v": rn(B, cfg.num_kv_heads, max(R, 1), cfg.head_dim).half()}
+
+
+def _call(kind, cfg, s, B, N, ws, num_splits=0, seq_lens=None, variant=vb.VARIANT_AUTO):
+    """(out, lse) of one decode call over the first B sequences of the state."""
+    t = {k: (v if k in ("lam", "cb_k", "cb_v") else v[:B]) for k, v in s.items()}
+    out = torch.empty((B, cfg.num_q_heads, cfg.head_dim), dtype=torch.float16, device="cuda")
+    lse = torch.empty((B, cfg.num_q_heads), dtype=torch.float32, device="cuda")
+    kw = dict(lse=lse, seq_lens=seq_lens, N=N, num_splits=num_splits, variant=variant)
+    head = (cfg, t["q"], t["lam"], t["cb_k"], t["cb_v"], t["k_idx"], t["v_idx"])
+    if kind == "attention":
+        vb.vecinfer_decode_attention(*head, ws, out, **kw)
+    elif kind == "window":
+        vb.vecinfer_decode_attention_residual(*head, t["k"], t["v"], ws, out, **kw)
+    else:
+        vb.vecinfer_decode_step(cfg, t["q"], t["k"], t["v"], *head[2:], ws, out, **kw)
+    return out, lse
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("most", [5, 17, 24])
+def test_one_workspace_serves_every_smaller_batch(most):
+    cfg, N = vb.Config(128, 32, 8, 4, 4), 8192
+    s = _decode_state(cfg, most, N, most)
+    ws = vb.new_workspace(cfg, most, N)
+    for B in range(1, most + 1):
+        out, lse = _call("attention", cfg, s, B, N, ws)
+        own, own_lse = _call("attention", cfg, s, B, N, vb.new_workspace(cfg, B, N))
+        # another number of splits at most: fp16 outputs and softmax weights, fp32 sums
+        assert (out - own).abs().max() <= 2e-3 * own.abs().max(), B
+        assert (lse - own_lse).abs().max() <= 1e-3, B
+
+
+@pytest.mark.gpu
+def test_window_call_in_a_workspace_of_the_reported_splits():
+    cfg, B, N = vb.Config(128, 8, 8, 4, 4), 16, 1500
+    s = _decode_state(cfg, B, N, 3, R=40)
+    few = vb.new_workspace(cfg, B, N, vb.vecinfer_decode_auto_splits(cfg, B, N))
+    out, lse = _call("window", cfg, s, B, N, few)
+    own, own_lse = _call("window", cfg, s, B, N, vb.new_workspace(cfg, B, N))
+    assert (out - own).abs().max() <= 2e-3 * own.abs().max()
+    assert (lse - own_lse).abs().max() <= 1e-3
+    with pytest.raises(vb.VecInferError):                  # not even one split
+        _call("window", cfg, s, B, N, vb.new_workspace(cfg, B, N, 1)[:-256])
