@@ -242,8 +242,8 @@ int vecinfer_kmeans_train(const vecinfer_cfg *cfg, const void *x_f16, const floa
 /*
  * Number of sequence splits the library would pick for (B, N) when num_splits = 0
  * (grid axis "num_splits" of Sec. 3.3) and the workspace has room for them; a call with a residual
- * window takes two or three for a short sequence where the others take one.  Host-only; returns >= 1,
- * or a negative code.
+ * window takes two or three for a short sequence where the others take one, and VECINFER_VARIANT_LUT
+ * one more for some batches.  Host-only; returns >= 1, or a negative code.
  */
 int32_t vecinfer_decode_auto_splits(const vecinfer_cfg *cfg, int32_t B, int64_t N);
 

@@ -101,6 +101,17 @@ int32_t splits_of_1024(const vecinfer_cfg *c, int32_t B, int64_t N)
     return (int32_t)s;
 }
 
+// Splits of the lookup-table kernel, the larger count of the two rules: its time goes with the tokens of a
+// split alone, and several of its workgroups fit a compute unit, so that more splits than one round of
+// workgroups still gain (32 / 8 heads, 4000 tokens: 17 sequences at head dim 128 1600 us whole, 1245 in two;
+// 24 at head dim 64 624 and 423), as does the finer cut of a short sequence (one of 1000 tokens: 304 us whole,
+// 125 in 16).
+int32_t lut_splits(const vecinfer_cfg *c, int32_t B, int64_t N)
+{
+    const int32_t a = auto_splits(c, B, N, true), b = splits_of_1024(c, B, N);
+    return a > b ? a : b;
+}
+
 // Device address of `scratch` on the current device, resolved once per device.
 constexpr int kMaxDevices = 64;
 std::atomic<void *> g_scratch_ptr[kMaxDevices];
@@ -227,12 +238,6 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     if (!aligned(q_f16, 16) || !aligned(lambda, 16) || !aligned(cb_k_f16, 16) || !aligned(cb_v_f16, 16) ||
         !aligned(k_idx, 16) || !aligned(v_idx, 16) || !aligned(out_f16, 16))
         return VECINFER_EINVAL;
-    int32_t S = N == 0 ? 1 : (num_splits ? num_splits : auto_splits(cfg, B, N, window));
-    WorkspaceLayout w = ws_layout(cfg, B, S);
-    if (num_splits == 0)                // fewer where the workspace has no room for that many
-        while (S > 1 && workspace_bytes < w.total) w = ws_layout(cfg, B, --S);
-    if (!workspace || !aligned(workspace, 256) || workspace_bytes < w.total) return VECINFER_EWORKSPACE;
-
     DecodeParams p;
     p.q = static_cast<const __half *>(q_f16);
     p.lam = lambda;
@@ -255,6 +260,15 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     p.v_tiled = cfg->v_tiled;
     p.N = N;
     p.n_cap = n_cap;
+    const bool mfma_ok = decode_mfma_supports(p);
+    const bool use_roles = variant == VECINFER_VARIANT_ROLES;
+    const bool use_mfma = use_roles || (variant == VECINFER_VARIANT_MFMA) || (variant == VECINFER_VARIANT_AUTO && mfma_ok);
+
+    int32_t S = N == 0 ? 1 : (num_splits ? num_splits : use_mfma ? auto_splits(cfg, B, N, window) : lut_splits(cfg, B, N));
+    WorkspaceLayout w = ws_layout(cfg, B, S);
+    if (num_splits == 0)                // fewer where the workspace has no room for that many
+        while (S > 1 && workspace_bytes < w.total) w = ws_layout(cfg, B, --S);
+    if (!workspace || !aligned(workspace, 256) || workspace_bytes < w.total) return VECINFER_EWORKSPACE;
     p.S = S;
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     p.part_o = reinterpret_cast<float *>(ws + w.off_o);
@@ -272,11 +286,8 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     p.new_sc = reinterpret_cast<float *>(ws + w.off_nsc);
     p.new_v = reinterpret_cast<float *>(ws + w.off_nv);
 
-    const bool mfma_ok = decode_mfma_supports(p);
     if (variant == VECINFER_VARIANT_MFMA && !mfma_ok) return VECINFER_EUNSUPPORTED;
-    const bool use_roles = variant == VECINFER_VARIANT_ROLES;
     if (use_roles && !(mfma_ok && decode_roles_supports(p))) return VECINFER_EUNSUPPORTED;
-    const bool use_mfma = use_roles || (variant == VECINFER_VARIANT_MFMA) || (variant == VECINFER_VARIANT_AUTO && mfma_ok);
     // the lookup-table kernel reads one byte per code, from rows
     if (!use_mfma && (wide(cfg) || cfg->v_tiled)) return VECINFER_EUNSUPPORTED;
     int rc = 0;
@@ -440,11 +451,8 @@ int32_t vecinfer_decode_auto_splits(const vecinfer_cfg *cfg, int32_t B, int64_t 
 size_t vecinfer_decode_workspace_bytes(const vecinfer_cfg *cfg, int32_t B, int64_t N, int32_t num_splits)
 {
     if (!cfg_ok(cfg) || B < 1 || N < 0 || num_splits < 0 || num_splits > VECINFER_MAX_SPLITS) return 0;
-    int32_t S = num_splits;
-    if (S == 0) {                       // (room for the splits of a call with a residual window too)
-        const int32_t most = N == 0 ? 1 : auto_splits(cfg, B, N, true), other = N == 0 ? 1 : splits_of_1024(cfg, B, N);
-        S = most > other ? most : other;
-    }
+    // (the lookup-table kernel's count is the largest of all)
+    const int32_t S = N == 0 ? 1 : (num_splits ? num_splits : lut_splits(cfg, B, N));
     return ws_layout(cfg, B, S).total;
 }
 

@@ -75,13 +75,17 @@ def _decode_state(cfg, B, N, seed, R=0):
     """Random codes, codebooks and query of one layer on the GPU (the values do not matter here, only
     that the calls run and agree)."""
     g = torch.Generator(device="cuda").manual_seed(seed)
-    rn = lambda *s: torch.randn(s, generator=g, device="cuda")  # noqa: E731
-    code = lambda keys: torch.randint(0, 256, (B, cfg.num_kv_heads, N, cfg.row_bytes(keys)), generator=g, device="cuda",  # noqa: E731
-                                      dtype=torch.uint8)
-    return {"q": rn(B, cfg.num_q_heads, cfg.head_dim).half(), "lam": torch.exp(0.5 * rn(cfg.num_kv_heads, cfg.head_dim)),
+    Hkv, D = cfg.num_kv_heads, cfg.head_dim
+
+    def rn(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+
+    def code(keys):
+        return torch.randint(0, 256, (B, Hkv, N, cfg.row_bytes(keys)), generator=g, device="cuda", dtype=torch.uint8)
+    return {"q": rn(B, cfg.num_q_heads, D).half(), "lam": torch.exp(0.5 * rn(Hkv, D)),
             "cb_k": rn(*cfg.cb_shape(True)).half(), "cb_v": rn(*cfg.cb_shape(False)).half(),
-            "k_idx": code(True), "v_idx": code(False), "k": rn(B, cfg.num_kv_heads, max(R, 1), cfg.head_dim).half(),
-            "v": rn(B, cfg.num_kv_heads, max(R, 1), cfg.head_dim).half()}
+            "k_idx": code(True), "v_idx": code(False),
+            "k": rn(B, Hkv, max(R, 1), D).half(), "v": rn(B, Hkv, max(R, 1), D).half()}
 
 
 def _call(kind, cfg, s, B, N, ws, num_splits=0, seq_lens=None, variant=vb.VARIANT_AUTO):
@@ -96,7 +100,8 @@ def _call(kind, cfg, s, B, N, ws, num_splits=0, seq_lens=None, variant=vb.VARIAN
     elif kind == "window":
         vb.vecinfer_decode_attention_residual(*head, t["k"], t["v"], ws, out, **kw)
     else:
-        vb.vecinfer_decode_step(cfg, t["q"], t["k"], t["v"], *head[2:], ws, out, **kw)
+        new = (t[n][:, :, :1].contiguous() for n in ("k", "v"))
+        vb.vecinfer_decode_step(cfg, t["q"], *new, *head[2:], ws, out, **kw)
     return out, lse
 
 
@@ -125,3 +130,27 @@ def test_window_call_in_a_workspace_of_the_reported_splits():
     assert (lse - own_lse).abs().max() <= 1e-3
     with pytest.raises(vb.VecInferError):                  # not even one split
         _call("window", cfg, s, B, N, vb.new_workspace(cfg, B, N, 1)[:-256])
+
+
+# (call, Config arguments, B, N, ragged, variant) -> the splits that num_splits = 0 takes, and another
+# count whose result differs in some last bits
+CHOICES = [
+    # the lookup-table kernel: the larger of both rules
+    ("attention", (64, 4, 2, 4, 4), 90, 4000, 0, vb.VARIANT_LUT, 2, 1),
+    ("step", (128, 4, 2, 4, 4), 48, 2500, 0, vb.VARIANT_LUT, 3, 2),
+    ("attention", (128, 4, 1, 4, 4), 3, 1000, 0, vb.VARIANT_LUT, 16, 1),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind,args,B,N,ragged,variant,want,other", CHOICES)
+def test_automatic_choice(kind, args, B, N, ragged, variant, want, other):
+    """The automatic call is bit for bit the call with the expected number of splits (and the number
+    shows in the bits)."""
+    cfg = vb.Config(*args)
+    s = _decode_state(cfg, B, N, N + B, R=33)
+    lens = torch.linspace(N // 8, N, B, device="cuda").to(torch.int32) if ragged else None
+    run = lambda S: _call(kind, cfg, s, B, N, vb.new_workspace(cfg, B, N, S), S, lens, variant)  # noqa: E731
+    (out, lse), (w_out, w_lse), (o_out, o_lse) = run(0), run(want), run(other)
+    assert torch.equal(out, w_out) and torch.equal(lse, w_lse)
+    assert not (torch.equal(out, o_out) and torch.equal(lse, o_lse))
