@@ -71,9 +71,14 @@ namespace {
 // 1000 / 8000 tokens 15.2 / 34.5 us whole, 17.0 / 28.3 in two (head dim 64, up to 3000 tokens: 14.8
 // whole, 13.3 in two); one at 300 / 1000 tokens 12.9 / 15.0 us whole, 14.1 / 14.4 in three.  With a
 // residual window the merge runs in any case (16 sequences at 1500 tokens: 17.8 us whole, 15.8 in two).
-// The merge reads 32 partials in one go, more than 32 in a second dependent round: 28 / 4 heads, one
-// sequence of 2000 / 32000 tokens 17.3 / 21.0 us in 32 splits, 22.0 / 23.6 in 64; by these slopes
-// the lines cross near 67000 tokens.
+// The merge reads 32 partials in one go, and every further 32 are another dependent round (about 2 us, 5
+// with more than four query heads per KV head), against a split's stream, which grows with N and the bytes
+// of a token's codes: more than 32, 64 and 128 splits pay from about 55000, 200000 and 500000 tokens on,
+// the first two sooner with 96 bytes or more.  One sequence, us per step in 32 / 64 / 128 / 256 splits:
+//   heads          57000 tokens       65536                  131072              262144             786432
+//   4 / 1, d = 4  17.9 18.2 -   -  18.7 18.1 20.4 28.2   -  20.8 22.1 28.8   - 26.8 25.2 30.7   - - 36.9 37.4
+//   8 / 1, d = 4  24.9 26.7 -   -  26.0 26.6 32.4 48.2   -  30.5 34.7 48.8   - 38.7 39.1 51.4   - - 55.5 61.2
+//   4 / 1, d = 2  22.2 20.6 -   -  23.4 21.0 21.8 28.9   -  26.0 25.5 30.7   - 35.9 30.5 34.6   - - 50.1 45.8
 int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, bool window = false)
 {
     const int64_t groups = (int64_t)B * c->num_kv_heads;
@@ -82,7 +87,12 @@ int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, bool window = f
     const int64_t cap = (N + min_tokens - 1) / min_tokens;
     if (s > cap) s = cap;
     if (s > VECINFER_MAX_SPLITS) s = VECINFER_MAX_SPLITS;
-    if (s > 32 && N < 65536) s = 32;
+    const bool many_bytes = (c->head_dim / c->k_sub_dim * c->k_bits + c->head_dim / c->v_sub_dim * c->v_bits) / 8 >= 96;
+    const int64_t most = N < (many_bytes && c->num_q_heads <= 4 * c->num_kv_heads ? 49152 : 57344) ? 32
+                         : N < (many_bytes ? 131072 : 196608)                                      ? 64
+                         : N < 524288                                                              ? 128
+                                                                                                   : VECINFER_MAX_SPLITS;
+    if (s > most) s = most;
     if (!wide(c) && !window && ((s == 2 && N < (c->head_dim == 64 ? 1024 : 2048)) || (s == 3 && N < 768))) s = 1;
     if (s < 1) s = 1;
     return (int32_t)s;

@@ -139,6 +139,17 @@ CHOICES = [
     ("attention", (64, 4, 2, 4, 4), 90, 4000, 0, vb.VARIANT_LUT, 2, 1),
     ("step", (128, 4, 2, 4, 4), 48, 2500, 0, vb.VARIANT_LUT, 3, 2),
     ("attention", (128, 4, 1, 4, 4), 3, 1000, 0, vb.VARIANT_LUT, 16, 1),
+    # few KV heads: no more splits than the length pays for
+    ("attention", (128, 4, 1, 4, 4), 1, 57343, 0, 0, 32, 64),
+    ("attention", (128, 4, 1, 2, 2), 1, 49151, 0, 0, 32, 64),
+    ("step", (128, 4, 1, 2, 2), 1, 49152, 0, 0, 64, 32),
+    ("window", (128, 8, 1, 2, 2), 1, 57343, 0, 0, 32, 64),
+    ("step", (128, 8, 1, 8, 8, 12, 12), 1, 57344, 0, 0, 64, 256),
+    ("attention", (128, 1, 1, 4, 4), 1, 196607, 0, 0, 64, 256),
+    ("attention", (128, 1, 1, 2, 2), 1, 131072, 0, 0, 128, 64),
+    ("step", (128, 4, 2, 4, 4), 1, 196608, 0, 0, 128, 64),
+    ("step", (128, 4, 1, 4, 4), 1, 524287, 0, 0, 128, 256),
+    ("step", (128, 4, 1, 4, 4), 1, 524288, 0, 0, 256, 128),
 ]
 
 
