@@ -61,16 +61,26 @@ int num_cus()
 
 namespace {
 
+enum class Call { kAttention, kStep, kWindow };
+
 // Splits of a sequence: as many as fill the compute units once and no more (a compute unit holds one
 // workgroup, so one split too many runs a second round: 3 sequences x 8 heads at 32000 tokens take
 // 33.7 us with 11 splits on 256 compute units, 21.4 with 10), down to one wavefront's tile of 64
-// tokens each (1000 tokens: 15.0 us whole, 12.3 in 8 splits, 11.9 in 16; 8000: 15.0 in 8, 12.7 in
+// tokens each (a step at 1000 tokens: 15.0 us whole, 12.3 in 8 splits, 11.9 in 16; 8000: 15.0 in 8, 12.7 in
 // 32), 32 tokens with codes wider than 8 bits, where the search for a fused new token is what the
 // workgroups share (d8b12, 1000 tokens: 34.8 us whole, 17.0 in 4, 13.6 in 8).
-// Two or three splits cost more in the merge launch than they gain on short sequences: 16 sequences at
-// 1000 / 8000 tokens 15.2 / 34.5 us whole, 17.0 / 28.3 in two (head dim 64, up to 3000 tokens: 14.8
-// whole, 13.3 in two); one at 300 / 1000 tokens 12.9 / 15.0 us whole, 14.1 / 14.4 in three.  With a
-// residual window the merge runs in any case (16 sequences at 1500 tokens: 17.8 us whole, 15.8 in two).
+// What a split costs is the merge launch, 3 to 5 us (5 with more than four query heads per KV head):
+//   attention alone has nothing but its tokens to share: whole up to 1024 of them (8 sequences, 4 / 1
+//     heads: 250 / 600 / 1000 tokens 8.3 / 9.9 / 11.1 us whole, 11.4 / 11.6 / 11.6 in 4 / 10 / 16 splits; 8 / 1
+//     heads 9.9 / 12.1 / 13.7 and 15.1 / 15.7 / 15.9), 768 with d_k = 2, whose keys are twice the bytes (600 / 1000
+//     tokens, d = 2: 11.2 / 13.6 us whole, 11.8 / 12.0), and twice that where two is all there is room for (128
+//     sequences, 1100 / 1900 tokens: 12.1 / 14.7 us whole, 14.4 / 16.0 in two; d = 2 14.8 / 19.2 and 15.6 / 19.1);
+//   a step shares the search for its new token too: two or three splits cost more than they gain on short
+//     sequences (16 sequences at 1000 / 8000 tokens 15.2 / 34.5 us whole, 17.0 / 28.3 in two; head dim 64, up
+//     to 3000 tokens: 14.8 whole, 13.3 in two; one at 300 / 1000 tokens 12.9 / 15.0 us whole, 14.1 / 14.4 in
+//     three);
+//   with a residual window the merge runs in any case (16 sequences at 1500 tokens: 17.8 us whole, 15.8 in
+//     two; up to 256 tokens nothing is gained: 200 tokens, 8 / 1 heads, d8b12, 17.7 us whole, 18.3 in four).
 // The merge reads 32 partials in one go, and every further 32 are another dependent round (about 2 us, 5
 // with more than four query heads per KV head), against a split's stream, which grows with N and the bytes
 // of a token's codes: more than 32, 64 and 128 splits pay from about 55000, 200000 and 500000 tokens on,
@@ -79,7 +89,7 @@ namespace {
 //   4 / 1, d = 4  17.9 18.2 -   -  18.7 18.1 20.4 28.2   -  20.8 22.1 28.8   - 26.8 25.2 30.7   - - 36.9 37.4
 //   8 / 1, d = 4  24.9 26.7 -   -  26.0 26.6 32.4 48.2   -  30.5 34.7 48.8   - 38.7 39.1 51.4   - - 55.5 61.2
 //   4 / 1, d = 2  22.2 20.6 -   -  23.4 21.0 21.8 28.9   -  26.0 25.5 30.7   - 35.9 30.5 34.6   - - 50.1 45.8
-int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, bool window = false)
+int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, Call call)
 {
     const int64_t groups = (int64_t)B * c->num_kv_heads;
     int64_t s = num_cus() / groups;
@@ -93,8 +103,12 @@ int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, bool window = f
                          : N < 524288                                                              ? 128
                                                                                                    : VECINFER_MAX_SPLITS;
     if (s > most) s = most;
-    if (!wide(c) && !window && ((s == 2 && N < (c->head_dim == 64 ? 1024 : 2048)) || (s == 3 && N < 768))) s = 1;
-    if (s < 1) s = 1;
+    const bool long_keys = c->k_sub_dim == 2 && c->head_dim == 128;
+    const bool whole = call == Call::kWindow      ? N <= 256
+                       : call == Call::kAttention ? N <= (long_keys && s > 3 && c->num_q_heads <= 4 * c->num_kv_heads ? 768 : 1024) ||
+                                                        (s == 2 && N < (long_keys ? 1792 : 2048))
+                                                  : !wide(c) && ((s == 2 && N < (c->head_dim == 64 ? 1024 : 2048)) || (s == 3 && N < 768));
+    if (whole || s < 1) s = 1;
     return (int32_t)s;
 }
 
@@ -118,7 +132,7 @@ int32_t splits_of_1024(const vecinfer_cfg *c, int32_t B, int64_t N)
 // 125 in 16).
 int32_t lut_splits(const vecinfer_cfg *c, int32_t B, int64_t N)
 {
-    const int32_t a = auto_splits(c, B, N, true), b = splits_of_1024(c, B, N);
+    const int32_t a = auto_splits(c, B, N, Call::kWindow), b = splits_of_1024(c, B, N);
     return a > b ? a : b;
 }
 
@@ -231,6 +245,7 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     if (!cfg_ok(cfg)) return VECINFER_EUNSUPPORTED;
     const bool window = k_res != nullptr;
     const bool append = k_new != nullptr;
+    const Call call = window ? Call::kWindow : (append ? Call::kStep : Call::kAttention);
     if (append && (!v_new || !aligned(k_new, 16) || !aligned(v_new, 16))) return VECINFER_EINVAL;
     if (B < 1 || N < (window ? 0 : 1) || n_cap < N) return VECINFER_EINVAL;
     if (cfg->v_tiled && n_cap % 64 != 0) return VECINFER_EINVAL;                  // whole 64-token blocks
@@ -274,7 +289,7 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     const bool use_roles = variant == VECINFER_VARIANT_ROLES;
     const bool use_mfma = use_roles || (variant == VECINFER_VARIANT_MFMA) || (variant == VECINFER_VARIANT_AUTO && mfma_ok);
 
-    int32_t S = N == 0 ? 1 : (num_splits ? num_splits : use_mfma ? auto_splits(cfg, B, N, window) : lut_splits(cfg, B, N));
+    int32_t S = N == 0 ? 1 : (num_splits ? num_splits : use_mfma ? auto_splits(cfg, B, N, call) : lut_splits(cfg, B, N));
     WorkspaceLayout w = ws_layout(cfg, B, S);
     if (num_splits == 0)                // fewer where the workspace has no room for that many
         while (S > 1 && workspace_bytes < w.total) w = ws_layout(cfg, B, --S);
@@ -455,7 +470,7 @@ int32_t vecinfer_decode_auto_splits(const vecinfer_cfg *cfg, int32_t B, int64_t 
 {
     if (!cfg || B < 1 || N < 1) return VECINFER_EINVAL;
     if (!cfg_ok(cfg)) return VECINFER_EUNSUPPORTED;
-    return auto_splits(cfg, B, N);
+    return auto_splits(cfg, B, N, Call::kWindow);      // the largest of the three
 }
 
 size_t vecinfer_decode_workspace_bytes(const vecinfer_cfg *cfg, int32_t B, int64_t N, int32_t num_splits)

@@ -133,7 +133,7 @@ def test_window_call_in_a_workspace_of_the_reported_splits():
 
 
 # (call, Config arguments, B, N, ragged, variant) -> the splits that num_splits = 0 takes, and another
-# count whose result differs in some last bits
+# count whose result differs in some last bits (up to 512 tokens none does: a wavefront's tile each)
 CHOICES = [
     # the lookup-table kernel: the larger of both rules
     ("attention", (64, 4, 2, 4, 4), 90, 4000, 0, vb.VARIANT_LUT, 2, 1),
@@ -150,6 +150,19 @@ CHOICES = [
     ("step", (128, 4, 2, 4, 4), 1, 196608, 0, 0, 128, 64),
     ("step", (128, 4, 1, 4, 4), 1, 524287, 0, 0, 128, 256),
     ("step", (128, 4, 1, 4, 4), 1, 524288, 0, 0, 256, 128),
+    # attention alone: short sequences whole
+    ("attention", (128, 4, 1, 4, 4), 8, 1000, 0, 0, 1, 16),
+    ("attention", (64, 8, 1, 8, 8), 1, 1024, 0, 0, 1, 16),
+    ("attention", (128, 8, 1, 8, 8, 12, 12), 2, 900, 0, 0, 1, 29),
+    ("attention", (128, 4, 1, 4, 4), 8, 1025, 0, 0, 17, 1),
+    ("attention", (128, 4, 1, 4, 4), 100, 2047, 0, 0, 1, 2),
+    ("attention", (128, 4, 1, 4, 4), 100, 2048, 0, 0, 2, 1),
+    ("attention", (128, 4, 1, 2, 2), 100, 1792, 0, 0, 2, 1),
+    ("attention", (128, 4, 1, 2, 4), 8, 768, 0, 0, 1, 12),
+    ("attention", (128, 4, 1, 2, 4), 8, 769, 0, 0, 13, 1),
+    ("attention", (128, 4, 1, 2, 4), 80, 1024, 0, 0, 1, 3),
+    ("step", (128, 4, 1, 4, 4), 8, 1000, 0, 0, 16, 1),
+    ("window", (128, 4, 1, 4, 4), 8, 1000, 0, 0, 16, 1),
 ]
 
 
