@@ -125,6 +125,13 @@ int32_t splits_of_1024(const vecinfer_cfg *c, int32_t B, int64_t N)
     return (int32_t)s;
 }
 
+// The most that a decode call takes for (B, N), with the matrix-core kernel.
+int32_t largest_splits(const vecinfer_cfg *c, int32_t B, int64_t N)
+{
+    const int32_t a = auto_splits(c, B, N, Call::kWindow), b = auto_splits(c, B, N, Call::kStep);
+    return a > b ? a : b;
+}
+
 // Splits of the lookup-table kernel, the larger count of the two rules: its time goes with the tokens of a
 // split alone, and several of its workgroups fit a compute unit, so that more splits than one round of
 // workgroups still gain (32 / 8 heads, 4000 tokens: 17 sequences at head dim 128 1600 us whole, 1245 in two;
@@ -132,7 +139,7 @@ int32_t splits_of_1024(const vecinfer_cfg *c, int32_t B, int64_t N)
 // 125 in 16).
 int32_t lut_splits(const vecinfer_cfg *c, int32_t B, int64_t N)
 {
-    const int32_t a = auto_splits(c, B, N, Call::kWindow), b = splits_of_1024(c, B, N);
+    const int32_t a = largest_splits(c, B, N), b = splits_of_1024(c, B, N);
     return a > b ? a : b;
 }
 
@@ -470,7 +477,7 @@ int32_t vecinfer_decode_auto_splits(const vecinfer_cfg *cfg, int32_t B, int64_t 
 {
     if (!cfg || B < 1 || N < 1) return VECINFER_EINVAL;
     if (!cfg_ok(cfg)) return VECINFER_EUNSUPPORTED;
-    return auto_splits(cfg, B, N, Call::kWindow);      // the largest of the three
+    return largest_splits(cfg, B, N);
 }
 
 size_t vecinfer_decode_workspace_bytes(const vecinfer_cfg *cfg, int32_t B, int64_t N, int32_t num_splits)

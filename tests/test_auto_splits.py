@@ -71,6 +71,14 @@ def test_a_workspace_has_room_for_smaller_batches(heads):
             assert size <= vb.STATIC_SCRATCH_BYTES
 
 
+@pytest.mark.parametrize("N,splits", [(100, 4), (250, 8)])
+def test_a_workspace_has_room_for_a_step_with_wide_codes(N, splits):
+    """The step shares its search among splits of 32 tokens where attention and window calls take one."""
+    cfg = vb.Config(128, 32, 8, 8, 8, 12, 12)
+    assert vb.vecinfer_decode_auto_splits(cfg, 1, N) == splits
+    assert vb.vecinfer_decode_workspace_bytes(cfg, 1, N, 0) >= vb.vecinfer_decode_workspace_bytes(cfg, 1, N, splits)
+
+
 def _decode_state(cfg, B, N, seed, R=0):
     """Random codes, codebooks and query of one layer on the GPU (the values do not matter here, only
     that the calls run and agree)."""
