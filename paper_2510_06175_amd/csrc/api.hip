@@ -61,6 +61,34 @@ int num_cus()
 
 namespace {
 
+// The longest sequence that a step with 8-bit codes takes whole where there is room for s splits: below, the
+// merge launch costs more than the shared search and attention gain.  Time in splits over time whole, 4 / 1 or 8 / 1
+// heads (the merge of more than four query heads costs 5 us instead of 3), at s splits of 64 tokens:
+//   D = 128, s > 4, 4 / 1   250 tokens: d_v = 8 0.92, others 0.97 .. 1.06; 300 tokens: 0.82 .. 0.95
+//                   8 / 1   400 / 700 tokens: d_v = 4 1.06 .. 1.12 / 1.01 .. 1.08, others 0.98 .. 1.03 / 0.88 .. 0.96
+//            s = 4, 8 / 1   700 / 1000 tokens: d_k and d_v = 4 or 8, 4 1.11 / 1.04, others 1.01 .. 1.09 / 0.93 .. 1.0
+//            s = 3, 4 / 1   800 .. 1000 tokens: d = 4 1.02, others 0.87 .. 0.97; 8 / 1: 1.0 .. 1.13
+//            s = 2, 4 / 1   1100 / 2000 tokens: d = 4 1.14 / 1.05, others 0.89 .. 1.04 / 0.83 .. 0.97
+//                   8 / 1   d_v = 4 1.14 .. 1.22 / 1.04 .. 1.11, others 1.02 .. 1.10 / 0.92 .. 1.03
+//   D = 64   s > 3          300 / 600 tokens: d_k = 2 0.97 / 0.9 (d_v = 8 1.08 / 1.03), d = 4 1.0 / 1.0
+//                           1000 tokens: d_k = 2 or 4 0.81 .. 0.92, with a d = 8 side 1.0 .. 1.18
+//            s = 3          800 .. 1000 tokens: 0.96 .. 1.25
+int64_t step_whole(const vecinfer_cfg *c, int64_t s)
+{
+    const bool two_heads = c->num_q_heads > 4 * c->num_kv_heads;       // two groups of four query heads
+    const int dk = c->k_sub_dim, dv = c->v_sub_dim;
+    if (c->head_dim == 64) {
+        if (s <= 3) return 1024;
+        if (dk == 2) return dv == 8 ? 704 : 256;
+        return dk == 8 || dv == 8 ? 1024 : 704;
+    }
+    if (s == 2) return dv == 4 && (two_heads || dk == 4) ? 2047 : 1024;
+    if (s == 3) return two_heads || (dk == 4 && dv == 4) ? 1024 : 767;
+    if (!two_heads) return dv == 8 ? 192 : 256;
+    if (s == 4) return dk >= 4 && dv == 4 ? 1024 : 704;
+    return dv == 4 ? 704 : 448;
+}
+
 enum class Call { kAttention, kStep, kWindow };
 
 // Splits of a sequence: as many as fill the compute units once and no more (a compute unit holds one
@@ -75,10 +103,7 @@ enum class Call { kAttention, kStep, kWindow };
 //     heads 9.9 / 12.1 / 13.7 and 15.1 / 15.7 / 15.9), 768 with d_k = 2, whose keys are twice the bytes (600 / 1000
 //     tokens, d = 2: 11.2 / 13.6 us whole, 11.8 / 12.0), and twice that where two is all there is room for (128
 //     sequences, 1100 / 1900 tokens: 12.1 / 14.7 us whole, 14.4 / 16.0 in two; d = 2 14.8 / 19.2 and 15.6 / 19.1);
-//   a step shares the search for its new token too: two or three splits cost more than they gain on short
-//     sequences (16 sequences at 1000 / 8000 tokens 15.2 / 34.5 us whole, 17.0 / 28.3 in two; head dim 64, up
-//     to 3000 tokens: 14.8 whole, 13.3 in two; one at 300 / 1000 tokens 12.9 / 15.0 us whole, 14.1 / 14.4 in
-//     three);
+//   a step shares the search for its new token too, which pays sooner (step_whole);
 //   with a residual window the merge runs in any case (16 sequences at 1500 tokens: 17.8 us whole, 15.8 in
 //     two; up to 256 tokens nothing is gained: 200 tokens, 8 / 1 heads, d8b12, 17.7 us whole, 18.3 in four).
 // The merge reads 32 partials in one go, and every further 32 are another dependent round (about 2 us, 5
@@ -97,18 +122,22 @@ int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, Call call)
     const int64_t cap = (N + min_tokens - 1) / min_tokens;
     if (s > cap) s = cap;
     if (s > VECINFER_MAX_SPLITS) s = VECINFER_MAX_SPLITS;
+    const bool two_heads = c->num_q_heads > 4 * c->num_kv_heads;       // two groups of four query heads
     const bool many_bytes = (c->head_dim / c->k_sub_dim * c->k_bits + c->head_dim / c->v_sub_dim * c->v_bits) / 8 >= 96;
-    const int64_t most = N < (many_bytes && c->num_q_heads <= 4 * c->num_kv_heads ? 49152 : 57344) ? 32
-                         : N < (many_bytes ? 131072 : 196608)                                      ? 64
-                         : N < 524288                                                              ? 128
-                                                                                                   : VECINFER_MAX_SPLITS;
+    const int64_t most = N < (many_bytes && !two_heads ? 49152 : 57344) ? 32
+                         : N < (many_bytes ? 131072 : 196608)           ? 64
+                         : N < 524288                                   ? 128
+                                                                        : VECINFER_MAX_SPLITS;
     if (s > most) s = most;
     const bool long_keys = c->k_sub_dim == 2 && c->head_dim == 128;
-    const bool whole = call == Call::kWindow      ? N <= 256
-                       : call == Call::kAttention ? N <= (long_keys && s > 3 && c->num_q_heads <= 4 * c->num_kv_heads ? 768 : 1024) ||
-                                                        (s == 2 && N < (long_keys ? 1792 : 2048))
-                                                  : !wide(c) && ((s == 2 && N < (c->head_dim == 64 ? 1024 : 2048)) || (s == 3 && N < 768));
-    if (whole || s < 1) s = 1;
+    int64_t whole;                      // the longest sequence that is not split
+    if (call == Call::kWindow)
+        whole = 256;
+    else if (call == Call::kAttention)
+        whole = s == 2 ? (long_keys ? 1791 : 2047) : (long_keys && s > 3 && !two_heads ? 768 : 1024);
+    else
+        whole = wide(c) ? 0 : step_whole(c, s);
+    if (N <= whole || s < 1) s = 1;
     return (int32_t)s;
 }
 

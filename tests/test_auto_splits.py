@@ -169,7 +169,25 @@ CHOICES = [
     ("attention", (128, 4, 1, 2, 4), 8, 768, 0, 0, 1, 12),
     ("attention", (128, 4, 1, 2, 4), 8, 769, 0, 0, 13, 1),
     ("attention", (128, 4, 1, 2, 4), 80, 1024, 0, 0, 1, 3),
+    # the step: whole where the search for the new token is not worth a merge
     ("step", (128, 4, 1, 4, 4), 8, 1000, 0, 0, 16, 1),
+    ("step", (128, 8, 1, 4, 4), 8, 704, 0, 0, 1, 11),
+    ("step", (128, 8, 1, 4, 4), 8, 705, 0, 0, 12, 1),
+    ("step", (128, 8, 1, 2, 2), 8, 600, 0, 0, 10, 1),
+    ("step", (128, 8, 1, 4, 4), 64, 1024, 0, 0, 1, 4),
+    ("step", (128, 8, 1, 8, 8), 64, 705, 0, 0, 4, 1),
+    ("step", (128, 4, 1, 4, 4), 85, 1024, 0, 0, 1, 3),
+    ("step", (128, 4, 1, 2, 2), 85, 768, 0, 0, 3, 1),
+    ("step", (128, 4, 1, 4, 4), 128, 2047, 0, 0, 1, 2),
+    ("step", (128, 8, 1, 2, 4), 128, 2047, 0, 0, 1, 2),
+    ("step", (128, 4, 1, 8, 8), 128, 1025, 0, 0, 2, 1),
+    ("step", (128, 4, 1, 8, 8, 12, 12), 128, 700, 0, 0, 2, 1),
+    ("step", (64, 4, 1, 4, 4), 8, 704, 0, 0, 1, 11),
+    ("step", (64, 4, 1, 2, 2), 8, 600, 0, 0, 10, 1),
+    ("step", (64, 4, 1, 2, 8), 8, 705, 0, 0, 12, 1),
+    ("step", (64, 4, 1, 8, 8), 8, 1024, 0, 0, 1, 16),
+    ("step", (64, 4, 1, 4, 8), 8, 1025, 0, 0, 17, 1),
+    ("step", (64, 4, 1, 2, 2), 85, 1024, 0, 0, 1, 3),
     ("window", (128, 4, 1, 4, 4), 8, 1000, 0, 0, 16, 1),
 ]
 
