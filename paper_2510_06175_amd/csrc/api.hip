@@ -97,6 +97,10 @@ enum class Call { kAttention, kStep, kWindow };
 // tokens each (a step at 1000 tokens: 15.0 us whole, 12.3 in 8 splits, 11.9 in 16; 8000: 15.0 in 8, 12.7 in
 // 32), 32 tokens with codes wider than 8 bits, where the search for a fused new token is what the
 // workgroups share (d8b12, 1000 tokens: 34.8 us whole, 17.0 in 4, 13.6 in 8).
+// Sequences of different lengths are the exception: the short ones' workgroups end early and make room for
+// one more split of the others, where the splits are long (4096 tokens) and the sequences are more than a few
+// (from N / 8 to N tokens: 17 x 8 heads, 30000, d = 2 157 us whole, 90 in two; 9 x 8, 30000, d = 8 42.6 in three, 35.4
+// in four; 6 x 8, 120000, d = 2 130 in five, 111 in six; but 3 x 8, 30000 22.9 in ten, 28.6 in eleven).
 // What a split costs is the merge launch, 3 to 5 us (5 with more than four query heads per KV head):
 //   attention alone has nothing but its tokens to share: whole up to 1024 of them (8 sequences, 4 / 1
 //     heads: 250 / 600 / 1000 tokens 8.3 / 9.9 / 11.1 us whole, 11.4 / 11.6 / 11.6 in 4 / 10 / 16 splits; 8 / 1
@@ -114,10 +118,11 @@ enum class Call { kAttention, kStep, kWindow };
 //   4 / 1, d = 4  17.9 18.2 -   -  18.7 18.1 20.4 28.2   -  20.8 22.1 28.8   - 26.8 25.2 30.7   - - 36.9 37.4
 //   8 / 1, d = 4  24.9 26.7 -   -  26.0 26.6 32.4 48.2   -  30.5 34.7 48.8   - 38.7 39.1 51.4   - - 55.5 61.2
 //   4 / 1, d = 2  22.2 20.6 -   -  23.4 21.0 21.8 28.9   -  26.0 25.5 30.7   - 35.9 30.5 34.6   - - 50.1 45.8
-int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, Call call)
+int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, Call call, bool ragged = false)
 {
     const int64_t groups = (int64_t)B * c->num_kv_heads;
     int64_t s = num_cus() / groups;
+    if (ragged && B > 4 && N >= 4096 * (s > 1 ? s : 1)) s = (num_cus() + groups - 1) / groups;
     const int64_t min_tokens = wide(c) ? 32 : 64;
     const int64_t cap = (N + min_tokens - 1) / min_tokens;
     if (s > cap) s = cap;
@@ -325,7 +330,7 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     const bool use_roles = variant == VECINFER_VARIANT_ROLES;
     const bool use_mfma = use_roles || (variant == VECINFER_VARIANT_MFMA) || (variant == VECINFER_VARIANT_AUTO && mfma_ok);
 
-    int32_t S = N == 0 ? 1 : (num_splits ? num_splits : use_mfma ? auto_splits(cfg, B, N, call) : lut_splits(cfg, B, N));
+    int32_t S = N == 0 ? 1 : (num_splits ? num_splits : use_mfma ? auto_splits(cfg, B, N, call, seq_lens != nullptr) : lut_splits(cfg, B, N));
     WorkspaceLayout w = ws_layout(cfg, B, S);
     if (num_splits == 0)                // fewer where the workspace has no room for that many
         while (S > 1 && workspace_bytes < w.total) w = ws_layout(cfg, B, --S);

@@ -188,6 +188,13 @@ CHOICES = [
     ("step", (64, 4, 1, 8, 8), 8, 1024, 0, 0, 1, 16),
     ("step", (64, 4, 1, 4, 8), 8, 1025, 0, 0, 17, 1),
     ("step", (64, 4, 1, 2, 2), 85, 1024, 0, 0, 1, 3),
+    # sequences of different lengths: one more split where they are long
+    ("step", (128, 4, 1, 4, 4), 136, 4096, 1, 0, 2, 1),
+    ("attention", (128, 4, 1, 4, 4), 136, 4095, 1, 0, 1, 2),
+    ("window", (128, 4, 1, 4, 4), 100, 8192, 1, 0, 3, 2),
+    ("attention", (128, 16, 8, 8, 8), 5, 24576, 1, 0, 7, 6),
+    ("attention", (128, 16, 8, 8, 8), 5, 24576, 0, 0, 6, 7),
+    ("step", (128, 16, 8, 8, 8), 3, 50000, 1, 0, 10, 11),
     ("window", (128, 4, 1, 4, 4), 8, 1000, 0, 0, 16, 1),
 ]
 
