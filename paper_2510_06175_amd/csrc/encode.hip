@@ -150,13 +150,6 @@ constexpr int vq_group(int M)
     return M < most ? M : most;
 }
 
-// Wavefronts: 16 (four per SIMD, 128 registers) from 16 sub-spaces on, otherwise 8.
-template <int d, bool kAccumulate, int kGroup>
-constexpr int vq_block(int M)
-{
-    return vq_group<d, kAccumulate, kGroup>(M) >= 16 ? 2 * kVqBlock : kVqBlock;
-}
-
 template <int D, int d, bool kAccumulate, int kGroup>
 constexpr size_t vq_smem_bytes()
 {
@@ -173,19 +166,22 @@ struct KmeansState {
     int32_t pad;
 };
 
-template <int D, int d, bool kTransform, bool kAccumulate, int kGroup>
-__global__ __launch_bounds__((vq_block<d, kAccumulate, kGroup>(D / d))) __attribute__((amdgpu_waves_per_eu(kAccumulate && d == 8 ? 2 : 4))) void vq_tile_kernel(EncodeParams p, int tiles_per_wg, int iter, KmeansState *state)
+// NW: wavefronts.  16 (four per SIMD, 128 registers) for a cache fill of 16 sub-spaces or more; for K-Means 8, and
+// 16 where the runs are long (launch_kmeans_tiles); 8 for 8 sub-spaces.
+template <int D, int d, bool kTransform, bool kAccumulate, int kGroup, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kAccumulate && NW == 8 ? 2 : 4)))
+void vq_tile_kernel(EncodeParams p, int tiles_per_wg, int iter, KmeansState *state)
 {
     constexpr int M = D / d;
     constexpr int MSW = vq_group<d, kAccumulate, kGroup>(M); // sub-spaces of the workgroup
-    constexpr int BLOCK = vq_block<d, kAccumulate, kGroup>(M), NW = BLOCK / 64;
-    constexpr int SPW = (MSW + NW - 1) / NW;               // sub-spaces per wavefront: 1, 2 or 4
+    constexpr int BLOCK = 64 * NW;
+    constexpr int SPW = MSW / NW;                          // sub-spaces per wavefront: 1 or 2
     static_assert(MSW % NW == 0 && M % MSW == 0, "whole groups, dealt evenly to the wavefronts");
     // K-Means (the sums need the room) and small groups keep only their channels of the tile
     constexpr int NCH = kAccumulate || kGroup != kVqAll ? MSW * d : D;
     constexpr int XS = NCH + 4;                            // row stride of the transformed tile
     constexpr int TB = ScreenTab<d>::kBytes;
-    constexpr int DEPTH = kAccumulate && d == 8 ? 2 : 1;   // (K-Means at d = 8: one workgroup of 8 wavefronts fills the LDS)
+    constexpr int DEPTH = kAccumulate && NW == 8 ? 2 : 1;  // (K-Means: one workgroup fills the LDS, two wavefronts per SIMD)
     extern __shared__ __align__(16) unsigned char vq_smem[];
     unsigned char *const tab_s = vq_smem;                                          // [MSW] search tables
     float *const x_s = reinterpret_cast<float *>(tab_s + MSW * TB);                // [64][XS] transformed tile
@@ -886,32 +882,54 @@ int launch_encode_wide(const EncodeParams &p, hipStream_t stream)
     }
 }
 
-// vq_tile_kernel over the T tokens of p.
-template <int D, int d, bool kAccumulate, int kGroup = kVqAll>
-int launch_vq_tiles(const EncodeParams &p, int iter, void *state, hipStream_t stream)
+// vq_tile_kernel over the T tokens of p, `per` tiles per workgroup.
+template <int D, int d, bool kAccumulate, int kGroup, int NW>
+int launch_vq_runs(const EncodeParams &p, long long per, int iter, void *state, hipStream_t stream)
 {
     constexpr int M = D / d, MSW = vq_group<d, kAccumulate, kGroup>(M);
     constexpr size_t smem = vq_smem_bytes<D, d, kAccumulate, kGroup>();
     static_assert(smem <= 160 * 1024, "LDS of a compute unit");
     static const bool configured =
-        hipFuncSetAttribute(reinterpret_cast<const void *>(vq_tile_kernel<D, d, true, kAccumulate, kGroup>),
+        hipFuncSetAttribute(reinterpret_cast<const void *>(vq_tile_kernel<D, d, true, kAccumulate, kGroup, NW>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess &&
-        hipFuncSetAttribute(reinterpret_cast<const void *>(vq_tile_kernel<D, d, false, kAccumulate, kGroup>),
+        hipFuncSetAttribute(reinterpret_cast<const void *>(vq_tile_kernel<D, d, false, kAccumulate, kGroup, NW>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess;
     if (!configured) return -4;
     const long long tiles = (p.T + kEncTokens - 1) / kEncTokens;
-    constexpr int block = vq_block<d, kAccumulate, kGroup>(M);
-    // (K-Means: a flush of 256 (d + 1) atomics per sub-space at about 90 G/s against a tile of about 6 us)
-    const long long per = tile_run(tiles, (long long)(M / MSW) * p.B * p.Hkv, 0.5,
-                                   kAccumulate ? MSW * kCentroids * (d + 1) / (90e9 * 6e-6) : 0.0);
     dim3 grid((unsigned)((tiles + per - 1) / per), M / MSW, p.B * p.Hkv);
     if (p.lam)
-        hipLaunchKernelGGL((vq_tile_kernel<D, d, true, kAccumulate, kGroup>), grid, dim3(block), smem, stream, p, (int)per, iter,
-                           static_cast<KmeansState *>(state));
+        hipLaunchKernelGGL((vq_tile_kernel<D, d, true, kAccumulate, kGroup, NW>), grid, dim3(64 * NW), smem, stream, p,
+                           (int)per, iter, static_cast<KmeansState *>(state));
     else
-        hipLaunchKernelGGL((vq_tile_kernel<D, d, false, kAccumulate, kGroup>), grid, dim3(block), smem, stream, p, (int)per, iter,
-                           static_cast<KmeansState *>(state));
+        hipLaunchKernelGGL((vq_tile_kernel<D, d, false, kAccumulate, kGroup, NW>), grid, dim3(64 * NW), smem, stream, p,
+                           (int)per, iter, static_cast<KmeansState *>(state));
     return hipGetLastError() == hipSuccess ? 0 : -4;
+}
+
+template <int D, int d, int kGroup = kVqAll>
+int launch_fill_tiles(const EncodeParams &p, hipStream_t stream)
+{
+    constexpr int M = D / d, MSW = vq_group<d, false, kGroup>(M);
+    const long long tiles = (p.T + kEncTokens - 1) / kEncTokens;
+    const long long per = tile_run(tiles, (long long)(M / MSW) * p.B * p.Hkv, 0.5);
+    return launch_vq_runs<D, d, false, kGroup, (MSW >= 16 ? 16 : 8)>(p, per, 0, nullptr, stream);
+}
+
+// K-Means: 8 wavefronts per workgroup, 16 with runs of 48 tiles or more.  A workgroup fills the LDS alone, so 16
+// wavefronts hide more of the searches, but each has half of the registers and half of the sub-spaces between
+// two barriers.  4 iterations and the smoothing factors, 8 heads, D = 128, 8 / 16 wavefronts: d = 4, 2000 tokens (runs of
+// 4 tiles) 252 / 286 us, 8000 (12) 443 / 504, 32768 (32) 1133 / 1130, 65536 (64) 2052 / 1958; d = 2, 2000 (4) 292 / 373, 16000
+// (32) 1007 / 1013, 32768 (64) 1827 / 1750.
+template <int D, int d>
+int launch_kmeans_tiles(const EncodeParams &p, int iter, void *state, hipStream_t stream)
+{
+    constexpr int M = D / d, MSW = vq_group<d, true, kVqAll>(M);
+    const long long tiles = (p.T + kEncTokens - 1) / kEncTokens;
+    // (a flush of 256 (d + 1) atomics per sub-space at about 90 G/s against a tile of about 6 us)
+    const long long per = tile_run(tiles, (long long)(M / MSW) * p.B * p.Hkv, 0.5, MSW * kCentroids * (d + 1) / (90e9 * 6e-6));
+    if constexpr (MSW == 16)
+        if (per >= 48) return launch_vq_runs<D, d, true, kVqAll, 16>(p, per, iter, state, stream);
+    return launch_vq_runs<D, d, true, kVqAll, 8>(p, per, iter, state, stream);
 }
 
 template <int D, int d>
@@ -936,10 +954,10 @@ int launch_typed(const EncodeParams &p, hipStream_t stream)
     constexpr int M = D / d, all = M < kVqAll ? M : kVqAll;
     const long long tiles = (p.T + kEncTokens - 1) / kEncTokens * p.B * p.Hkv;
     if constexpr (all > 8)
-        if (tiles * (M / 8) <= num_cus()) return launch_vq_tiles<D, d, false, 8>(p, 0, nullptr, stream);
+        if (tiles * (M / 8) <= num_cus()) return launch_fill_tiles<D, d, 8>(p, stream);
     if constexpr (all > 16)
-        if (tiles * (M / 16) <= num_cus()) return launch_vq_tiles<D, d, false, 16>(p, 0, nullptr, stream);
-    return launch_vq_tiles<D, d, false>(p, 0, nullptr, stream);
+        if (tiles * (M / 16) <= num_cus()) return launch_fill_tiles<D, d, 16>(p, stream);
+    return launch_fill_tiles<D, d>(p, stream);
 }
 
 template <int D, int dk>
@@ -1002,12 +1020,12 @@ int launch_kmeans_assign(const EncodeParams &p, int iter, void *state, hipStream
     if ((p.T + kEncTokens - 1) / kEncTokens > 0x7fffffffLL || p.B * p.Hkv > 65535) return -2;
     const int key = p.D * 10 + p.d;
     switch (key) {
-    case 1282: return launch_vq_tiles<128, 2, true>(p, iter, state, stream);
-    case 1284: return launch_vq_tiles<128, 4, true>(p, iter, state, stream);
-    case 1288: return launch_vq_tiles<128, 8, true>(p, iter, state, stream);
-    case 642: return launch_vq_tiles<64, 2, true>(p, iter, state, stream);
-    case 644: return launch_vq_tiles<64, 4, true>(p, iter, state, stream);
-    case 648: return launch_vq_tiles<64, 8, true>(p, iter, state, stream);
+    case 1282: return launch_kmeans_tiles<128, 2>(p, iter, state, stream);
+    case 1284: return launch_kmeans_tiles<128, 4>(p, iter, state, stream);
+    case 1288: return launch_kmeans_tiles<128, 8>(p, iter, state, stream);
+    case 642: return launch_kmeans_tiles<64, 2>(p, iter, state, stream);
+    case 644: return launch_kmeans_tiles<64, 4>(p, iter, state, stream);
+    case 648: return launch_kmeans_tiles<64, 8>(p, iter, state, stream);
     default: return -2;
     }
 }

@@ -263,3 +263,42 @@ def test_train_heavily_shared_codes(n_distinct):
     assert abs(e[0] - ref_e) <= 2e-5 * ref_e
     _check_means(x, None, cb, codes, counts, "shared codes", cb_before=cb0)
     assert (counts > 0).sum(axis=2).max() <= n_distinct
+
+
+@pytest.mark.parametrize("keys", [True, False])
+@pytest.mark.parametrize("D,d,T", [(128, 4, 49181), (128, 2, 24601), (64, 4, 98323), (64, 2, 49181)])
+def test_step_with_long_runs(D, d, T, keys):
+    """More than 48 tiles per workgroup of 16 sub-spaces (8 KV heads, 256 compute units), where 16
+    wavefronts share them: codes those of the cache fill, counts their histogram, centroids the means of
+    the sub-vectors as the cache fill sees them."""
+    cfg = vb.Config(D, 8, 8, d, d)
+    M = D // d
+    g = torch.Generator(device="cuda").manual_seed(D + d)
+    x = torch.randn((1, 8, T, D), generator=g, device="cuda").half()
+    lam = torch.exp(0.3 * torch.randn((8, D), generator=g, device="cuda")) if keys else None
+    cb = torch.randn((8, M, 256, d), generator=g, device="cuda").half()
+    out, counts = torch.empty_like(cb), torch.empty((8, M, 256), dtype=torch.int32, device="cuda")
+    codes, want = (torch.zeros((1, 8, T, M), dtype=torch.uint8, device="cuda") for _ in range(2))
+    vb.vecinfer_kmeans_step(cfg, x, lam, cb, out, codes, vb.new_kmeans_workspace(cfg, keys), counts=counts)
+    if keys:
+        vb.vecinfer_encode_keys(cfg, x, lam, cb, want)
+    else:
+        vb.vecinfer_encode_values(cfg, x, cb, want)
+    assert torch.equal(codes, want)
+    # (on the host, in 64 bits: the transform as a product with the Hadamard matrix)
+    v = x[0].cpu().double()
+    if keys:
+        h = torch.ones((1, 1), dtype=torch.float64)
+        while h.shape[0] < D:
+            h = torch.cat([torch.cat([h, h], 1), torch.cat([h, -h], 1)], 0)
+        v = (v / lam.cpu().double()[:, None, :]) @ (h / D ** 0.5)
+    c, n = codes[0].cpu().long(), counts.cpu()
+    for head, m in ((0, 0), (3, M // 2), (7, M - 1)):
+        hist = torch.bincount(c[head, :, m], minlength=256)
+        assert torch.equal(hist.int(), n[head, m])
+        sums = torch.zeros((256, d), dtype=torch.float64).index_add_(0, c[head, :, m], v[head, :, m * d:(m + 1) * d])
+        full = hist > 0
+        got = out[head, m].cpu().double()
+        assert torch.equal(got[~full], cb[head, m].cpu().double()[~full])
+        # fp16 centroids (2^-11), fp32 sums of values of both signs
+        np.testing.assert_allclose(got[full], sums[full] / hist[full, None], rtol=1.5e-3, atol=1e-5)
