@@ -10,7 +10,6 @@ from __future__ import annotations
 import ctypes as C
 import os
 from dataclasses import dataclass
-from functools import cached_property
 
 import torch
 
@@ -39,6 +38,24 @@ class _Cfg(C.Structure):
                                          "v_sub_dim", "k_bits", "v_bits", "v_tiled")]
 
 
+class _once:
+    """A value worked out when it is first asked for and then kept in the object's own dictionary, which
+    from then on answers by itself.  (functools.cached_property takes a lock for it; here two threads may
+    both work it out, to the same value.)"""
+
+    def __init__(self, f):
+        self.f = f
+
+    def __set_name__(self, owner, name):
+        self.name = name
+
+    def __get__(self, obj, owner=None):
+        if obj is None:
+            return self
+        v = obj.__dict__[self.name] = self.f(obj)
+        return v
+
+
 @dataclass(frozen=True)
 class Config:
     """Mirror of ``vecinfer_cfg``."""
@@ -56,27 +73,27 @@ class Config:
                     self.v_sub_dim, self.k_bits, self.v_bits, self.v_tiled)
 
     # What every call needs of a configuration, worked out once per (immutable) object.
-    @cached_property
+    @_once
     def _c(self) -> _Cfg:
         return self.c()
 
-    @cached_property
+    @_once
     def _lam_shape(self) -> tuple:
         return (self.num_kv_heads, self.head_dim)
 
-    @cached_property
+    @_once
     def _cb_k(self) -> tuple:
         return self.cb_shape(True)
 
-    @cached_property
+    @_once
     def _cb_v(self) -> tuple:
         return self.cb_shape(False)
 
-    @cached_property
+    @_once
     def _row_k(self) -> int:
         return self.row_bytes(True)
 
-    @cached_property
+    @_once
     def _row_v(self) -> int:
         return self.row_bytes(False)
 
