@@ -124,17 +124,17 @@ __device__ __forceinline__ void tile_finish(const EncodeParams &p, const TileRow
 
 // Cache fill (Eq. 2, 3, 6, 8) and K-Means assignment (Sec. 2.2), 8-bit codes: one kernel.
 //
-// A workgroup (8 wavefronts) takes a group of MSW sub-spaces of one (sequence, KV head) and walks
+// A workgroup (8 or 16 wavefronts) takes a group of MSW sub-spaces of one (sequence, KV head) and walks
 // over a run of `tiles_per_wg` 64-token tiles, so that the group's search tables are built once
-// per run: per sub-space the fp16 centroids and -sigma |c|^2 / 2 (encode_screen.h), 3 to 5 KB.
-// Per tile: the rows are transformed into LDS (phase 1 above; once per group of sub-spaces, so
-// M / MSW times in all), every wavefront searches MSW / 8 sub-spaces for the 64 tokens (a lane
+// per run: per sub-space one entry per centroid with its fp16 values and -sigma |c|^2 / 2 (encode_screen.h),
+// 2 to 5 KB.  Per tile: the rows are transformed into LDS (phase 1 above; once per group of sub-spaces, so
+// M / MSW times in all), every wavefront searches one or two sub-spaces for the 64 tokens (a lane
 // owns a token at the end), and the group's MSW code bytes per token go out as 8- or 16-byte
 // stores (tiled value codes: byte by byte, each to its place in the token's 64-token block).
 // kAccumulate (K-Means): every sub-vector is also added to the sum of its centroid in LDS
 // (ds_add_f32; a run meets each centroid many times) and its squared distance to the run's error;
-// at the end of the run the partial sums go to memory, one atomic per non-empty centroid, and the
-// error to the training state.
+// at the end of the run the partial sums go to memory, one atomic per non-empty centroid and channel, and
+// the error to the training state.
 constexpr int kVqBlock = 512;
 
 // Sub-spaces per workgroup: all of them for the cache fill (32 at most: d = 2 at D = 128 takes two
@@ -525,11 +525,11 @@ __device__ __forceinline__ void store_packed_rows(const EncodeParams &p, const u
 }
 
 // Tiled kernel: as vq_tile_kernel, with one table for all sub-spaces.  A workgroup (8 wavefronts)
-// builds the search tables of its KV head's codebook once (the fp16 table as it is, 8 - 64 KB, and
-// -sigma |c|^2 / 2, 4 - 16 KB) and walks over a run of 64-token tiles; per tile every wavefront
-// searches M / 8 sub-spaces, 256 centroids at a time (screen_search_shared: matrix-core screen,
-// exact fp32 distances of what it keeps, the plain search where it gives up), and the tile's codes
-// are packed into rows.  K-Means (km_sums set): every sub-vector also joins the sum of its centroid
+// builds the search table of its KV head's codebook once (an entry per centroid as in vq_tile_kernel, 12 - 80 KB)
+// and walks over a run of 64-token tiles; per tile every wavefront searches M / 8 sub-spaces
+// (screen_search_shared: the matrix-core screen goes through the codebook in 4 or 8 chunks, marks are taken once
+// at the end, exact fp32 distances of what is marked; the plain search where there are no finite scores),
+// and the tile's codes are packed into rows.  K-Means (km_sums set): every sub-vector also joins the sum of its centroid
 // in the head's one table (fp32 hardware atomics, order of the additions not fixed) and its squared
 // distance the iteration's error.
 template <int D, int d, int BITS>
@@ -811,13 +811,15 @@ int launch_append_wide(const EncodeParams &pk, const EncodeParams &pv, hipStream
 }
 
 // Tiles per workgroup of the tile kernels, for `tiles` tiles of each of `groups` (sequence, KV head,
-// sub-space group)s.  A compute unit holds one workgroup at a time, so what the launch takes is the
-// number of rounds of workgroups times a run, and a run is its tiles plus `setup`, the search tables;
-// for K-Means every workgroup's flush of its sums comes on top (`flush`: atomics, which the memory takes
-// one workgroup after the other), both in tiles.  The least of that over a quarter to eight rounds.
-long long tile_run(long long tiles, long long groups, double setup, double flush = 0.0)
+// sub-space group)s, where `cus` workgroups run at once.  What the launch takes is the number of rounds of
+// workgroups times a run, and a run is its tiles plus `setup`, the search tables; for K-Means every
+// workgroup's flush of its sums comes on top (`flush`: atomics, which the memory takes one workgroup after
+// the other), both in tiles.  The least of that over a quarter to eight rounds.
+// Set-up, from one round of workgroups with 1 / 2 / 4 / 8 tiles each (us, keys, launch included): d = 4, 32 sub-spaces
+// 17.5 / 27.3 / 47.0 / 82.9, d = 8 12.2 / 19.3 / 33.5 / 60.7: half a tile; 12-bit codes, d = 8 54 / 98 / 189 / 352, d = 4 77 / 147 / 286 /
+// 566: a tenth.
+long long tile_run(long long tiles, long long groups, long long cus, double setup, double flush = 0.0)
 {
-    const long long cus = num_cus();
     long long best_per = tiles < 256 ? tiles : 256;
     double best = 1e300;
     for (int q = flush > 0.0 ? 1 : 4; q <= 32; q += q < 4 ? 1 : 4) {
@@ -857,7 +859,7 @@ int launch_wide_typed(const EncodeParams &p, hipStream_t stream)
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess;
     if (!configured) return -4;
     const long long tiles = (p.T + kEncTokens - 1) / kEncTokens;
-    const long long per = tile_run(tiles, (long long)p.B * p.Hkv, 0.1);
+    const long long per = tile_run(tiles, (long long)p.B * p.Hkv, num_cus(), 0.1);
     dim3 grid((unsigned)((tiles + per - 1) / per), 1, p.B * p.Hkv);
     const size_t smem_now = p.km_sums ? smem : smem_fill;     // (the partial sums only where they are used)
     if (p.lam)
@@ -911,8 +913,10 @@ int launch_fill_tiles(const EncodeParams &p, hipStream_t stream)
 {
     constexpr int M = D / d, MSW = vq_group<d, false, kGroup>(M);
     const long long tiles = (p.T + kEncTokens - 1) / kEncTokens;
-    const long long per = tile_run(tiles, (long long)(M / MSW) * p.B * p.Hkv, 0.5);
-    return launch_vq_runs<D, d, false, kGroup, (MSW >= 16 ? 16 : 8)>(p, per, 0, nullptr, stream);
+    // 16 wavefronts fill a compute unit; two workgroups of 8 sub-spaces fit (8 wavefronts, 34 .. 59 KB of LDS each)
+    constexpr int NW = MSW >= 16 ? 16 : 8;
+    const long long per = tile_run(tiles, (long long)(M / MSW) * p.B * p.Hkv, 16 / NW * num_cus(), 0.5);
+    return launch_vq_runs<D, d, false, kGroup, NW>(p, per, 0, nullptr, stream);
 }
 
 // K-Means: 8 wavefronts per workgroup, 16 with runs of 48 tiles or more.  A workgroup fills the LDS alone, so 16
@@ -926,7 +930,8 @@ int launch_kmeans_tiles(const EncodeParams &p, int iter, void *state, hipStream_
     constexpr int M = D / d, MSW = vq_group<d, true, kVqAll>(M);
     const long long tiles = (p.T + kEncTokens - 1) / kEncTokens;
     // (a flush of 256 (d + 1) atomics per sub-space at about 90 G/s against a tile of about 6 us)
-    const long long per = tile_run(tiles, (long long)(M / MSW) * p.B * p.Hkv, 0.5, MSW * kCentroids * (d + 1) / (90e9 * 6e-6));
+    const long long per = tile_run(tiles, (long long)(M / MSW) * p.B * p.Hkv, num_cus(), 0.5,
+                                   MSW * kCentroids * (d + 1) / (90e9 * 6e-6));
     if constexpr (MSW == 16)
         if (per >= 48) return launch_vq_runs<D, d, true, kVqAll, 16>(p, per, iter, state, stream);
     return launch_vq_runs<D, d, true, kVqAll, 8>(p, per, iter, state, stream);
@@ -944,13 +949,13 @@ int launch_typed(const EncodeParams &p, hipStream_t stream)
         return hipGetLastError() == hipSuccess ? 0 : -4;
     }
     // Few tiles (a residual window flushed into the cache, a short prompt): the smallest group of
-    // sub-spaces whose workgroups all run at once.  (A compute unit holds one at a time: two rounds of
-    // small groups take longer than one of large ones.)  D = 128, d = 4, keys / values, us per call:
+    // sub-spaces of which every compute unit gets one workgroup at most.  (Two workgroups of 8 fit a compute
+    // unit, but take longer there than one of 16.)  D = 128, d = 4, keys / values, us per call:
     //   tiles x heads    8 per workgroup     16 per workgroup    all 32
-    //        64            8.2 / 5.7               -            15.0 / 13.7
-    //       128           14.7 / 9.8           10.8 / 8.4       15.4 / 13.7
-    //       256           26.6 / 17.6              -            15.9 / 14.2
-    // (before 16 wavefronts per workgroup, which take 10.0 / 7.0 at 128 with 16 and need the same order.)
+    //        64            8.3 / 5.9            9.6 / 7.8         14.0 / 11.6
+    //       128           13.1 / 8.5           10.0 / 8.0         14.6 / 11.9
+    //       192           17.7 / 11.0          15.6 / 11.7        14.9 / 12.2
+    //       256           22.1 / 13.2          15.8 / 11.7        15.3 / 12.2
     constexpr int M = D / d, all = M < kVqAll ? M : kVqAll;
     const long long tiles = (p.T + kEncTokens - 1) / kEncTokens * p.B * p.Hkv;
     if constexpr (all > 8)
