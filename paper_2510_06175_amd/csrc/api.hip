@@ -98,9 +98,10 @@ enum class Call { kAttention, kStep, kWindow };
 // 32), 32 tokens with codes wider than 8 bits, where the search for a fused new token is what the
 // workgroups share (d8b12, 1000 tokens: 34.8 us whole, 17.0 in 4, 13.6 in 8).
 // Sequences of different lengths are the exception: the short ones' workgroups end early and make room for
-// one more split of the others, where the splits are long (4096 tokens) and the sequences are more than a few
-// (from N / 8 to N tokens: 17 x 8 heads, 30000, d = 2 157 us whole, 90 in two; 9 x 8, 30000, d = 8 42.6 in three, 35.4
-// in four; 6 x 8, 120000, d = 2 130 in five, 111 in six; but 3 x 8, 30000 22.9 in ten, 28.6 in eleven).
+// one more split of the others, where the splits are long (4096 tokens, 8192 where one round occupies nine tenths of
+// the compute units and a token has less than 128 bytes) and the sequences are more than a few (from N / 8 to N
+// tokens: 17 x 8 heads, 30000, d = 2 157 us whole, 90 in two; 9 x 8, 30000, d = 8 42.6 in three, 35.4 in four; 5 x 8, 60000,
+// d = 4, ten thousand a split, 1.10 of the time in five, but 30000 0.77; 3 x 8, 30000 22.9 in ten, 28.6 in eleven).
 // What a split costs is the merge launch, 3 to 5 us (5 with more than four query heads per KV head):
 //   attention alone has nothing but its tokens to share: whole up to 1024 of them (8 sequences, 4 / 1
 //     heads: 250 / 600 / 1000 tokens 8.3 / 9.9 / 11.1 us whole, 11.4 / 11.6 / 11.6 in 4 / 10 / 16 splits; 8 / 1
@@ -122,15 +123,18 @@ int32_t auto_splits(const vecinfer_cfg *c, int32_t B, int64_t N, Call call, bool
 {
     const int64_t groups = (int64_t)B * c->num_kv_heads;
     int64_t s = num_cus() / groups;
-    if (ragged && B > 4 && N >= 4096 * (s > 1 ? s : 1)) s = (num_cus() + groups - 1) / groups;
+    const int bytes = (c->head_dim / c->k_sub_dim * c->k_bits + c->head_dim / c->v_sub_dim * c->v_bits) / 8;
+    if (ragged && B > 4) {
+        const int64_t line = bytes >= 128 || 10 * s * groups < 9 * num_cus() ? 4096 : 8192;
+        if (N >= line * (s > 1 ? s : 1)) s = (num_cus() + groups - 1) / groups;
+    }
     const int64_t min_tokens = wide(c) ? 32 : 64;
     const int64_t cap = (N + min_tokens - 1) / min_tokens;
     if (s > cap) s = cap;
     if (s > VECINFER_MAX_SPLITS) s = VECINFER_MAX_SPLITS;
     const bool two_heads = c->num_q_heads > 4 * c->num_kv_heads;       // two groups of four query heads
-    const bool many_bytes = (c->head_dim / c->k_sub_dim * c->k_bits + c->head_dim / c->v_sub_dim * c->v_bits) / 8 >= 96;
-    const int64_t most = N < (many_bytes && !two_heads ? 49152 : 57344) ? 32
-                         : N < (many_bytes ? 131072 : 196608)           ? 64
+    const int64_t most = N < (bytes >= 96 && !two_heads ? 49152 : 57344) ? 32
+                         : N < (bytes >= 96 ? 131072 : 196608)           ? 64
                          : N < 524288                                   ? 128
                                                                         : VECINFER_MAX_SPLITS;
     if (s > most) s = most;

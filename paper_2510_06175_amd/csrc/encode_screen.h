@@ -362,7 +362,9 @@ __device__ __forceinline__ const unsigned char *screen_lane_tab(const unsigned c
 // DEPTH = 2 (workgroups that leave a SIMD two wavefronts): the MFMAs of a step are issued ahead of the
 // maxima of the step before, so that the matrix cores and the vector ALU work side by side within
 // the wavefront.  DEPTH = 1 (four wavefronts per SIMD, which do that among themselves): one set of
-// results, 32 registers less, which is what lets the kernel stay within 128.
+// results, 32 registers less, which is what brings the kernel to 128.  (Not quite with 32 sub-spaces, two searches
+// per wavefront: the keys' fills spill 7, 5 and 3 registers at D = 128, d = 4 and 2, and D = 64, d = 2, the values' fill
+// at D = 128, d = 4 spills one.)
 // (The fences keep it at that: left alone the compiler issues many more MFMAs first, whose
 // results then spill.)
 template <int d, int NB, int DEPTH>

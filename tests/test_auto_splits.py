@@ -192,8 +192,10 @@ CHOICES = [
     ("step", (128, 4, 1, 4, 4), 136, 4096, 1, 0, 2, 1),
     ("attention", (128, 4, 1, 4, 4), 136, 4095, 1, 0, 1, 2),
     ("window", (128, 4, 1, 4, 4), 100, 8192, 1, 0, 3, 2),
-    ("attention", (128, 16, 8, 8, 8), 5, 24576, 1, 0, 7, 6),
-    ("attention", (128, 16, 8, 8, 8), 5, 24576, 0, 0, 6, 7),
+    ("attention", (128, 16, 8, 8, 8), 5, 49152, 1, 0, 7, 6),
+    ("attention", (128, 16, 8, 8, 8), 5, 49152, 0, 0, 6, 7),
+    ("attention", (128, 16, 8, 8, 8), 5, 49151, 1, 0, 6, 7),
+    ("attention", (128, 16, 8, 2, 2), 5, 24576, 1, 0, 7, 6),
     ("step", (128, 16, 8, 8, 8), 3, 50000, 1, 0, 10, 11),
     ("window", (128, 4, 1, 4, 4), 8, 1000, 0, 0, 16, 1),
 ]
