@@ -116,7 +116,7 @@ def test_keys_with_outliers_full_tile_mix():
 @pytest.mark.parametrize("d", [2, 4, 8])
 def test_many_groups_within_the_margin(d):
     """Codebooks in which every group of the screen holds centroids at the smallest distance (all
-    centroids equal; 16 vectors repeated with a period that is no multiple of 32), and a NaN and an
+    centroids equal; 15 vectors repeated, so with a period that does not divide 32), and a NaN and an
     infinite centroid (no screen for that sub-space, never the nearest): the lowest index must win."""
     D = 128
     g = synth.rng(5 + d)
