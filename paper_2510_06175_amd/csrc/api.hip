@@ -100,8 +100,8 @@ enum class Call { kAttention, kStep, kWindow };
 // Sequences of different lengths are the exception: the short ones' workgroups end early and make room for
 // one more split of the others, where the splits are long (4096 tokens, 8192 where one round occupies nine tenths of
 // the compute units and a token has less than 128 bytes) and the sequences are more than a few (from N / 8 to N
-// tokens: 17 x 8 heads, 30000, d = 2 157 us whole, 90 in two; 9 x 8, 30000, d = 8 42.6 in three, 35.4 in four; 5 x 8, 60000,
-// d = 4, ten thousand a split, 1.10 of the time in five, but 30000 0.77; 3 x 8, 30000 22.9 in ten, 28.6 in eleven).
+// tokens: 17 x 8 heads, 30000, d = 2 157 us whole, 90 in two; 9 x 8, 30000, d = 8 42.6 in three, 35.4 in four; 5 x 8, d = 4,
+// 30000 / 60000 27.6 / 40.1 in six, 35.9 / 36.4 in seven; 3 x 8, 30000 22.9 in ten, 28.6 in eleven).
 // What a split costs is the merge launch, 3 to 5 us (5 with more than four query heads per KV head):
 //   attention alone has nothing but its tokens to share: whole up to 1024 of them (8 sequences, 4 / 1
 //     heads: 250 / 600 / 1000 tokens 8.3 / 9.9 / 11.1 us whole, 11.4 / 11.6 / 11.6 in 4 / 10 / 16 splits; 8 / 1
@@ -334,7 +334,8 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     const bool use_roles = variant == VECINFER_VARIANT_ROLES;
     const bool use_mfma = use_roles || (variant == VECINFER_VARIANT_MFMA) || (variant == VECINFER_VARIANT_AUTO && mfma_ok);
 
-    int32_t S = N == 0 ? 1 : (num_splits ? num_splits : use_mfma ? auto_splits(cfg, B, N, call, seq_lens != nullptr) : lut_splits(cfg, B, N));
+    int32_t S = N == 0 ? 1 : num_splits;
+    if (S == 0) S = use_mfma ? auto_splits(cfg, B, N, call, seq_lens != nullptr) : lut_splits(cfg, B, N);
     WorkspaceLayout w = ws_layout(cfg, B, S);
     if (num_splits == 0)                // fewer where the workspace has no room for that many
         while (S > 1 && workspace_bytes < w.total) w = ws_layout(cfg, B, --S);
