@@ -263,11 +263,11 @@ def main() -> int:
                    "num_splits": splits, "variant": args.variant,
                    "us_per_step": round(ms_per_step * 1e3, 3),
                    "pct_hbm_peak": round(100.0 * value / HBM_PEAK_GBS, 2)},
-        # `kernel` is the call the events bracket: the attention kernel plus, with more than one split,
-        # the merge kernel right behind it (rocprofv3 lists the two separately, see profiles/)
+        # `kernel` is the call the events bracket: the attention kernel (which merges its splits
+        # itself; the variants that do not are followed by the merge kernel)
         "roofline": {"bound": "hbm", "kernel": "vecinfer_decode_attention",
                      "launches_per_call": [{vb.VARIANT_LUT: "decode_lut_kernel", vb.VARIANT_ROLES: "decode_roles_kernel"}.get(variant, "decode_mfma_kernel")]
-                     + (["merge_kernel"] if splits > 1 else []),
+                     + (["merge_kernel"] if splits > 1 and variant in (vb.VARIANT_LUT, vb.VARIANT_ROLES) else []),
                      "achieved": round(achieved, 2),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic, "traffic_kernel": traffic_kernel, "traffic_source": traffic_src,

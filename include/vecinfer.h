@@ -268,8 +268,9 @@ size_t vecinfer_decode_workspace_bytes(const vecinfer_cfg *cfg, int32_t B, int64
  *   L = log sum_n exp(s_n)                                      (Alg. 1 step 22)
  * computed per (b, q head h), g = h / G, fp32 accumulation, fp16 output.  The sequence
  * is cut into `num_splits` chunks handled by different workgroups; their (o, m, l)
- * partials go through `workspace` and are merged by log-sum-exp by a second small kernel
- * enqueued right behind (with one split the attention kernel finalises by itself).
+ * partials go through `workspace` and are merged by log-sum-exp by the last workgroup of a
+ * (sequence, KV head) to finish (VECINFER_VARIANT_LUT and _ROLES: by a second small kernel enqueued
+ * right behind; with one split the attention kernel finalises by itself).
  * The result does not depend on num_splits beyond fp32 rounding, and not at all on the layout
  * of the value codes (cfg.v_tiled: v_idx is then read as tiles; n_cap a multiple of 64, else EINVAL).
  *   seq_lens  int32 [B] on the device, or NULL: every sequence has N tokens.  Values are
@@ -356,7 +357,7 @@ int vecinfer_decode_attention_residual(const vecinfer_cfg *cfg, const void *q_f1
  * and yields o = 0, L = -inf.
  * With VECINFER_VARIANT_MFMA (or AUTO when it covers cfg) nothing is launched in front of the
  * attention: its workgroups share out the sub-spaces of the new token while the code cache of
- * the older tokens streams, and the merge kernel joins the new token as one more partial.
+ * the older tokens streams, and the merge of the splits joins the new token as one more partial.
  * The lookup-table variant runs the append kernel first.
  *   k_new_f16, v_new_f16  fp16 [B, H_kv, 1, D]
  *   k_idx, v_idx          as in vecinfer_decode_attention, but written at row len_b - 1 (with

@@ -4,6 +4,7 @@
 #include "common.h"
 
 #include <atomic>
+#include <chrono>
 #include <mutex>
 
 using namespace vecinfer;
@@ -228,6 +229,18 @@ WorkspaceLayout ws_layout(const vecinfer_cfg *c, int32_t B, int32_t S)
     return w;
 }
 
+// A launch's own number (split_merge.h): 48 bits, not 0.  Counted from a start of the process's own, so that a
+// word that something else left behind in memory is no more likely to carry it than any other number.
+unsigned long long next_nonce()
+{
+    static std::atomic<unsigned long long> count{
+        (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9e3779b97f4a7c15ull};
+    unsigned long long n;
+    do n = count.fetch_add(1, std::memory_order_relaxed) & 0xffffffffffffull;
+    while (n == 0);
+    return n;
+}
+
 // Validates one encode request and fills the kernel arguments; VECINFER_OK or an error code.
 int encode_args(const vecinfer_cfg *cfg, const void *x, const float *lambda, bool keys, const void *cb,
                 uint8_t *idx, int32_t B, int64_t T, int64_t pos0, int64_t n_cap, EncodeParams &p)
@@ -361,6 +374,9 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     if (use_roles && !(mfma_ok && decode_roles_supports(p))) return VECINFER_EUNSUPPORTED;
     // the lookup-table kernel reads one byte per code, from rows
     if (!use_mfma && (wide(cfg) || cfg->v_tiled)) return VECINFER_EUNSUPPORTED;
+    // The matrix-core kernel's last workgroups merge the splits; behind the other kernels, and with a window, a
+    // merge launch follows.
+    p.nonce = use_mfma && !use_roles && !window && S > 1 ? next_nonce() : 0;
     int rc = 0;
     if (append && use_mfma) {           // the attention launch encodes the new token itself
         p.k_new = static_cast<const __half *>(k_new);
@@ -385,7 +401,7 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     else
         p.S = 0;                        // nothing but the window: the merge kernel sees no split partial
     // log-sum-exp merge of the splits and of the window (single split, no window: done in-kernel)
-    if (rc == 0 && (p.S != 1 || window)) rc = launch_merge(p, static_cast<hipStream_t>(stream));
+    if (rc == 0 && (p.S != 1 || window) && p.nonce == 0) rc = launch_merge(p, static_cast<hipStream_t>(stream));
     return launch_status(rc);
 }
 

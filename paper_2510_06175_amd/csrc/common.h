@@ -30,6 +30,8 @@ struct DecodeParams {
     float *part_o;           // [B, Hkv, S, G, D]  unnormalised partial outputs
     float *part_m;           // [B, Hkv, S, G]     partial running max (log2 units)
     float *part_l;           // [B, Hkv, S, G]     partial sum of exp2(s2 - m)
+    unsigned long long nonce;     // this launch's number where its last workgroups merge the splits (split_merge.h);
+                                  // 0: a merge launch follows, or there is nothing to merge
     __half *out;             // [B, Hq, D]
     float *lse;              // [B, Hq] or nullptr
     // full-precision residual window (Sec. 4.1, residual length); k_res == nullptr: none
@@ -42,13 +44,13 @@ struct DecodeParams {
     // The new token is the last one of each sequence (position len_b - 1): the attention kernel
     // reads codes of the len_b - 1 older tokens only, its workgroups share out the sub-spaces of
     // the new token (nearest centroid, code byte, score share, dequantized value) and the merge
-    // kernel joins the new token as one more partial.
+    // of the splits joins the new token as one more partial.
     const __half *k_new;     // [B, Hkv, 1, D] raw key of the new token
     const __half *v_new;     // [B, Hkv, 1, D] raw value
     uint8_t *k_idx_w;        // = k_idx, writable: row len_b - 1 receives the key codes
     uint8_t *v_idx_w;        // = v_idx, writable
     float *new_sc;           // [B, Hkv, Mk, G] score share of each key sub-space (log2 units)
-    float *new_v;            // [B, Hkv, D]     dequantized value of the new token
+    float *new_v;            // [B, Hkv, D]     dequantized value of the new token (split_merge.h: fp16, arrival word behind)
 };
 
 // Tiled value codes: byte offset of (token n, sub-space m) in the cache of one (sequence, KV head).
@@ -173,8 +175,7 @@ __device__ __forceinline__ void merge_splits(const DecodeParams &p, int b, int g
 
 // End of a decode workgroup.  With a single split and no residual window the workgroup's own
 // partial is the whole answer and it finalises the output rows itself; otherwise a merge kernel follows
-// in the same stream (a device-scope release inside the kernel would write the whole L2 of the
-// XCD back per workgroup, which costs more than the kernel boundary does).
+// in the same stream.  (The matrix-core kernel merges its splits itself: split_merge.h.)
 template <int BLOCK>
 __device__ __forceinline__ void finish_split(const DecodeParams &p, int b, int g)
 {

@@ -31,10 +31,12 @@
 //   needed anywhere.
 //
 // Each wavefront runs its own online softmax (steps 12-13) over the 64-token tiles it owns;
-// wavefronts are merged through LDS at the end of the split, splits through the workspace.
+// wavefronts are merged through LDS at the end of the split, splits through the workspace by the last
+// workgroup to finish (split_merge.h).
 #pragma once
 #include "common.h"
 #include "mfma_helpers.h"
+#include "split_merge.h"
 
 namespace vecinfer {
 
@@ -244,13 +246,23 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
         }
     }
 
+    // The arrival word of this (sequence, KV head): the look at it travels behind the tables.
+    arrival_t word = 0;
+    if (p.nonce && tid == 0) word = arrival_peek(arrival_word<kD>(p, bg));
+    asm volatile("" ::: "memory");
+
     if (n0 >= n1 && !has_new) {                        // empty split: neutral partial
-        for (int e = tid; e < G_ * kD; e += BLOCK) p.part_o[(bg * S_ + s) * G_ * kD + e] = 0.f;
+        for (int e = tid; e < G_ * kD; e += BLOCK) shared_store(p.part_o + (bg * S_ + s) * G_ * kD + e, 0.f);
         if (tid < G_) {
-            p.part_m[(bg * S_ + s) * G_ + tid] = -INFINITY;
-            p.part_l[(bg * S_ + s) * G_ + tid] = 0.f;
+            shared_store(p.part_m + (bg * S_ + s) * G_ + tid, -INFINITY);
+            shared_store(p.part_l + (bg * S_ + s) * G_ + tid, 0.f);
         }
-        finish_split<BLOCK>(p, b, g);
+        if (p.nonce) {
+            if (tid == 0) arrival_open(arrival_word<kD>(p, bg), word, p.nonce);
+            merge_arrived<kD, KG, BLOCK>(p, reinterpret_cast<float *>(smem), bg, ((size_t)b * Hkv_ + g) * G_, S_, G_, fused);
+        } else {
+            finish_split<BLOCK>(p, b, g);
+        }
         return;
     }
 
@@ -512,6 +524,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
             }
         }
     }
+    if (p.nonce && tid == 0) arrival_open(arrival_word<kD>(p, bg), word, p.nonce);
     __syncthreads();
 
     // ---- B operands of the score MFMAs: q~_h[(D/4) kg + 8r .. +8); columns with t0 < 2 take the
@@ -549,7 +562,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     // scans centroids lane, lane + 64, ..; squared distances summed in channel order in fp32; the
     // lowest index among the centroids at minimum distance wins.  The key item
     // also leaves the new token's score share of its sub-space for the 4 heads, the value item
-    // the dequantized channels, for the merge kernel.
+    // the dequantized channels, for the merge of the splits.
     const long long pos = len - 1;
     const float fold = kLog2e / (float)kD;
     // A wavefront takes up to four items of one kind at a time (items i0, i0 + NW, ..): their
@@ -618,7 +631,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
 #pragma unroll
                     for (int jj = 0; jj < DS; ++jj)
                         sc = fmaf(sm_qt[lane * kD + m[b4] * DS + jj] * fold, (float)win[jj], sc);
-                    p.new_sc[((size_t)bg * MK + m[b4]) * G_ + lane] = sc;
+                    shared_store(p.new_sc + ((size_t)bg * MK + m[b4]) * G_ + lane, sc);
                     sm_nsc[m[b4] * KG + lane] = sc;
                 }
             } else {
@@ -629,7 +642,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
 #pragma unroll
                 for (int jj = 1; jj < DS; ++jj) mine = lane == jj ? (float)win[jj] : mine;
                 if (lane < DS) {
-                    p.new_v[(size_t)bg * kD + m[b4] * DS + lane] = mine;
+                    shared_store_half(new_value<kD>(p, bg) + m[b4] * DS + lane, mine);
                     sm_nv[m[b4] * DS + lane] = mine;
                 }
             }
@@ -699,7 +712,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
 #pragma unroll
                     for (int jj = 0; jj < DS; ++jj)
                         sc = fmaf(sm_qt[l16 * kD + m * DS + jj] * fold, (float)win[jj], sc);
-                    p.new_sc[((size_t)bg * MK + m) * G_ + l16] = sc;
+                    shared_store(p.new_sc + ((size_t)bg * MK + m) * G_ + l16, sc);
                     sm_nsc[m * KG + l16] = sc;
                 }
             } else {
@@ -707,7 +720,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
 #pragma unroll
                 for (int jj = 1; jj < DS; ++jj) mine = l16 == jj ? (float)win[jj] : mine;
                 if (l16 < DS) {
-                    p.new_v[(size_t)bg * kD + m * DS + l16] = mine;
+                    shared_store_half(new_value<kD>(p, bg) + m * DS + l16, mine);
                     sm_nv[m * DS + l16] = mine;
                 }
             }
@@ -1193,13 +1206,15 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
             if (c == 0 && p.lse) p.lse[row] = l > 0.f ? (mx + log2f(l)) * kLn2 : -INFINITY;
         } else {
             const size_t pi = (bg * S_ + s) * G_;
-            p.part_o[pi * kD + e] = o;
+            shared_store(p.part_o + pi * kD + e, o);
             if (c == 0) {
-                p.part_m[pi + hh] = mx;
-                p.part_l[pi + hh] = l;
+                shared_store(p.part_m + pi + hh, mx);
+                shared_store(p.part_l + pi + hh, l);
             }
         }
     }
+    if (p.nonce)
+        merge_arrived<kD, KG, BLOCK>(p, reinterpret_cast<float *>(smem), bg, ((size_t)b * Hkv_ + g) * G_, S_, G_, fused);
 }
 
 template <int kD, int DK, int DV, int HG, int NW, bool SPLITQ, int BK, int BV, bool VT>
@@ -1211,7 +1226,9 @@ int launch_hg(const DecodeParams &p, hipStream_t stream)
     // the tables, q~ and the new token's scratch during the tile loop; the wavefronts' partials after it
     constexpr size_t loop_bytes = cbk + cbv + sizeof(float) * ((KG + 3) * kD + (kD / DK) * KG) + 8 * 4 * NW + 16;
     constexpr size_t merge_bytes = sizeof(float) * (NW * KG * kD + 2 * NW * KG);
-    constexpr size_t smem = loop_bytes > merge_bytes ? loop_bytes : merge_bytes;
+    constexpr size_t final_bytes = sizeof(float) * merge_arrived_floats(kD, KG);
+    constexpr size_t wave_bytes = merge_bytes > final_bytes ? merge_bytes : final_bytes;
+    constexpr size_t smem = loop_bytes > wave_bytes ? loop_bytes : wave_bytes;
     // once per process and instantiation (function-local static: initialised thread-safely)
     static const bool configured = [] {
         const void *fn = reinterpret_cast<const void *>(decode_mfma_kernel<kD, DK, DV, HG, NW, SPLITQ, BK, BV, VT>);

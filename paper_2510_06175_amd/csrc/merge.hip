@@ -1,6 +1,7 @@
-// Second kernel of a decode step: log-sum-exp merge of the split partials, and, when the caller
-// keeps the most recent tokens unquantized (Sec. 4.1, residual length), attention over that
-// fp16 window computed here and merged in with them.
+// Second kernel of a decode call whose kernel does not merge its splits itself (the lookup-table kernel,
+// the score / value wavefront kernel, every call with a residual window): log-sum-exp merge of the
+// split partials, and, when the caller keeps the most recent tokens unquantized (Sec. 4.1, residual
+// length), attention over that fp16 window computed here and merged in with them.
 //
 // The kernel runs right behind the attention kernel on data that sits in other compute units'
 // caches or in memory, so what it costs is dependent memory round trips, not arithmetic: every
