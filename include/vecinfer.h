@@ -326,7 +326,7 @@ int vecinfer_decode_attention_static(const vecinfer_cfg *cfg, const void *q_f16,
  *   s_r = q . k_res[b, g, r, :] / sqrt(D)     raw query against raw key, which equals the
  *                                             transformed product q~ . k~ by Eq. 7
  *   p = softmax over the len_b + res_len_b scores;   o += sum_r p_r v_res[b, g, r, :]
- * The window is scored by the merge kernel and joins the log-sum-exp merge as one more partial.
+ * The window is scored beside the quantized tokens and joins the log-sum-exp merge.
  * Filling the window and flushing it into the code cache (vecinfer_encode_keys / _values with
  * T = window length, pos0 = N, reading the window as [B, H_kv, T, D] when r_cap = T) is the caller's.
  *   k_res_f16, v_res_f16  fp16 [B, H_kv, r_cap, D], rows 0 .. res_len_b - 1 are attended

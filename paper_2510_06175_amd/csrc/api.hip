@@ -374,9 +374,10 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     if (use_roles && !(mfma_ok && decode_roles_supports(p))) return VECINFER_EUNSUPPORTED;
     // the lookup-table kernel reads one byte per code, from rows
     if (!use_mfma && (wide(cfg) || cfg->v_tiled)) return VECINFER_EUNSUPPORTED;
-    // The matrix-core kernel's last workgroups merge the splits; behind the other kernels, and with a window, a
-    // merge launch follows.
-    p.nonce = use_mfma && !use_roles && !window && S > 1 ? next_nonce() : 0;
+    // The matrix-core kernel attends to the window, and its last workgroups merge the splits; behind the other
+    // kernels, and where there is nothing but a window, a merge launch follows.
+    const bool in_kernel = use_mfma && !use_roles && N > 0;
+    p.nonce = in_kernel && S > 1 ? next_nonce() : 0;
     int rc = 0;
     if (append && use_mfma) {           // the attention launch encodes the new token itself
         p.k_new = static_cast<const __half *>(k_new);
@@ -400,8 +401,8 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
                         : launch_decode_lut(p, static_cast<hipStream_t>(stream));
     else
         p.S = 0;                        // nothing but the window: the merge kernel sees no split partial
-    // log-sum-exp merge of the splits and of the window (single split, no window: done in-kernel)
-    if (rc == 0 && (p.S != 1 || window) && p.nonce == 0) rc = launch_merge(p, static_cast<hipStream_t>(stream));
+    // log-sum-exp merge of the splits and of the window (single split, no window: nothing left to do)
+    if (rc == 0 && (p.S != 1 || window) && !in_kernel) rc = launch_merge(p, static_cast<hipStream_t>(stream));
     return launch_status(rc);
 }
 

@@ -30,8 +30,7 @@ struct DecodeParams {
     float *part_o;           // [B, Hkv, S, G, D]  unnormalised partial outputs
     float *part_m;           // [B, Hkv, S, G]     partial running max (log2 units)
     float *part_l;           // [B, Hkv, S, G]     partial sum of exp2(s2 - m)
-    unsigned long long nonce;     // this launch's number where its last workgroups merge the splits (split_merge.h);
-                                  // 0: a merge launch follows, or there is nothing to merge
+    unsigned long long nonce;     // matrix-core kernel with S > 1: this launch's number (split_merge.h)
     __half *out;             // [B, Hq, D]
     float *lse;              // [B, Hq] or nullptr
     // full-precision residual window (Sec. 4.1, residual length); k_res == nullptr: none

@@ -119,6 +119,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     float *const sm_nsc = sm_new + 2 * kD;                                 // [MK][KG]: its score shares (log2 units)
     float *const sm_nv = sm_nsc + MK * KG;                                 // [D]:    its dequantized value
     unsigned long long *const sm_red = reinterpret_cast<unsigned long long *>(sm_nv + kD);   // [4][NW] (wide codes)
+    float *const sm_win = reinterpret_cast<float *>(sm_red + 4 * NW);      // [NW][18][KG]: window rows' p, then m, l
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int Hkv_ = (int)(hkv_g_arg & 0xffffffu), G_ = (int)(hkv_g_arg >> 24);   // = p.Hkv, p.G
     // Workgroups are dealt to the 8 XCDs round-robin in linear order, so the KV head varies
@@ -246,23 +247,40 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
         }
     }
 
+    // Residual window: rows 16 w .. 16 w + 15 are item w of kWinItems, done by workgroup w % S: its i-th item by the
+    // i-th wavefront from the end (the last ones get the fewest tiles).
+    constexpr int kWinItems = kMaxResidual / 16;
+    static_assert(kWinItems <= NW, "at most one item per wavefront, whatever S is");
+    int r_len = 0;
+    if (p.k_res) {
+        r_len = p.R;
+        if (p.res_lens) {
+            typedef const int32_t __attribute__((address_space(4))) *const_i32_ptr;
+            const int v = ((const_i32_ptr)(uintptr_t)p.res_lens)[b];
+            r_len = v < 0 ? 0 : (v > p.R ? p.R : v);
+        }
+    }
+    const bool has_win = s < kWinItems && 16 * s < r_len;
+
     // The arrival word of this (sequence, KV head): the look at it travels behind the tables.
     arrival_t word = 0;
-    if (p.nonce && tid == 0) word = arrival_peek(arrival_word<kD>(p, bg));
+    if (S_ > 1 && tid == 0) word = arrival_peek(arrival_word<kD>(p, bg));
     asm volatile("" ::: "memory");
 
-    if (n0 >= n1 && !has_new) {                        // empty split: neutral partial
+    if (n0 >= n1 && !has_new && !has_win) {            // empty split
+        if (S_ == 1) {                                 // .. and nothing else: o = 0, L = -inf
+            const size_t row = bg * G_;
+            for (int e = tid; e < G_ * kD; e += BLOCK) p.out[row * kD + e] = __float2half(0.f);
+            if (tid < G_ && p.lse) p.lse[row + tid] = -INFINITY;
+            return;
+        }
         for (int e = tid; e < G_ * kD; e += BLOCK) shared_store(p.part_o + (bg * S_ + s) * G_ * kD + e, 0.f);
         if (tid < G_) {
             shared_store(p.part_m + (bg * S_ + s) * G_ + tid, -INFINITY);
             shared_store(p.part_l + (bg * S_ + s) * G_ + tid, 0.f);
         }
-        if (p.nonce) {
-            if (tid == 0) arrival_open(arrival_word<kD>(p, bg), word, p.nonce);
-            merge_arrived<kD, KG, BLOCK>(p, reinterpret_cast<float *>(smem), bg, ((size_t)b * Hkv_ + g) * G_, S_, G_, fused);
-        } else {
-            finish_split<BLOCK>(p, b, g);
-        }
+        if (tid == 0) arrival_open(arrival_word<kD>(p, bg), word, p.nonce);
+        merge_arrived<kD, KG, BLOCK>(p, reinterpret_cast<float *>(smem), bg, bg * G_, S_, G_, fused);
         return;
     }
 
@@ -432,6 +450,20 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     // is the slowest load of the kernel, so the other way round the staging would wait behind it.
     load_codes(ca, tile_base(0));
     load_codes(cb, tile_base(1));
+    // The wavefront's window rows, if it has any: raw queries and keys as the MFMA wants them, 8 consecutive channels
+    // of row / column lane % 16 per lane.  (Clamped to row R - 1, which is always inside the allocation.)
+    const int win_row0 = 16 * (s + (NW - 1 - wave_u) * S_);
+    const bool win_item = has_win && win_row0 < r_len && win_row0 < 16 * kWinItems;
+    half8 win_q[kD / 32], win_k[kD / 32];
+    if (win_item) {
+        const __half *const qw = q_arg + (bg * G_ + (col < G_ ? col : 0)) * kD;
+        const __half *const kw = p.k_res + (bg * p.r_cap + (win_row0 + col < p.R ? win_row0 + col : p.R - 1)) * kD;
+#pragma unroll
+        for (int ks = 0; ks < kD / 32; ++ks) {
+            win_q[ks] = *reinterpret_cast<const half8 *>(qw + 32 * ks + 8 * kg);
+            win_k[ks] = *reinterpret_cast<const half8 *>(kw + 32 * ks + 8 * kg);
+        }
+    }
     // ---- q~ = (q * lambda) H_D for the 4 heads of the group (un-normalised butterflies):
     // wavefront hh transforms head hh in registers, a lane holding channels `lane` and
     // `lane + 64`: one in-lane butterfly (partner distance 64), six across lanes.
@@ -524,7 +556,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
             }
         }
     }
-    if (p.nonce && tid == 0) arrival_open(arrival_word<kD>(p, bg), word, p.nonce);
+    if (S_ > 1 && tid == 0) arrival_open(arrival_word<kD>(p, bg), word, p.nonce);
     __syncthreads();
 
     // ---- B operands of the score MFMAs: q~_h[(D/4) kg + 8r .. +8); columns with t0 < 2 take the
@@ -766,6 +798,75 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
         l_part[hg] = 0.f;
 #pragma unroll
         for (int r = 0; r < NACC; ++r) acc_o[hg][r] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    // ---- residual window (Sec. 4.1): the wavefront's 16 rows are where its softmax starts from.  q . k =
+    // (q * lambda) H . (k / lambda) H (Eq. 7), so raw queries against raw keys give scores on the scale of the
+    // quantized tokens'.  Scores on the matrix cores, p and P.V in fp32: p goes through LDS to the lanes that own a
+    // head's channels, which read those channels of the 16 rows.  (A merge launch that scored the window behind the
+    // attention kernel took 4.9 us; these items run beside the other wavefronts' tiles.)
+    if (win_item) {
+        constexpr int kChan = kD / 16;                     // channels of a lane: kChan col ..
+        typedef _Float16 halfc __attribute__((ext_vector_type(kChan)));
+        const __half *const vw = p.v_res + (bg * p.r_cap + win_row0) * kD + kChan * col;
+        halfc wv[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            wv[r] = halfc{};
+            if (win_row0 + r < r_len) wv[r] = *reinterpret_cast<const halfc *>(vw + (size_t)r * kD);
+        }
+        floatx4 sc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < kD / 32; ++ks) sc = MFMA16(win_q[ks], win_k[ks], sc, 0, 0, 0);
+        // register v of lane (col, kg): window row win_row0 + col, head 4 kg + v
+        const float scale = kLog2e * rsqrtf((float)kD);
+        float *const wp = sm_win + wave * (18 * KG);       // [KG][16] p, [KG] m, [KG] l
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float s2 = win_row0 + col < r_len ? sc[v] * scale : -INFINITY;
+            float m = s2;
+            m = fmaxf(m, row_ror<8>(m));
+            m = fmaxf(m, row_ror<4>(m));
+            m = fmaxf(m, row_ror<2>(m));
+            m = fmaxf(m, row_ror<1>(m));
+            const float pr = __builtin_amdgcn_exp2f(s2 - m);   // row win_row0 is valid, so m is finite
+            float l = pr;
+            l += row_ror<8>(l);
+            l += row_ror<4>(l);
+            l += row_ror<2>(l);
+            l += row_ror<1>(l);
+            const int hh = 4 * kg + v;
+            if (hh < KG) {                                 // (head slots G .. KG - 1 hold finite filler)
+                wp[hh * 16 + col] = pr;
+                if (col == 0) {
+                    wp[16 * KG + hh] = m;
+                    wp[17 * KG + hh] = l;
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();                   // (the wavefront's own LDS operations execute in order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg) {
+            m_run[hg] = wp[16 * KG + kG * hg + (col >> 2)];
+            l_part[hg] = kg == 0 && (col & 3) == 0 ? wp[17 * KG + kG * hg + (col >> 2)] : 0.f;
+            float o[kChan];
+#pragma unroll
+            for (int c = 0; c < kChan; ++c) o[c] = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; r += 4) {
+                const float4 pr = *reinterpret_cast<const float4 *>(wp + (kG * hg + kg) * 16 + r);
+                const float p4[4] = {pr.x, pr.y, pr.z, pr.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int c = 0; c < kChan; ++c) o[c] = fmaf(p4[i], (float)wv[r + i][c], o[c]);
+            }
+#pragma unroll
+            for (int r = 0; r < NACC; ++r)
+#pragma unroll
+                for (int v = 0; v < kChanBlock; ++v) acc_o[hg][r][v] = o[kChanBlock * r + v];
+        }
     }
 
     // LDS byte address of centroid `code byte k of w` in the sub-space table at `base`:
@@ -1141,7 +1242,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     // sides, two head groups) the wavefronts' partials written next reach into that scratch:
     // every thread takes what it will need into registers first.
     constexpr int kMergeIters = (KG * kD + BLOCK - 1) / BLOCK;
-    const bool fold_new = S_ == 1 && !p.k_res && has_new;
+    const bool fold_new = S_ == 1 && has_new;
     float new_s[kMergeIters], new_val[kMergeIters];
     if (fold_new) {
         __syncthreads();                                   // the items' scratch writes
@@ -1190,7 +1291,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
             o += f * sm_o[w * KG * kD + e];
             l += f * sm_l[w * KG + hh];
         }
-        if (S_ == 1 && !p.k_res) {
+        if (S_ == 1) {
             // the workgroup holds the whole answer (a single split also encoded every sub-space of
             // a fused new token): fold the new token in and write the output rows
             if (has_new) {
@@ -1213,8 +1314,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
             }
         }
     }
-    if (p.nonce)
-        merge_arrived<kD, KG, BLOCK>(p, reinterpret_cast<float *>(smem), bg, ((size_t)b * Hkv_ + g) * G_, S_, G_, fused);
+    if (S_ > 1) merge_arrived<kD, KG, BLOCK>(p, reinterpret_cast<float *>(smem), bg, bg * G_, S_, G_, fused);
 }
 
 template <int kD, int DK, int DV, int HG, int NW, bool SPLITQ, int BK, int BV, bool VT>
@@ -1223,8 +1323,8 @@ int launch_hg(const DecodeParams &p, hipStream_t stream)
     constexpr int KG = kG * HG;
     constexpr size_t cbk = BK > 8 ? ((size_t)1 << BK) * DK * 2 : (size_t)kCentroids * kD * 2;
     constexpr size_t cbv = BV > 8 ? ((size_t)1 << BV) * DV * 2 : (size_t)kCentroids * kD * 2;
-    // the tables, q~ and the new token's scratch during the tile loop; the wavefronts' partials after it
-    constexpr size_t loop_bytes = cbk + cbv + sizeof(float) * ((KG + 3) * kD + (kD / DK) * KG) + 8 * 4 * NW + 16;
+    // the tables, q~, the new token's and the window's scratch during the tile loop; the wavefronts' partials after it
+    constexpr size_t loop_bytes = cbk + cbv + sizeof(float) * ((KG + 3) * kD + (kD / DK) * KG + NW * 18 * KG) + 8 * 4 * NW + 16;
     constexpr size_t merge_bytes = sizeof(float) * (NW * KG * kD + 2 * NW * KG);
     constexpr size_t final_bytes = sizeof(float) * merge_arrived_floats(kD, KG);
     constexpr size_t wave_bytes = merge_bytes > final_bytes ? merge_bytes : final_bytes;

@@ -1,12 +1,13 @@
-// Second kernel of a decode call whose kernel does not merge its splits itself (the lookup-table kernel,
-// the score / value wavefront kernel, every call with a residual window): log-sum-exp merge of the
-// split partials, and, when the caller keeps the most recent tokens unquantized (Sec. 4.1, residual
-// length), attention over that fp16 window computed here and merged in with them.
+// Second kernel of a decode call whose kernel does not merge its splits itself (the lookup-table kernel and
+// the score / value wavefront kernel; the only kernel of a call with nothing but a window): log-sum-exp
+// merge of the split partials, and, when the caller keeps the most recent tokens unquantized (Sec. 4.1,
+// residual length), attention over that fp16 window computed here and merged in with them.
 //
 // The kernel runs right behind the attention kernel on data that sits in other compute units'
 // caches or in memory, so what it costs is dependent memory round trips, not arithmetic: every
 // global load it needs is issued up front, back to back, and consumed after one barrier.
 #include "common.h"
+#include "mfma_helpers.h"
 
 namespace vecinfer {
 namespace {
@@ -17,16 +18,6 @@ constexpr int kMaxSplits = 256;                         // VECINFER_MAX_SPLITS
 constexpr int kBatch = 32;                              // split partials a thread keeps in flight
 constexpr int kRowsPerWave = kMaxResidual / kWaves;     // 16: one MFMA column block of window rows per wave
 static_assert(kRowsPerWave == 16, "a wave scores 16 window rows with 16x16x32 MFMAs");
-
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-// x of the lane N places further on in its row of 16 lanes (DPP row_ror)
-template <int N>
-__device__ __forceinline__ float row_ror(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x120 + N, 0xf, 0xf, true));
-}
 
 // One workgroup per (KV head g, sequence b); D = head dim, HB = bound on G (4 or 8), MODE below.
 //

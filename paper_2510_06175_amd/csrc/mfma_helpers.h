@@ -62,6 +62,13 @@ __device__ __forceinline__ float quad_xor(float x)
     return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), ctrl, 0xf, 0xf, true));
 }
 
+// x of the lane N places further on in its row of 16 lanes (DPP row_ror)
+template <int N>
+__device__ __forceinline__ float row_ror(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x120 + N, 0xf, 0xf, true));
+}
+
 // max over the four 16-lane rows of the wavefront, on the vector ALU (v_permlane16_swap /
 // v_permlane32_swap exchange rows between two copies of the value; no LDS round trip)
 __device__ __forceinline__ float rows_max(float x)
