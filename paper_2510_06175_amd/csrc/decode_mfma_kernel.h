@@ -777,12 +777,15 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
         if (has_new)
             for (int grp = vgrp0; grp < ITEMS_V; grp += S_) wide_item(std::integral_constant<int, 1>{}, grp);
     }
-    // 8-bit codes: key item i (sub-space s + i S) goes to wavefront i % NW, value item i to
-    // wavefront (i + 1) % NW; a wavefront with one item of a kind (the usual case: at least as
-    // many splits as sub-spaces) takes it alone, otherwise four at a time
+    // 8-bit codes: the key items (sub-spaces s, s + S, ..), then the value items, go to wavefront after wavefront,
+    // starting with the first one that has no tile (a workgroup with a tile for everybody: with the first
+    // ones, which finish their tiles first); a wavefront with one item of a kind (the usual case: at least as
+    // many splits as sub-spaces) takes it alone, otherwise four at a time.
+    const int tiles_here = (int)(n1 - n0 < NW * kTile ? (n1 - n0 + kTile - 1) / kTile : NW);
     auto items8 = [&](auto kv_c) {
         constexpr int kv = decltype(kv_c)::value, MX = kv == 0 ? MK : MV;
-        const int first = kv == 0 ? wave_u : (wave_u + NW - 1) % NW;
+        const int key_items = WK ? 0 : (MK - s + S_ - 1) / S_;
+        const int first = (wave_u + 2 * NW - tiles_here % NW - (kv == 0 ? 0 : key_items % NW)) % NW;
         if (s + (first + NW) * S_ < MX) {
             for (int i0 = first; s + i0 * S_ < MX; i0 += 4 * NW) new_items(kv_c, std::integral_constant<int, 4>{}, i0);
         } else if (s + first * S_ < MX) {
