@@ -3,8 +3,8 @@
 //
 // Cache fill and K-Means assignment work on tiles of 64 tokens of one (batch, KV head):
 //   phase 1  transform: a lane owns 4 consecutive channels of one token; the first two
-//            butterfly stages run inside the lane, the others across lanes with wavefront
-//            shuffles.  The transformed tile is kept, as fp32, in LDS.
+//            butterfly stages run inside the lane, the others across lanes on the vector
+//            ALU.  The transformed tile is kept, as fp32, in LDS.
 //            (Values skip the transform: the lane just widens its fp16 inputs.)
 //   phase 2  search (encode_screen.h): a wavefront owns one sub-space at a time and a lane one
 //            token; the matrix cores shortlist, the exact fp32 distances decide.
@@ -25,7 +25,9 @@ constexpr int kEncTokens = 64;     // tokens per workgroup = lanes per wavefront
 // Phase 1 of the tiled kernels: the 64 tokens of the tile, smoothed and Hadamard-transformed
 // (kTransform) or just widened (values), as fp32 rows of x_s (row stride D + 4 floats).  A lane
 // owns 4 consecutive channels of one token; the first two butterfly stages run inside the lane,
-// the others across lanes with wavefront shuffles.
+// the others across lanes on the vector ALU (DPP, row swaps): shuffles through LDS cost a trip per stage
+// that nothing covers, since all wavefronts are in this phase together (with divisions instead of tile_lambda's
+// reciprocals as well: 65536 x 8 keys and values, d = 4 539 us, now 498; 8 training iterations over 32768 x 8 keys 2207 / 1828).
 // NCH < D: only channels ch0 .. ch0 + NCH - 1 are kept (row stride NCH + 4), for a workgroup that
 // searches a group of sub-spaces; values outside the window are then not even loaded.
 // The two halves are separate so that a kernel can request the next tile's rows before it searches
@@ -40,13 +42,22 @@ struct TileRows {
     uint2 raw[NP];
 };
 
+// Which 4 channels of its token a lane owns: lane i of 8 owns block i, or i ^ 3 in the upper half, so that the
+// butterfly between blocks 4 apart is a reversal of the 8 lanes, which DPP has (block ^ 1, ^ 2 and ^ 8 are lane ^ 1,
+// ^ 2 and ^ 8 all the same).
+template <int LPT>
+__device__ __forceinline__ int tile_block(int lane)
+{
+    return (lane & 4 ? lane ^ 3 : lane) % LPT;
+}
+
 template <int D, bool kTransform, int BLOCK = kEncBlock, int NCH = D>
 __device__ __forceinline__ void tile_request(const EncodeParams &p, TileRows<D, BLOCK> &rows, long long t0, int bg,
                                              int ch0 = 0)
 {
     constexpr int LPT = TileRows<D, BLOCK>::LPT, TPW = TileRows<D, BLOCK>::TPW, NP = TileRows<D, BLOCK>::NP;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c0 = 4 * (lane % LPT), tw = lane / LPT;
+    const int c0 = 4 * tile_block<LPT>(lane), tw = lane / LPT;
     const bool kept = NCH == D || (c0 >= ch0 && c0 < ch0 + NCH);
 #pragma unroll
     for (int pi = 0; pi < NP; ++pi) {
@@ -58,25 +69,40 @@ __device__ __forceinline__ void tile_request(const EncodeParams &p, TileRows<D, 
     }
 }
 
+// The smoothing factors of KV head g and their reciprocals -> LDS (2 D floats).  True where x / lambda may be worked
+// out from the reciprocal for every channel (same for every lane): with r = 1 / lambda correctly rounded,
+//   q = x r,  e = x - q lambda (exact),  q + e r  is x / lambda correctly rounded (Markstein),
+// unless lambda's mantissa is all ones; and nothing over- or underflows for fp16 x where lambda lies within
+// 2^-60 .. 2^60.  Three instructions instead of the ten of a division.
+template <int D>
+__device__ __forceinline__ bool tile_lambda(const EncodeParams &p, float *lam_s, int g)
+{
+    bool ok = true;
+    for (int c = threadIdx.x & 63; c < D; c += 64) {           // (every wavefront looks at all of them)
+        const float l = p.lam[(size_t)g * D + c];
+        ok = ok && l >= 0x1p-60f && l <= 0x1p60f && (__float_as_uint(l) & 0x7fffffu) != 0x7fffffu;
+        if (threadIdx.x < 64) {
+            lam_s[c] = l;
+            lam_s[D + c] = 1.0f / l;
+        }
+    }
+    return __all(ok);
+}
+
 template <int D, bool kTransform, int BLOCK = kEncBlock, int NCH = D>
-__device__ __forceinline__ void tile_finish(const EncodeParams &p, const TileRows<D, BLOCK> &rows, float *x_s, int g,
+__device__ __forceinline__ void tile_finish(const TileRows<D, BLOCK> &rows, float *x_s, const float *lam_s, bool by_reciprocal,
                                             int ch0 = 0)
 {
     constexpr int LPT = TileRows<D, BLOCK>::LPT, TPW = TileRows<D, BLOCK>::TPW, NP = TileRows<D, BLOCK>::NP;
     constexpr int XS = NCH + 4;                // padded row stride of the LDS tile (floats)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int sub = lane % LPT;                // which 4 channels of the token
+    const int sub = tile_block<LPT>(lane);     // which 4 channels of the token
     const int tw = lane / LPT;                 // which token of this pass
     const int c0 = 4 * sub;
-    const bool kept = NCH == D || (c0 >= ch0 && c0 < ch0 + NCH);
-    float rl[4] = {1.f, 1.f, 1.f, 1.f};
-    if (kTransform) {
-        const float4 l4 = *reinterpret_cast<const float4 *>(p.lam + (size_t)g * D + c0);
-        rl[0] = l4.x; rl[1] = l4.y; rl[2] = l4.z; rl[3] = l4.w;
-    }
-    const float hs = 1.0f / sqrtf((float)D);
-    // All passes of the wavefront advance stage by stage, so that a stage's shuffles (NP x 4
-    // independent ones) are in flight together instead of one LDS round trip at a time.
+    auto store = [&](int pi, int c, float4 w) {
+        const int tl = (wave + pi * (BLOCK / 64)) * TPW + tw;
+        if (NCH == D || (c >= ch0 && c < ch0 + NCH)) *reinterpret_cast<float4 *>(&x_s[tl * XS + c - ch0]) = w;
+    };
     float v[NP][4];
 #pragma unroll
     for (int pi = 0; pi < NP; ++pi) {
@@ -85,40 +111,77 @@ __device__ __forceinline__ void tile_finish(const EncodeParams &p, const TileRow
         v[pi][0] = __low2float(h01); v[pi][1] = __high2float(h01);
         v[pi][2] = __low2float(h23); v[pi][3] = __high2float(h23);
     }
-    if (kTransform) {
+    if constexpr (!kTransform) {
 #pragma unroll
-        for (int pi = 0; pi < NP; ++pi) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[pi][j] = v[pi][j] / rl[j];
-            // butterflies with partner distance 1 and 2 (inside the lane)
-            const float a0 = v[pi][0] + v[pi][1], a1 = v[pi][0] - v[pi][1];
-            const float a2 = v[pi][2] + v[pi][3], a3 = v[pi][2] - v[pi][3];
-            v[pi][0] = a0 + a2; v[pi][1] = a1 + a3; v[pi][2] = a0 - a2; v[pi][3] = a1 - a3;
-        }
-        // partner distance 4 .. D/2 (across lanes)
-#pragma unroll
-        for (int x = 1; x < LPT; x <<= 1) {
-            float o[NP][4];
-#pragma unroll
-            for (int pi = 0; pi < NP; ++pi)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) o[pi][j] = __shfl_xor(v[pi][j], x);
-            const bool up = (sub & x) != 0;
-#pragma unroll
-            for (int pi = 0; pi < NP; ++pi)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[pi][j] = up ? (o[pi][j] - v[pi][j]) : (v[pi][j] + o[pi][j]);
-        }
+        for (int pi = 0; pi < NP; ++pi) store(pi, c0, make_float4(v[pi][0], v[pi][1], v[pi][2], v[pi][3]));
+        return;
+    }
+    const float4 l4 = *reinterpret_cast<const float4 *>(lam_s + c0);
+    const float lam[4] = {l4.x, l4.y, l4.z, l4.w};
+    if (by_reciprocal) {
+        const float4 r4 = *reinterpret_cast<const float4 *>(lam_s + D + c0);
+        const float rec[4] = {r4.x, r4.y, r4.z, r4.w};
 #pragma unroll
         for (int pi = 0; pi < NP; ++pi)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[pi][j] *= hs;
+            for (int j = 0; j < 4; ++j) {
+                const float q = v[pi][j] * rec[j];
+                v[pi][j] = fmaf(fmaf(-q, lam[j], v[pi][j]), rec[j], q);
+            }
+    } else {
+#pragma unroll
+        for (int pi = 0; pi < NP; ++pi)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[pi][j] = v[pi][j] / lam[j];
     }
 #pragma unroll
     for (int pi = 0; pi < NP; ++pi) {
-        const int tl = (wave + pi * (BLOCK / 64)) * TPW + tw;
-        float4 w; w.x = v[pi][0]; w.y = v[pi][1]; w.z = v[pi][2]; w.w = v[pi][3];
-        if (kept) *reinterpret_cast<float4 *>(&x_s[tl * XS + c0 - ch0]) = w;
+        // butterflies with partner distance 1 and 2 (inside the lane)
+        const float a0 = v[pi][0] + v[pi][1], a1 = v[pi][0] - v[pi][1];
+        const float a2 = v[pi][2] + v[pi][3], a3 = v[pi][2] - v[pi][3];
+        v[pi][0] = a0 + a2; v[pi][1] = a1 + a3; v[pi][2] = a0 - a2; v[pi][3] = a1 - a3;
+    }
+    // partner distance 4, 8, 16, 32: blocks 1, 2, 4, 8 apart.  The upper one of a pair takes the difference: its own
+    // value's sign is turned, then the other's is added.
+    auto stage = [&](auto ctrl, int x) {
+        const unsigned turn = (sub & x) != 0 ? 0x80000000u : 0u;
+#pragma unroll
+        for (int pi = 0; pi < NP; ++pi)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float o = __builtin_bit_cast(
+                    float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v[pi][j]), decltype(ctrl)::value, 0xf, 0xf, true));
+                v[pi][j] = o + __uint_as_float(__float_as_uint(v[pi][j]) ^ turn);
+            }
+    };
+    stage(std::integral_constant<int, 0xB1>{}, 1);              // quad_perm:[1,0,3,2]
+    stage(std::integral_constant<int, 0x4E>{}, 2);              // quad_perm:[2,3,0,1]
+    stage(std::integral_constant<int, 0x141>{}, 4);             // row_half_mirror
+    stage(std::integral_constant<int, 0x128>{}, 8);             // row_ror:8
+    const float hs = 1.0f / sqrtf((float)D);
+    if constexpr (LPT == 16) {
+#pragma unroll
+        for (int pi = 0; pi < NP; ++pi)
+            store(pi, c0, make_float4(v[pi][0] * hs, v[pi][1] * hs, v[pi][2] * hs, v[pi][3] * hs));
+    } else {
+        // partner distance 64: blocks 16 apart, for two passes at a time.  v_permlane16_swap(a, b) exchanges the odd rows of 16
+        // lanes of a with the even rows of b: with a, b the two passes' values, even rows then hold both halves of
+        // the first pass's token and odd rows those of the second's, and the sums and differences stay there.
+        static_assert(LPT == 32 && NP % 2 == 0, "two passes at a time");
+        const int odd = lane >> 4 & 1, lo = 4 * (sub & 15);
+#pragma unroll
+        for (int pi = 0; pi < NP; pi += 2) {
+            float a[4], b[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[pi][j]), __float_as_uint(v[pi + 1][j]), false, false);
+                a[j] = __uint_as_float(sw[0]);
+                b[j] = __uint_as_float(sw[1]);
+            }
+            store(pi + odd, lo, make_float4((a[0] + b[0]) * hs, (a[1] + b[1]) * hs, (a[2] + b[2]) * hs, (a[3] + b[3]) * hs));
+            store(pi + odd, lo + 64,
+                  make_float4((a[0] - b[0]) * hs, (a[1] - b[1]) * hs, (a[2] - b[2]) * hs, (a[3] - b[3]) * hs));
+        }
     }
 }
 
@@ -156,7 +219,7 @@ constexpr size_t vq_smem_bytes()
     constexpr int MSW = vq_group<d, kAccumulate, kGroup>(D / d);
     constexpr int NCH = kAccumulate || kGroup != kVqAll ? MSW * d : D; // channels of the tile kept in LDS
     return (size_t)MSW * ScreenTab<d>::kBytes + sizeof(float) * kEncTokens * (NCH + 4) + (size_t)kEncTokens * MSW +
-           (kAccumulate ? (sizeof(float) * (d + 1) + 1) * MSW * kCentroids : 0);
+           sizeof(float) * 2 * D + (kAccumulate ? (sizeof(float) * (d + 1) + 1) * MSW * kCentroids : 0);
 }
 
 struct KmeansState {
@@ -186,7 +249,8 @@ void vq_tile_kernel(EncodeParams p, int tiles_per_wg, int iter, KmeansState *sta
     unsigned char *const tab_s = vq_smem;                                          // [MSW] search tables
     float *const x_s = reinterpret_cast<float *>(tab_s + MSW * TB);                // [64][XS] transformed tile
     uint8_t *const idx_s = reinterpret_cast<uint8_t *>(x_s + kEncTokens * XS);     // [64][MSW] codes of the tile
-    float *const acc_s = reinterpret_cast<float *>(idx_s + kEncTokens * MSW);      // [MSW][256][d + 1] sums, counts
+    float *const lam_s = reinterpret_cast<float *>(idx_s + kEncTokens * MSW);      // [2][D] smoothing factors, reciprocals
+    float *const acc_s = lam_s + 2 * D;                                            // [MSW][256][d + 1] sums, counts
     volatile uint8_t *const tag_s = reinterpret_cast<volatile uint8_t *>(acc_s + MSW * kCentroids * (d + 1));   // [MSW][256]
 
     if (kAccumulate && iter > 0 && iter > state->stop_at) return;     // training already stopped (every thread alike)
@@ -198,6 +262,7 @@ void vq_tile_kernel(EncodeParams p, int tiles_per_wg, int iter, KmeansState *sta
     const int win0 = NCH == D ? 0 : grp * MSW * d;         // first channel of the tile that is kept
     TileRows<D, BLOCK> rows;                            // (the first tile's rows travel while the tables are built)
     if (tile0 * kEncTokens < p.T) tile_request<D, kTransform, BLOCK, NCH>(p, rows, tile0 * kEncTokens, bg, win0);
+    const bool by_reciprocal = kTransform && tile_lambda<D>(p, lam_s, g);          // (the first tile's barrier follows)
     // ---- the search tables of this wavefront's sub-spaces (nobody else reads them)
     ScreenConsts sc[SPW];
 #pragma unroll
@@ -213,7 +278,7 @@ void vq_tile_kernel(EncodeParams p, int tiles_per_wg, int iter, KmeansState *sta
         const long long t0 = (tile0 + ti) * kEncTokens;
         if (t0 >= p.T) break;
         __syncthreads();                       // previous tile's x_s and idx_s consumed (first tile: accumulators cleared)
-        tile_finish<D, kTransform, BLOCK, NCH>(p, rows, x_s, g, win0);
+        tile_finish<D, kTransform, BLOCK, NCH>(rows, x_s, lam_s, by_reciprocal, win0);
         __syncthreads();
         // the next tile's rows travel while this one is searched
         if (ti + 1 < tiles_per_wg && t0 + kEncTokens < p.T)
@@ -536,7 +601,7 @@ template <int D, int d, int BITS>
 constexpr size_t vq_wide_smem_bytes()
 {
     return (size_t)ScreenTab<d, (1 << BITS)>::kBytes + sizeof(float) * kEncTokens * (D + 4) +
-           sizeof(unsigned short) * kEncTokens * (D / d);
+           sizeof(unsigned short) * kEncTokens * (D / d) + sizeof(float) * 2 * D;
 }
 // K-Means with a shared table: a run's partial sums and counts [C][d + 1] stay in LDS where that
 // fits beside the search tables (1024 centroids: 20 or 36 KB), and go to memory once per run with
@@ -562,6 +627,7 @@ __global__ __launch_bounds__(kVqBlock) void vq_tile_wide_kernel(EncodeParams p, 
     unsigned char *const tab_s = vqw_smem;                                                  // the head's search tables
     float *const x_s = reinterpret_cast<float *>(tab_s + Tab::kBytes);                      // [64][XS] transformed tile
     unsigned short *const idx_s = reinterpret_cast<unsigned short *>(x_s + kEncTokens * XS);   // [64][M] codes of the tile
+    float *const lam_s = reinterpret_cast<float *>(idx_s + kEncTokens * M);                  // [2][D] smoothing factors, reciprocals
     constexpr bool kLdsSums = vq_wide_lds_sums<D, d, BITS>();
     float *const acc_s = reinterpret_cast<float *>(vqw_smem + vq_wide_smem_bytes<D, d, BITS>());   // [C][d + 1] (K-Means)
 
@@ -573,6 +639,7 @@ __global__ __launch_bounds__(kVqBlock) void vq_tile_wide_kernel(EncodeParams p, 
 
     if (kLdsSums && p.km_sums)
         for (int e = tid; e < C * (d + 1); e += kVqBlock) acc_s[e] = 0.f;     // (the barriers of the table set-up follow)
+    const bool by_reciprocal = kTransform && tile_lambda<D>(p, lam_s, g);     // (those barriers as well)
     const ScreenConsts sc = screen_prepare_shared<d, C, kVqBlock>(p.cb + (size_t)g * C * d, tab_s, x_s);
 
     float err = 0.f;
@@ -582,7 +649,7 @@ __global__ __launch_bounds__(kVqBlock) void vq_tile_wide_kernel(EncodeParams p, 
         const long long t0 = (tile0 + ti) * kEncTokens;
         if (t0 >= p.T) break;
         if (ti > 0) __syncthreads();           // previous tile's x_s and idx_s consumed
-        tile_finish<D, kTransform, kVqBlock>(p, rows, x_s, g);
+        tile_finish<D, kTransform, kVqBlock>(rows, x_s, lam_s, by_reciprocal);
         __syncthreads();
         // the next tile's rows travel while this one is searched
         if (ti + 1 < tiles_per_wg && t0 + kEncTokens < p.T)
