@@ -490,16 +490,14 @@ int kmeans_common(const vecinfer_cfg *cfg, const void *x_f16, const float *lambd
         lr = hipMemcpyAsync(cb_out_f16, cb_in_f16, cen * p.d * sizeof(__half), hipMemcpyDeviceToDevice, st) == hipSuccess
                  ? 0 : -4;
     p.cb = static_cast<const __half *>(cb_out_f16);
+    if (lr == 0) lr = launch_kmeans_begin(p.km_sums, p.km_counts, cen * p.d, cen, state, st);
     for (int it = 0; it < max_iters && lr == 0; ++it) {
-        lr = launch_kmeans_begin(p.km_sums, p.km_counts, cen * p.d, cen, it, state, st);
-        if (lr == 0) {
-            if (p.bits == 8) {
-                lr = launch_kmeans_assign(p, it, state, st);
-            } else {           // 10- / 12-bit codes: the tiled wide cache-fill kernel with its accumulation epilogue
-                p.km_state = state;
-                p.km_iter = it;
-                lr = launch_encode(p, st);
-            }
+        if (p.bits == 8) {
+            lr = launch_kmeans_assign(p, it, state, st);
+        } else {               // 10- / 12-bit codes: the tiled wide cache-fill kernel with its accumulation epilogue
+            p.km_state = state;
+            p.km_iter = it;
+            lr = launch_encode(p, st);
         }
         if (lr == 0)
             lr = launch_kmeans_end(p.km_sums, p.km_counts, static_cast<__half *>(cb_out_f16), counts, cen, p.d, it, tol,

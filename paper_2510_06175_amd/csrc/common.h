@@ -214,19 +214,18 @@ struct EncodeParams {
     // K-Means training: when km_sums != nullptr the wide tiled kernel also adds every (transformed)
     // sub-vector into the sum of the centroid it was assigned to and its squared distance to the
     // iteration's error in km_state (8-bit codes: launch_kmeans_assign)
-    float *km_sums;       // [Hkv, M, 256, d] fp32 (wide codes: [Hkv, 2^b, d]), cleared by launch_kmeans_begin
+    float *km_sums;       // [Hkv, M, 256, d] fp32 (wide codes: [Hkv, 2^b, d]), cleared by launch_kmeans_begin and _end
     int32_t *km_counts;   // [Hkv, M, 256]         (wide codes: [Hkv, 2^b])
     void *km_state;       // kmeans_state_bytes() of device memory
     int km_iter;          // iteration the launch belongs to (a launch behind the stop does nothing)
 };
-// K-Means training iteration: begin (clear), assign + accumulate (8-bit codes: launch_kmeans_assign; wide
-// codes: launch_encode with km_sums set), end (update in place, error, stopping rule); `state` is
+// K-Means training: begin (clear), then per iteration assign + accumulate (8-bit codes: launch_kmeans_assign; wide
+// codes: launch_encode with km_sums set) and end (update in place, error, stopping rule, clear); `state` is
 // kmeans_state_bytes() of device memory
 size_t kmeans_state_bytes();
-int launch_kmeans_begin(float *sums, int32_t *counts, size_t n_sums, size_t n_counts, int iter, void *state,
-                        hipStream_t stream);
+int launch_kmeans_begin(float *sums, int32_t *counts, size_t n_sums, size_t n_counts, void *state, hipStream_t stream);
 int launch_kmeans_assign(const EncodeParams &p, int iter, void *state, hipStream_t stream);
-int launch_kmeans_end(const float *sums, const int32_t *counts, __half *cb, int32_t *counts_out, size_t n_centroids,
+int launch_kmeans_end(float *sums, int32_t *counts, __half *cb, int32_t *counts_out, size_t n_centroids,
                       int d, int iter, float tol, void *state, int32_t *iters_run, double *errors, hipStream_t stream);
 int launch_encode(const EncodeParams &p, hipStream_t stream);
 int launch_export_value_codes(const uint8_t *tiled, uint8_t *rows, int BH, int M, long long N, long long n_cap,

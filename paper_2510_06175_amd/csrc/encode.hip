@@ -358,28 +358,25 @@ void vq_tile_kernel(EncodeParams p, int tiles_per_wg, int iter, KmeansState *sta
 }
 
 
-// Start of a training iteration: sums and counts cleared, the error accumulator reset (and, before
-// the first iteration, the whole state).
-__global__ void kmeans_begin_kernel(float *sums, int32_t *counts, size_t n_sums, size_t n_counts, int iter,
-                                    KmeansState *state)
+// Start of a training: sums, counts and state cleared.  (Every iteration's end leaves them cleared for the next one:
+// a launch of its own per iteration took about 3 us.)
+__global__ void kmeans_begin_kernel(float *sums, int32_t *counts, size_t n_sums, size_t n_counts, KmeansState *state)
 {
-    if (iter > 0 && iter > state->stop_at) return;
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n_sums) sums[i] = 0.f;
     if (i < n_counts) counts[i] = 0;
     if (i == 0) {
         state->err_cur = 0.0;
-        if (iter == 0) {
-            state->err_prev = 0.0;
-            state->stop_at = 0x7fffffff;
-        }
+        state->err_prev = 0.0;
+        state->stop_at = 0x7fffffff;
     }
 }
 
 // End of a training iteration: the centroid update in place (an empty cluster keeps its centroid),
 // the cluster sizes, the iteration's error, and the stopping rule: the training stops after this
-// update when the error improved by no more than tol times the error of the iteration before.
-__global__ void kmeans_end_kernel(const float *sums, const int32_t *counts, __half *cb, int32_t *counts_out,
+// update when the error improved by no more than tol times the error of the iteration before.  Sums, counts and the
+// error accumulator are cleared as they are read.
+__global__ void kmeans_end_kernel(float *sums, int32_t *counts, __half *cb, int32_t *counts_out,
                                   size_t n_centroids, int d, int iter, float tol, KmeansState *state,
                                   int32_t *iters_run, double *errors)
 {
@@ -391,12 +388,17 @@ __global__ void kmeans_end_kernel(const float *sums, const int32_t *counts, __ha
         if (iters_run) *iters_run = iter + 1;
         if (iter >= 1 && prev - e <= (double)tol * prev) state->stop_at = iter;
         state->err_prev = e;
+        state->err_cur = 0.0;
     }
     if (c >= n_centroids) return;
     const int n = counts[c];
     if (counts_out) counts_out[c] = n;
+    counts[c] = 0;
     if (n > 0)
-        for (int j = 0; j < d; ++j) cb[c * d + j] = __float2half(sums[c * d + j] / (float)n);
+        for (int j = 0; j < d; ++j) {
+            cb[c * d + j] = __float2half(sums[c * d + j] / (float)n);
+            sums[c * d + j] = 0.f;
+        }
 }
 
 // Decode-time append (Eq. 9) and other short inputs: one wavefront per token and NS (4, or M / 4 if
@@ -989,8 +991,8 @@ int launch_fill_tiles(const EncodeParams &p, hipStream_t stream)
 // K-Means: 8 wavefronts per workgroup, 16 with runs of 48 tiles or more.  A workgroup fills the LDS alone, so 16
 // wavefronts hide more of the searches, but each has half of the registers and half of the sub-spaces between
 // two barriers.  4 iterations and the smoothing factors, 8 heads, D = 128, 8 / 16 wavefronts: d = 4, 2000 tokens (runs of
-// 4 tiles) 252 / 286 us, 8000 (12) 443 / 504, 32768 (32) 1133 / 1130, 65536 (64) 2052 / 1958; d = 2, 2000 (4) 292 / 373, 16000
-// (32) 1007 / 1013, 32768 (64) 1827 / 1750.
+// 4 tiles) 240 / 281 us, 8000 (12) 395 / 470, 32768 (32) 938 / 959, 65536 (64) 1688 / 1626; d = 2, 2000 (4) 276 / 365, 16000
+// (32) 809 / 824, 65536 (128) 2732 / 2548.
 template <int D, int d>
 int launch_kmeans_tiles(const EncodeParams &p, int iter, void *state, hipStream_t stream)
 {
@@ -1102,16 +1104,15 @@ int launch_kmeans_assign(const EncodeParams &p, int iter, void *state, hipStream
     }
 }
 
-int launch_kmeans_begin(float *sums, int32_t *counts, size_t n_sums, size_t n_counts, int iter, void *state,
-                        hipStream_t stream)
+int launch_kmeans_begin(float *sums, int32_t *counts, size_t n_sums, size_t n_counts, void *state, hipStream_t stream)
 {
     const size_t n = n_sums > n_counts ? n_sums : n_counts;
     hipLaunchKernelGGL(kmeans_begin_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, sums, counts,
-                       n_sums, n_counts, iter, static_cast<KmeansState *>(state));
+                       n_sums, n_counts, static_cast<KmeansState *>(state));
     return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
-int launch_kmeans_end(const float *sums, const int32_t *counts, __half *cb, int32_t *counts_out, size_t n_centroids,
+int launch_kmeans_end(float *sums, int32_t *counts, __half *cb, int32_t *counts_out, size_t n_centroids,
                       int d, int iter, float tol, void *state, int32_t *iters_run, double *errors, hipStream_t stream)
 {
     hipLaunchKernelGGL(kmeans_end_kernel, dim3((unsigned)((n_centroids + 255) / 256)), dim3(256), 0, stream, sums,
