@@ -1,4 +1,5 @@
-"""ctypes binding of ``libvecinfer.so``: same names as the C ABI, argument marshalling only.
+"""Binding of ``libvecinfer.so``: same names as the C ABI, argument marshalling only, by ctypes and, for the calls
+of a decode step and the cache fill, by a native module that makes the same checks in less time (``csrc/fastcall.cpp``).
 
 Tensors are torch CUDA (HIP) tensors used purely as device buffers; shapes, dtypes,
 contiguity and device are checked here and the raw pointers handed to the library,
@@ -76,6 +77,10 @@ class Config:
     @_once
     def _c(self) -> _Cfg:
         return self.c()
+
+    @_once
+    def _p(self) -> int:
+        return C.addressof(self._c)
 
     @_once
     def _lam_shape(self) -> tuple:
@@ -176,7 +181,25 @@ def lib() -> C.CDLL:
         L.vecinfer_strerror.restype = C.c_char_p
         L.vecinfer_version.restype = C.c_int
         _lib = L
+        _bind_fast(L)
     return _lib
+
+
+# The module that does the hot calls' checks and conversions natively, once the library is loaded.  Its functions
+# return None for arguments they leave to the checks here; without it every call takes that way.
+_fast = None
+
+
+def _bind_fast(L: C.CDLL) -> None:
+    global _fast
+    try:
+        from . import _fastcall as m
+    except ImportError:
+        return
+    if m.torch_version == torch.__version__.split("+")[0]:
+        m.bind(*(C.cast(getattr(L, "vecinfer_" + n), C.c_void_p).value for n in (
+            "encode_keys", "encode_values", "append_kv", "decode_attention", "decode_attention_residual", "decode_step")), _stream)
+        _fast = m
 
 
 def strerror(code: int) -> str:
@@ -212,6 +235,10 @@ def _stream(stream) -> int:
 
 def vecinfer_encode_keys(cfg: Config, k_f16, lam, cb_k, k_idx, pos0: int = 0, stream=None) -> None:
     """Smooth + Hadamard + VQ of T new keys into rows pos0.. of the code cache."""
+    if _fast is not None:
+        rc = _fast.encode(cfg._p, k_f16, lam, cb_k, k_idx, pos0, stream) if lam is not None else None
+        if rc is not None:
+            return _check(rc)
     B, Hkv, T, D = k_f16.shape
     n_cap = k_idx.shape[2]
     _check(lib().vecinfer_encode_keys(
@@ -224,6 +251,10 @@ def vecinfer_encode_keys(cfg: Config, k_f16, lam, cb_k, k_idx, pos0: int = 0, st
 
 def vecinfer_encode_values(cfg: Config, v_f16, cb_v, v_idx, pos0: int = 0, stream=None) -> None:
     """VQ of T new (untransformed) values into rows pos0.. of the code cache."""
+    if _fast is not None:
+        rc = _fast.encode(cfg._p, v_f16, None, cb_v, v_idx, pos0, stream)
+        if rc is not None:
+            return _check(rc)
     B, Hkv, T, D = v_f16.shape
     n_cap = v_idx.shape[2]
     _check(lib().vecinfer_encode_values(
@@ -235,6 +266,10 @@ def vecinfer_encode_values(cfg: Config, v_f16, cb_v, v_idx, pos0: int = 0, strea
 
 def vecinfer_append_kv(cfg: Config, k_f16, v_f16, lam, cb_k, cb_v, k_idx, v_idx, pos0: int, stream=None) -> None:
     """Decode-time append (Eq. 9): encode T <= 16 new keys and values in one launch."""
+    if _fast is not None:
+        rc = _fast.append(cfg._p, k_f16, v_f16, lam, cb_k, cb_v, k_idx, v_idx, pos0, stream)
+        if rc is not None:
+            return _check(rc)
     B, Hkv, T, D = k_f16.shape
     n_cap = k_idx.shape[2]
     _check(lib().vecinfer_append_kv(
@@ -268,6 +303,11 @@ def vecinfer_decode_attention(cfg: Config, q_f16, lam, cb_k, cb_v, k_idx, v_idx,
                               lse=None, seq_lens=None, N: int | None = None, num_splits: int = 0,
                               variant: int = VARIANT_AUTO, stream=None) -> None:
     """One fused VQ decode-attention step; writes out_f16 [B, Hq, D] (and lse [B, Hq])."""
+    if _fast is not None:
+        rc = _fast.decode(cfg._p, q_f16, lam, cb_k, cb_v, k_idx, v_idx, workspace, out_f16, lse, seq_lens, N, num_splits,
+                          variant, stream)
+        if rc is not None:
+            return _check(rc)
     B = q_f16.shape[0]
     n_cap = k_idx.shape[2]
     N = n_cap if N is None else N
@@ -315,6 +355,11 @@ def vecinfer_decode_attention_residual(cfg: Config, q_f16, lam, cb_k, cb_v, k_id
                                        R: int | None = None, num_splits: int = 0, variant: int = VARIANT_AUTO,
                                        stream=None) -> None:
     """Decode step over the code cache plus a full-precision window k_res / v_res [B, Hkv, r_cap, D]."""
+    if _fast is not None:
+        rc = _fast.decode(cfg._p, q_f16, lam, cb_k, cb_v, k_idx, v_idx, workspace, out_f16, lse, seq_lens, N, num_splits,
+                          variant, stream, k_res, v_res, res_lens, R)
+        if rc is not None:
+            return _check(rc)
     B = q_f16.shape[0]
     n_cap = k_idx.shape[2]
     N = n_cap if N is None else N
@@ -342,6 +387,11 @@ def vecinfer_decode_step(cfg: Config, q_f16, k_new, v_new, lam, cb_k, cb_v, k_id
                          lse=None, seq_lens=None, N: int | None = None, num_splits: int = 0,
                          variant: int = VARIANT_AUTO, stream=None) -> None:
     """Append the new token (k_new, v_new [B, Hkv, 1, D]) as each sequence's last one and attend."""
+    if _fast is not None:
+        rc = _fast.decode(cfg._p, q_f16, lam, cb_k, cb_v, k_idx, v_idx, workspace, out_f16, lse, seq_lens, N, num_splits,
+                          variant, stream, k_new, v_new)
+        if rc is not None:
+            return _check(rc)
     B = q_f16.shape[0]
     n_cap = k_idx.shape[2]
     N = n_cap if N is None else N

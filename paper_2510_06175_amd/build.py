@@ -4,10 +4,12 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvecinfer.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")       # the hot calls' argument checks, see csrc/fastcall.cpp
 SOURCES = ["api.hip", "merge.hip", "encode.hip", "calibrate.hip", "probe.hip", "decode_lut.hip", "decode_mfma.hip", "decode_mfma_wide.hip", "decode_mfma_wide64.hip", "decode_mfma_tiled.hip", "decode_roles.hip"]
 
 # Packed-fp32 VALU forms are switched off for the device pass: hipcc otherwise forms them
@@ -31,6 +33,20 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
+def fastcall_command() -> list | None:
+    """The host compiler's line for the Python module; None without Python's headers (the calls then go through ctypes)."""
+    python = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(python, "Python.h")):
+        return None
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    return ["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include/torch/csrc/api/include"), "-I", python,
+            os.path.join(CSRC, "fastcall.cpp"), "-o", FASTCALL, "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch",
+            "-ltorch_cpu", "-lc10"]
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
     """Compile every kernel source and link the shared library.  Always recompiles."""
     objs = []
@@ -42,12 +58,17 @@ def build(verbose: bool = False, extra_flags=()) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    if os.path.exists(FASTCALL):
+        os.remove(FASTCALL)
+    cmd = fastcall_command()
+    if cmd:
+        procs.append(("fastcall.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, pr in procs:
         out, _ = pr.communicate()
         # the host pass warns that it does not know the packed-fp32 feature: harmless
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l and l.strip())
         if pr.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{out}")
+            raise RuntimeError(f"compiling {src} failed:\n{out}")
         if verbose and out:
             print(out, flush=True)
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
