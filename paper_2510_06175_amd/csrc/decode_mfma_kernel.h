@@ -212,8 +212,11 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     const int vgrp0 = (s + S_ - ITEMS_K % S_) % S_;        // first value group of this workgroup
     const bool has_new = fused && (s < ITEMS_K || (WV ? vgrp0 < ITEMS_V : s < ITEMS_V));
     long long n0, n1;
-    {
-        // equal chunks of whole tiles; trailing splits may be empty (a sequence is shorter than 2^31: 32-bit division)
+    if constexpr (WK || WV) {
+        // (in 32 bits as below, 32 ragged sequences of up to 8411 tokens, D = 64, 12-bit codes, took 43.81 us instead of 43.44)
+        split_range(fused ? len - 1 : len, S_, s, kTile, n0, n1);
+    } else {
+        // equal chunks of whole tiles; trailing splits may be empty (the host checks N D / 2 < 2^31: 32-bit division)
         const unsigned n = (unsigned)(fused ? len - 1 : len);
         const unsigned chunk = ((n + S_ - 1) / (unsigned)S_ + kTile - 1) / kTile * kTile;
         n0 = (long long)s * chunk;
@@ -236,7 +239,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
         constexpr int IK = WK ? ITEMS_K : 0, IV = WV ? ITEMS_V : 0;
         if (fused && S_ >= IK && S_ >= IV) {
             const long long total = len - 1 + wK * IK + wV * IV;
-            long long chunk = ((unsigned)total + S_ - 1) / (unsigned)S_;
+            long long chunk = (total + S_ - 1) / S_;
             chunk = (chunk + kTile - 1) / kTile * kTile;
             if (chunk >= wK + wV) {
                 const int a = ITEMS_K % S_;                    // first workgroup with a value group
@@ -792,8 +795,8 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     const int tiles_here = (int)(n1 - n0 < NW * kTile ? (n1 - n0 + kTile - 1) / kTile : NW);
     auto items8 = [&](auto kv_c) {
         constexpr int kv = decltype(kv_c)::value, MX = kv == 0 ? MK : MV;
-        const int key_items = WK ? 0 : (MK - s + S_ - 1) / S_;
-        const int first = (wave_u + 2 * NW - tiles_here % NW - (kv == 0 ? 0 : key_items % NW)) % NW;
+        const int key_items = S_ >= MK ? (s < MK) : 2 * S_ >= MK ? 2 : 4 * S_ >= MK ? 4 : 0;   // about; any deal is right
+        const int first = (wave_u + 2 * NW - tiles_here % NW - (kv == 0 || WK ? 0 : key_items)) % NW;
         if (s + (first + NW) * S_ < MX) {
             for (int i0 = first; s + i0 * S_ < MX; i0 += 4 * NW) new_items(kv_c, std::integral_constant<int, 4>{}, i0);
         } else if (s + first * S_ < MX) {
