@@ -791,12 +791,12 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     // 8-bit codes: the key items (sub-spaces s, s + S, ..), then the value items, go to wavefront after wavefront,
     // starting with the first one that has no tile (a workgroup with a tile for everybody: with the first
     // ones, which finish their tiles first); a wavefront with one item of a kind (the usual case: at least as
-    // many splits as sub-spaces) takes it alone, otherwise four at a time.
+    // many splits as sub-spaces) takes it alone, otherwise four at a time.  The value items start two wavefronts behind the
+    // keys': with the keys' own number of items instead, 4 sequences of 2500 tokens (8 splits) took 11.70 us instead of 11.34.
     const int tiles_here = (int)(n1 - n0 < NW * kTile ? (n1 - n0 + kTile - 1) / kTile : NW);
     auto items8 = [&](auto kv_c) {
         constexpr int kv = decltype(kv_c)::value, MX = kv == 0 ? MK : MV;
-        const int key_items = S_ >= MK ? (s < MK) : 2 * S_ >= MK ? 2 : 4 * S_ >= MK ? 4 : 0;   // about; any deal is right
-        const int first = (wave_u + 2 * NW - tiles_here % NW - (kv == 0 || WK ? 0 : key_items)) % NW;
+        const int first = (wave_u + 2 * NW - tiles_here % NW - (kv == 0 || WK ? 0 : 2)) % NW;
         if (s + (first + NW) * S_ < MX) {
             for (int i0 = first; s + i0 * S_ < MX; i0 += 4 * NW) new_items(kv_c, std::integral_constant<int, 4>{}, i0);
         } else if (s + first * S_ < MX) {
