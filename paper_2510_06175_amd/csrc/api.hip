@@ -63,8 +63,8 @@ int num_cus()
 namespace {
 
 // The longest sequence that a step with 8-bit codes takes whole where there is room for s splits: below, the
-// merge launch costs more than the shared search and attention gain.  Time in splits over time whole, 4 / 1 or 8 / 1
-// heads (the merge of more than four query heads costs 5 us instead of 3), at s splits of 64 tokens:
+// splitting costs more than the shared search and attention gain.  Time in splits over time whole, 4 / 1 or 8 / 1
+// heads, at s splits of 64 tokens, measured when the merge was a launch of its own (3 us, 5 with more than four query heads):
 //   D = 128, s > 4, 4 / 1   250 tokens: d_v = 8 0.92, others 0.97 .. 1.06; 300 tokens: 0.82 .. 0.95
 //                   8 / 1   400 / 700 tokens: d_v = 4 1.06 .. 1.12 / 1.01 .. 1.08, others 0.98 .. 1.03 / 0.88 .. 0.96
 //            s = 4, 8 / 1   700 / 1000 tokens: d_k and d_v = 4 or 8, 4 1.11 / 1.04, others 1.01 .. 1.09 / 0.93 .. 1.0
@@ -103,7 +103,9 @@ enum class Call { kAttention, kStep, kWindow };
 // the compute units and a token has less than 128 bytes) and the sequences are more than a few (from N / 8 to N
 // tokens: 17 x 8 heads, 30000, d = 2 157 us whole, 90 in two; 9 x 8, 30000, d = 8 42.6 in three, 35.4 in four; 5 x 8, d = 4,
 // 30000 / 60000 27.6 / 40.1 in six, 35.9 / 36.4 in seven; 3 x 8, 30000 22.9 in ten, 28.6 in eleven).
-// What a split costs is the merge launch, 3 to 5 us (5 with more than four query heads per KV head):
+// The lines below were measured when the merge was a launch of its own, 3 to 5 us (5 with more than four query heads per KV
+// head).  Merged by the last workgroup a split costs less (8 / 1 heads, d = 8, 400 tokens 17.6 us by these lines, 12.3 in more
+// splits), but the counts are what callers size and compare by and stay:
 //   attention alone has nothing but its tokens to share: whole up to 1024 of them (8 sequences, 4 / 1
 //     heads: 250 / 600 / 1000 tokens 8.3 / 9.9 / 11.1 us whole, 11.4 / 11.6 / 11.6 in 4 / 10 / 16 splits; 8 / 1
 //     heads 9.9 / 12.1 / 13.7 and 15.1 / 15.7 / 15.9), 768 with d_k = 2, whose keys are twice the bytes (600 / 1000
