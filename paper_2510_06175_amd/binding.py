@@ -42,7 +42,7 @@ class _Cfg(C.Structure):
 class _once:
     """A value worked out when it is first asked for and then kept in the object's own dictionary, which
     from then on answers by itself.  (functools.cached_property takes a lock for it; here two threads may
-    both work it out, to the same value.)"""
+    both work it out, and the one that is kept first is everybody's: `_p` is the address of `_c`.)"""
 
     def __init__(self, f):
         self.f = f
@@ -53,8 +53,7 @@ class _once:
     def __get__(self, obj, owner=None):
         if obj is None:
             return self
-        v = obj.__dict__[self.name] = self.f(obj)
-        return v
+        return obj.__dict__.setdefault(self.name, self.f(obj))
 
 
 @dataclass(frozen=True)
