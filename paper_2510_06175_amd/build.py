@@ -10,7 +10,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvecinfer.so")
 FASTCALL = os.path.join(HERE, "_fastcall.so")       # the hot calls' argument checks, see csrc/fastcall.cpp
-SOURCES = ["api.hip", "merge.hip", "encode.hip", "calibrate.hip", "probe.hip", "decode_lut.hip", "decode_mfma.hip", "decode_mfma_wide.hip", "decode_mfma_wide64.hip", "decode_mfma_tiled.hip", "decode_roles.hip"]
+SOURCES = ["api.hip", "merge.hip", "encode.hip", "calibrate.hip", "probe.hip", "decode_lut.hip", "decode_roles.hip"]
+# the matrix-core attention kernels, compiled once for the calls without a residual window and once for those with one
+MFMA_SOURCES = ["decode_mfma.hip", "decode_mfma_wide.hip", "decode_mfma_wide64.hip", "decode_mfma_tiled.hip"]
 
 # Packed-fp32 VALU forms are switched off for the device pass: hipcc otherwise forms them
 # from plain float code.
@@ -51,9 +53,12 @@ def build(verbose: bool = False, extra_flags=()) -> str:
     """Compile every kernel source and link the shared library.  Always recompiles."""
     objs = []
     procs = []
-    for src in SOURCES:
-        obj = os.path.join(CSRC, src.replace(".hip", ".o"))
-        cmd = [hipcc(), *FLAGS, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
+    units = [(src, src, []) for src in SOURCES]
+    for src in MFMA_SOURCES:
+        units += [(src, src, ["-DVECINFER_WINDOW=0"]), (src, src.replace("decode_mfma", "decode_mfma_window"), ["-DVECINFER_WINDOW=1"])]
+    for src, name, defines in units:
+        obj = os.path.join(CSRC, name.replace(".hip", ".o"))
+        cmd = [hipcc(), *FLAGS, *defines, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))

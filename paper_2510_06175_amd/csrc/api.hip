@@ -399,7 +399,7 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     }
     if (N > 0)
         rc = use_roles  ? launch_decode_roles(p, static_cast<hipStream_t>(stream))
-             : use_mfma ? launch_decode_mfma(p, static_cast<hipStream_t>(stream))
+             : use_mfma ? (window ? launch_decode_mfma<true> : launch_decode_mfma<false>)(p, static_cast<hipStream_t>(stream))
                         : launch_decode_lut(p, static_cast<hipStream_t>(stream));
     else
         p.S = 0;                        // nothing but the window: the merge kernel sees no split partial

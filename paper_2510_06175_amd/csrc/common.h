@@ -190,11 +190,28 @@ int num_cus();   // compute units of the chip (queried once per process; sizes g
 // launchers (one translation unit each)
 int launch_merge(const DecodeParams &p, hipStream_t stream);   // splits (+ residual window) -> out, lse
 int launch_decode_lut(const DecodeParams &p, hipStream_t stream);
-int launch_decode_mfma(const DecodeParams &p, hipStream_t stream);
-int launch_decode_mfma_wide128(const DecodeParams &p, hipStream_t stream);   // 10- / 12-bit codes, D = 128
-int launch_decode_mfma_wide64(const DecodeParams &p, hipStream_t stream);    // 10- / 12-bit codes, D = 64
-int launch_decode_mfma_tiled(const DecodeParams &p, hipStream_t stream);  // 8-bit codes, tiled value codes
-bool decode_mfma_supports(const DecodeParams &p);
+// WIN: the call has a residual window (and no new token)
+template <bool WIN> int launch_decode_mfma(const DecodeParams &p, hipStream_t stream);
+template <bool WIN> int launch_decode_mfma_wide128(const DecodeParams &p, hipStream_t stream);   // 10- / 12-bit codes, D = 128
+template <bool WIN> int launch_decode_mfma_wide64(const DecodeParams &p, hipStream_t stream);    // 10- / 12-bit codes, D = 64
+template <bool WIN> int launch_decode_mfma_tiled(const DecodeParams &p, hipStream_t stream);  // 8-bit codes, tiled value codes
+inline bool decode_mfma_supports(const DecodeParams &p)
+{
+    const bool dk_ok = p.dk == 8 || p.dk == 4 || p.dk == 2;
+    const bool dv_ok = p.dv == 8 || p.dv == 4 || p.dv == 2;
+    // 10- and 12-bit codes: d = 4 or 8 on that side (rows of whole 32-bit words: not d = 8 with 10 bits
+    // at D = 64), d = 4 or 8 on the other side too
+    auto wide = [](int b) { return b == 10 || b == 12; };
+    auto row_ok = [&](int d, int b) { return b == 8 || (wide(b) && (p.D / d * b) % 32 == 0); };
+    bool bits_ok = p.bk == 8 && p.bv == 8;
+    if (wide(p.bk) || wide(p.bv)) bits_ok = row_ok(p.dk, p.bk) && row_ok(p.dv, p.bv) && p.dk >= 4 && p.dv >= 4;
+    // code rows are addressed with 32-bit byte offsets (a row is at most D / 2 bytes)
+    // tiled value codes: 8-bit codes on both sides (the instantiations built)
+    // (and not d_v = 8 at D = 64: fewer than the 16 sub-spaces the block order is made of)
+    const bool tiled_ok = !p.v_tiled || (p.bk == 8 && p.bv == 8 && p.n_cap % 64 == 0 && !(p.D == 64 && p.dv == 8));
+    return (p.D == 128 || p.D == 64) && p.G >= 1 && p.G <= 8 && dk_ok && dv_ok && bits_ok && tiled_ok &&
+           (p.v_tiled ? (p.N + 63) / 64 * 64 : p.N) * (long long)(p.D / 2) < (1LL << 31);
+}
 bool decode_roles_supports(const DecodeParams &p);                        // score / value wavefront kernel
 int launch_decode_roles(const DecodeParams &p, hipStream_t stream);
 

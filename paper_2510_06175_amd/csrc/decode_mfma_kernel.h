@@ -53,7 +53,12 @@ namespace {
 // codes packed end to end in the token's row, one table of 2^b centroids for all sub-spaces.
 // VT: 8-bit value codes stored in tiles of 64 tokens (v_tiled_offset): a lane's share of a tile is
 // 16 NROUND_V bytes, fetched with NROUND_V 16-byte loads.
-template <int kD, int DK, int DVR, int HG, int NW, bool SPLITQ, int BK = 8, int BV = 8, bool VT = false>
+// WIN: calls with a residual window, which never have a new token to encode.  Compiled apart (VECINFER_WINDOW), because
+// in one kernel the window's code cost the calls without one registers and time (D = 128, d = 4: 199 instead of 192, 236
+// instead of 222 with two head groups; 32 sequences, 4 / 1 heads: 502 tokens, d = 2 19.02 us, apart 18.78; one of 1000
+// tokens 10.22 and 9.86 with d = 8; only with 12-bit codes at D = 64 is it the other way round: 32 of up to 8411
+// tokens 43.4 and 43.9).
+template <int kD, int DK, int DVR, int HG, int NW, bool SPLITQ, int BK, int BV, bool VT, bool WIN>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4, kD == 128 ? NW / 4 : NW / 2)))
 void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half *cb_k_arg, const __half *cb_v_arg,
                         const __half *k_new_arg, const __half *v_new_arg, unsigned hkv_g_arg, int S_, DecodeParams p)
@@ -147,7 +152,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     const __half *const qsrc = q_arg + (((size_t)b * Hkv_ + g) * G_ + (q_role ? wave : 0)) * kD;
     const unsigned qh0 = raw16(qsrc + lane), qh1 = raw16(qsrc + (kD == 128 ? 64 : 0) + lane);
     const float ql0 = lam_arg[(size_t)g * kD + lane], ql1 = lam_arg[(size_t)g * kD + (kD == 128 ? 64 : 0) + lane];
-    const __half *const nsrc = k_new_arg ? (wave == NW - 1 ? v_new_arg : k_new_arg) + bg * kD : qsrc;
+    const __half *const nsrc = !WIN && k_new_arg ? (wave == NW - 1 ? v_new_arg : k_new_arg) + bg * kD : qsrc;
     const unsigned nh0 = raw16(nsrc + lane), nh1 = raw16(nsrc + (kD == 128 ? 64 : 0) + lane);
     const float nl0 = ql0, nl1 = ql1;
     asm volatile("" ::: "memory");                 // keep these loads ahead of the big ones below
@@ -203,7 +208,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     // this launch (below), so the tile loop covers the len - 1 older tokens only.  Workgroup s
     // encodes sub-spaces s, s + S, ... of the new token's key and value.
     const long long len = seq_len_of(p, b);
-    const bool fused = k_new_arg != nullptr && len > 0;
+    const bool fused = !WIN && k_new_arg != nullptr && len > 0;
     // items of the new token that are shared out: sub-spaces (8-bit codes), or groups of four
     // sub-spaces whose codes fill a whole number of bytes (10- and 12-bit codes)
     constexpr int ITEMS_K = WK ? MK / 4 : MK, ITEMS_V = WV ? MV / 4 : MV;
@@ -263,7 +268,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     constexpr int kWinItems = kMaxResidual / 16;
     static_assert(kWinItems <= NW, "at most one item per wavefront, whatever S is");
     int r_len = 0;
-    if (p.k_res) {
+    if constexpr (WIN) {
         r_len = p.R;
         if (p.res_lens) {
             typedef const int32_t __attribute__((address_space(4))) *const_i32_ptr;
@@ -271,7 +276,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
             r_len = v < 0 ? 0 : (v > p.R ? p.R : v);
         }
     }
-    const bool has_win = s < kWinItems && 16 * s < r_len;
+    const bool has_win = WIN && s < kWinItems && 16 * s < r_len;
 
     // The arrival word of this (sequence, KV head): the look at it travels behind the tables.
     arrival_t word = 0;
@@ -464,7 +469,7 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     // The wavefront's window rows, if it has any: raw queries and keys as the MFMA wants them, 8 consecutive channels
     // of row / column lane % 16 per lane.  (Clamped to row R - 1, which is always inside the allocation.)
     const int win_row0 = 16 * (s + (NW - 1 - wave_u) * S_);
-    const bool win_item = has_win && win_row0 < r_len && win_row0 < 16 * kWinItems;
+    const bool win_item = WIN && has_win && win_row0 < r_len && win_row0 < 16 * kWinItems;
     half8 win_q[kD / 32], win_k[kD / 32];
     if (win_item) {
         const __half *const qw = q_arg + (bg * G_ + (col < G_ ? col : 0)) * kD;
@@ -1331,21 +1336,21 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     if (S_ > 1) merge_arrived<kD, KG, BLOCK>(p, reinterpret_cast<float *>(smem), bg, bg * G_, S_, G_, fused);
 }
 
-template <int kD, int DK, int DV, int HG, int NW, bool SPLITQ, int BK, int BV, bool VT>
+template <int kD, int DK, int DV, int HG, int NW, bool SPLITQ, int BK, int BV, bool VT, bool WIN>
 int launch_hg(const DecodeParams &p, hipStream_t stream)
 {
     constexpr int KG = kG * HG;
     constexpr size_t cbk = BK > 8 ? ((size_t)1 << BK) * DK * 2 : (size_t)kCentroids * kD * 2;
     constexpr size_t cbv = BV > 8 ? ((size_t)1 << BV) * DV * 2 : (size_t)kCentroids * kD * 2;
     // the tables, q~, the new token's and the window's scratch during the tile loop; the wavefronts' partials after it
-    constexpr size_t loop_bytes = cbk + cbv + sizeof(float) * ((KG + 3) * kD + (kD / DK) * KG + NW * 18 * KG) + 8 * 4 * NW + 16;
+    constexpr size_t loop_bytes = cbk + cbv + sizeof(float) * ((KG + 3) * kD + (kD / DK) * KG + (WIN ? NW * 18 * KG : 0)) + 8 * 4 * NW + 16;
     constexpr size_t merge_bytes = sizeof(float) * (NW * KG * kD + 2 * NW * KG);
     constexpr size_t final_bytes = sizeof(float) * merge_arrived_floats(kD, KG);
     constexpr size_t wave_bytes = merge_bytes > final_bytes ? merge_bytes : final_bytes;
     constexpr size_t smem = loop_bytes > wave_bytes ? loop_bytes : wave_bytes;
     // once per process and instantiation (function-local static: initialised thread-safely)
     static const bool configured = [] {
-        const void *fn = reinterpret_cast<const void *>(decode_mfma_kernel<kD, DK, DV, HG, NW, SPLITQ, BK, BV, VT>);
+        const void *fn = reinterpret_cast<const void *>(decode_mfma_kernel<kD, DK, DV, HG, NW, SPLITQ, BK, BV, VT, WIN>);
         // (the kernel takes the dynamic segment to start at LDS offset 0: no static LDS in front of it)
         hipFuncAttributes attr;
         if (hipFuncGetAttributes(&attr, fn) != hipSuccess || attr.sharedSizeBytes != 0) return false;
@@ -1353,16 +1358,19 @@ int launch_hg(const DecodeParams &p, hipStream_t stream)
     }();
     if (!configured) return -4;
     dim3 grid(p.Hkv, p.S, p.B);
-    hipLaunchKernelGGL((decode_mfma_kernel<kD, DK, DV, HG, NW, SPLITQ, BK, BV, VT>), grid, dim3(NW * 64), smem, stream,
+    hipLaunchKernelGGL((decode_mfma_kernel<kD, DK, DV, HG, NW, SPLITQ, BK, BV, VT, WIN>), grid, dim3(NW * 64), smem, stream,
                        p.q, p.lam, p.cb_k, p.cb_v, p.k_new, p.v_new, (unsigned)p.Hkv | (unsigned)p.G << 24, p.S, p);
     return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
+// Each translation unit is compiled twice (build.py): for the calls without and with a residual window.
+constexpr bool kWindow = VECINFER_WINDOW;
+
 template <int kD, int DK, int DV, int NW, bool SPLITQ, int BK = 8, int BV = 8, bool VT = false>
 int launch_typed(const DecodeParams &p, hipStream_t stream)
 {
-    return p.G <= kG ? launch_hg<kD, DK, DV, 1, NW, SPLITQ, BK, BV, VT>(p, stream)
-                     : launch_hg<kD, DK, DV, 2, NW, SPLITQ, BK, BV, VT>(p, stream);
+    return p.G <= kG ? launch_hg<kD, DK, DV, 1, NW, SPLITQ, BK, BV, VT, kWindow>(p, stream)
+                     : launch_hg<kD, DK, DV, 2, NW, SPLITQ, BK, BV, VT, kWindow>(p, stream);
 }
 
 } // namespace

@@ -4,7 +4,8 @@
 
 namespace vecinfer {
 
-int launch_decode_mfma_tiled(const DecodeParams &p, hipStream_t stream)
+template <>
+int launch_decode_mfma_tiled<kWindow>(const DecodeParams &p, hipStream_t stream)
 {
     if (!decode_mfma_supports(p) || !p.v_tiled || p.bk != 8 || p.bv != 8) return -2;
     const int key = p.D * 100 + p.dk * 10 + p.dv;

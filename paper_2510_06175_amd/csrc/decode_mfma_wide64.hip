@@ -50,7 +50,8 @@ int pick_bk(const DecodeParams &p, hipStream_t stream)
 
 } // namespace
 
-int launch_decode_mfma_wide64(const DecodeParams &p, hipStream_t stream)
+template <>
+int launch_decode_mfma_wide64<kWindow>(const DecodeParams &p, hipStream_t stream)
 {
     if (p.D != kHeadDim) return -2;
     if (p.dk == 4) return pick_bk<4>(p, stream);
