@@ -470,7 +470,9 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
     // of row / column lane % 16 per lane.  (Clamped to row R - 1, which is always inside the allocation.)
     const int win_row0 = 16 * (s + (NW - 1 - wave_u) * S_);
     const bool win_item = WIN && has_win && win_row0 < r_len && win_row0 < 16 * kWinItems;
+    constexpr bool kWinEarly = HG == 1 || kD == 64 || (DK > 2 && DVR > 2);   // where the rows meet their values, below
     half8 win_q[kD / 32], win_k[kD / 32];
+    unsigned win_touch = 0;                                // 64 bytes per lane: the value rows come to the L2 cache now
     if (win_item) {
         const __half *const qw = q_arg + (bg * G_ + (col < G_ ? col : 0)) * kD;
         const __half *const kw = p.k_res + (bg * p.r_cap + (win_row0 + col < p.R ? win_row0 + col : p.R - 1)) * kD;
@@ -479,6 +481,10 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
             win_q[ks] = *reinterpret_cast<const half8 *>(qw + 32 * ks + 8 * kg);
             win_k[ks] = *reinterpret_cast<const half8 *>(kw + 32 * ks + 8 * kg);
         }
+        const int touch_row = win_row0 + lane / (kD / 32);
+        if (!kWinEarly && lane < kD / 2)
+            win_touch = *reinterpret_cast<const unsigned *>(
+                p.v_res + (bg * p.r_cap + (touch_row < p.R ? touch_row : p.R - 1)) * kD + lane % (kD / 32) * 32);
     }
     // ---- q~ = (q * lambda) H_D for the 4 heads of the group (un-normalised butterflies):
     // wavefront hh transforms head hh in registers, a lane holding channels `lane` and
@@ -818,27 +824,35 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
 #pragma unroll
         for (int r = 0; r < NACC; ++r) acc_o[hg][r] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
-    // ---- residual window (Sec. 4.1): the wavefront's 16 rows are where its softmax starts from.  q . k =
-    // (q * lambda) H . (k / lambda) H (Eq. 7), so raw queries against raw keys give scores on the scale of the
-    // quantized tokens'.  Scores on the matrix cores, p and P.V in fp32: p goes through LDS to the lanes that own a
-    // head's channels, which read those channels of the 16 rows.  (A merge launch that scored the window behind the
+    // ---- residual window (Sec. 4.1), scores: q . k = (q * lambda) H . (k / lambda) H (Eq. 7), so raw queries against raw
+    // keys give scores on the scale of the quantized tokens'.  The wavefront's 16 rows are a partial (m, l, o) of their
+    // own, which joins behind the tiles: their maximum must not scale the quantized tokens' weights, which are fp16 (a
+    // window ahead by 2^20 would leave those few bits or none).  (A merge launch that scored the window behind the
     // attention kernel took 4.9 us; these items run beside the other wavefronts' tiles.)
-    if (win_item) {
-        constexpr int kChan = kD / 16;                     // channels of a lane: kChan col ..
-        typedef _Float16 halfc __attribute__((ext_vector_type(kChan)));
+    constexpr int kChan = kD / 16;                         // channels of a lane in P.V: kChan col ..
+    typedef _Float16 halfc __attribute__((ext_vector_type(kChan)));
+    float *const wp = sm_win + wave * (18 * KG);           // [KG][16] p, [KG] m, [KG] l
+    // P.V of the rows, in fp32: the lanes that own a head's channels read those of the 16 rows, and p from LDS.  Here (16
+    // sequences of 15468 tokens, 7 / 1 heads, d = 4 28.2 us, behind the tiles 28.8; 24 of up to 974, 4 / 1 heads, d = 2 13.4
+    // and 13.7) unless a lane's share of the result, 16 registers with two head groups, would be spilled, which it is at
+    // d = 2: then behind the tiles (32 of up to 1500 tokens, 8 / 1 heads 23.8 us, spilled 25.3).
+    halfc win_v[16];
+    float win_o[HG][kChan], win_m[HG], win_l[HG];
+    auto win_values = [&] {
         const __half *const vw = p.v_res + (bg * p.r_cap + win_row0) * kD + kChan * col;
-        halfc wv[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            wv[r] = halfc{};
-            if (win_row0 + r < r_len) wv[r] = *reinterpret_cast<const halfc *>(vw + (size_t)r * kD);
+            win_v[r] = halfc{};
+            if (win_row0 + r < r_len) win_v[r] = *reinterpret_cast<const halfc *>(vw + (size_t)r * kD);
         }
+    };
+    if (win_item) {
+        if constexpr (kWinEarly) win_values();
         floatx4 sc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < kD / 32; ++ks) sc = MFMA16(win_q[ks], win_k[ks], sc, 0, 0, 0);
         // register v of lane (col, kg): window row win_row0 + col, head 4 kg + v
         const float scale = kLog2e * rsqrtf((float)kD);
-        float *const wp = sm_win + wave * (18 * KG);       // [KG][16] p, [KG] m, [KG] l
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const float s2 = win_row0 + col < r_len ? sc[v] * scale : -INFINITY;
@@ -862,16 +876,18 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
                 }
             }
         }
+        asm volatile("" ::"v"(win_touch));                 // (on its way since the keys were requested)
+    }
+    auto win_pv = [&] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();                   // (the wavefront's own LDS operations execute in order)
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
         for (int hg = 0; hg < HG; ++hg) {
-            m_run[hg] = wp[16 * KG + kG * hg + (col >> 2)];
-            l_part[hg] = kg == 0 && (col & 3) == 0 ? wp[17 * KG + kG * hg + (col >> 2)] : 0.f;
-            float o[kChan];
+            win_m[hg] = wp[16 * KG + kG * hg + (col >> 2)];
+            win_l[hg] = wp[17 * KG + kG * hg + (col >> 2)];
 #pragma unroll
-            for (int c = 0; c < kChan; ++c) o[c] = 0.f;
+            for (int c = 0; c < kChan; ++c) win_o[hg][c] = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; r += 4) {
                 const float4 pr = *reinterpret_cast<const float4 *>(wp + (kG * hg + kg) * 16 + r);
@@ -879,14 +895,12 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int c = 0; c < kChan; ++c) o[c] = fmaf(p4[i], (float)wv[r + i][c], o[c]);
+                    for (int c = 0; c < kChan; ++c) win_o[hg][c] = fmaf(p4[i], (float)win_v[r + i][c], win_o[hg][c]);
             }
-#pragma unroll
-            for (int r = 0; r < NACC; ++r)
-#pragma unroll
-                for (int v = 0; v < kChanBlock; ++v) acc_o[hg][r][v] = o[kChanBlock * r + v];
         }
-    }
+    };
+    if constexpr (kWinEarly)
+        if (win_item) win_pv();
 
     // LDS byte address of centroid `code byte k of w` in the sub-space table at `base`:
     // one v_dot4_u32_u8 (w . (ENTRY_K << 8k) + base) instead of a bit-field extract and a shift-add.
@@ -1247,6 +1261,8 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
         if constexpr (!WK) items8(std::integral_constant<int, 0>{});
         if constexpr (!WV) items8(std::integral_constant<int, 1>{});
     }
+    if constexpr (!kWinEarly)
+        if (win_item) win_values();
     // ---- merge the wavefronts of this split through LDS (the codebooks are no longer needed)
     float l_head[HG];
 #pragma unroll
@@ -1255,6 +1271,21 @@ void decode_mfma_kernel(const __half *q_arg, const float *lam_arg, const __half 
         l_head[hg] += quad_xor<2>(l_head[hg]);
         l_head[hg] += __shfl_xor(l_head[hg], 16);
         l_head[hg] += __shfl_xor(l_head[hg], 32);
+    }
+    if (win_item) {                                        // the wavefront's tokens and its window rows: one partial
+        if constexpr (!kWinEarly) win_pv();
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg) {
+            const float m = fmaxf(m_run[hg], win_m[hg]);
+            const float a = __builtin_amdgcn_exp2f(m_run[hg] - m), w = __builtin_amdgcn_exp2f(win_m[hg] - m);
+            l_head[hg] = a * l_head[hg] + w * win_l[hg];
+            m_run[hg] = m;
+            const float a_o = __shfl(a, 4 * kg), w_o = __shfl(w, 4 * kg);      // lane 4 kg serves head kg
+#pragma unroll
+            for (int r = 0; r < NACC; ++r)
+#pragma unroll
+                for (int v = 0; v < kChanBlock; ++v) acc_o[hg][r][v] = fmaf(w_o, win_o[hg][kChanBlock * r + v], a_o * acc_o[hg][r][v]);
+        }
     }
     // A single split folds the fused new token in below.  Its score shares and dequantized value
     // sit in the scratch behind the tables, and with small shared tables (10-bit codes on both

@@ -123,9 +123,9 @@ def gpu_decode(shape, x, seq_lens=None, N=None, num_splits=0, variant=vb.VARIANT
 
 
 def gpu_decode_residual(shape, x, seq_lens=None, res_lens=None, N=None, R=None, num_splits=0,
-                        variant=vb.VARIANT_AUTO):
+                        variant=vb.VARIANT_AUTO, v_tiled=0):
     """As gpu_decode, plus the fp16 window x["k_res"], x["v_res"] [B, Hkv, r_cap, D]."""
-    cfg = cfg_of(shape)
+    cfg = cfg_of(shape, v_tiled)
     t = {k: dev(v) for k, v in x.items() if k in ("q", "lam", "cb_k", "cb_v", "k_idx", "v_idx", "k_res", "v_res")}
     B = t["q"].shape[0]
     N = t["k_idx"].shape[2] if N is None else N
