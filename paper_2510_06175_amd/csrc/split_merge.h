@@ -80,8 +80,9 @@ __device__ __forceinline__ float shared_load_half(const __half *p)
         __hip_atomic_load(reinterpret_cast<const unsigned short *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
 }
 
-// Sum and maximum over the wavefront, in every lane, on the vector ALU (DPP inside the rows of 16 lanes, row swaps
-// across them): no trip through the LDS crossbar.
+// Maximum over the wavefront, in every lane, or sum, on the vector ALU (DPP inside the rows of 16 lanes, row swaps
+// across them): no trip through the LDS crossbar.  The quads of a row add each other in turned orders, so a sum's last
+// bits differ from quad to quad: whoever needs one value takes one lane's.
 template <typename Op>
 __device__ __forceinline__ float wave_all(float x, Op op)
 {
@@ -181,7 +182,8 @@ __device__ __forceinline__ void merge_arrived(const DecodeParams &p, float *lds,
             M = fmaxf(M, tm[i]);
         }
         M = wave_all(M, max2);
-        const float s_new = new_tok ? wave_all(share, add2) : -INFINITY;
+        // (one lane's: all splits and the new token have to be weighed against the same M)
+        const float s_new = new_tok ? __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wave_all(share, add2)))) : -INFINITY;
         M = fmaxf(M, s_new);
         const float Mc = M > -INFINITY ? M : 0.f;        // nothing to attend to: all weights 0
         const float w_new = __builtin_amdgcn_exp2f(s_new - Mc);

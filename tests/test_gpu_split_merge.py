@@ -82,3 +82,38 @@ def test_replays_without_anything_between():
         call()
         torch.cuda.synchronize()
         assert torch.equal(got, out)
+
+
+def test_every_split_is_weighed_against_the_same_maximum():
+    """A new token whose score is the largest, at a size (about 2^18) where the order in which its shares are added
+    shows: 32 splits of equal tokens, each with a value channel of its own, must come out with equal weights."""
+    D, d, S = 128, 4, 32
+    N = 64 * S + 1
+    cfg, g = vb.Config(D, 1, 1, d, d), synth.rng(3)
+    H = oracle.hadamard(D)                                                 # orthonormal
+    row = g.uniform(15, 30, D).astype(np.float16)                          # the key of every token ..
+    x = g.uniform(50, 120, D)
+    x[0] = 1.0                                                             # .. but for channel 0, where the query is small
+    cb_k = np.zeros((1, D // d, 256, d), np.float16)
+    cb_k[0, :, 1] = cb_k[0, :, 2] = row.reshape(D // d, d)
+    cb_k[0, 0, 2, 0] -= 1                                                  # the older tokens score one unit (log2) less
+    cb_v = np.zeros((1, D // d, 256, d), np.float16)
+    cb_v[0, :, 1:1 + d] = 8 * np.eye(d)
+    q = (x * (D / np.log2(np.e)) @ H / np.sqrt(D)).astype(np.float16)      # (q H sqrt(D)) log2(e) / D = x
+    k_new = (row.astype(np.float64) @ H).astype(np.float16)
+    k_idx = np.ones((1, 1, N, D // d), np.uint8)
+    k_idx[:, :, :, 0] = 2
+    v_idx = np.zeros_like(k_idx)
+    for s in range(S):
+        v_idx[0, 0, 64 * s:64 * s + 64, s // d] = 1 + s % d
+    t = {n: dev(a) for n, a in dict(q=q[None, None], k=k_new[None, None, None], v=np.zeros((1, 1, 1, D), np.float16),
+                                    lam=np.ones((1, D), np.float32), cb_k=cb_k, cb_v=cb_v, k_idx=k_idx, v_idx=v_idx).items()}
+    out, lse = torch.zeros((1, 1, D), dtype=torch.float16, device="cuda"), torch.zeros((1, 1), device="cuda")
+    vb.vecinfer_decode_step(cfg, t["q"], t["k"], t["v"], t["lam"], t["cb_k"], t["cb_v"], t["k_idx"], t["v_idx"],
+                            vb.new_workspace(cfg, 1, N, S), out, lse=lse, num_splits=S)
+    torch.cuda.synchronize()
+    assert (t["k_idx"][0, 0, -1] == 1).all()                               # the new token is what it was made to be
+    assert lse.item() * np.log2(np.e) > 1 << 17
+    got = out[0, 0, :S].cpu().numpy()
+    assert 0.2 < got[0] < 0.26                                             # 8 / 32, less the new token's share
+    np.testing.assert_array_equal(got, got[0])
