@@ -302,3 +302,27 @@ def test_step_with_long_runs(D, d, T, keys):
         assert torch.equal(got[~full], cb[head, m].cpu().double()[~full])
         # fp16 centroids (2^-11), fp32 sums of values of both signs
         np.testing.assert_allclose(got[full], sums[full] / hist[full, None], rtol=1.5e-3, atol=1e-5)
+
+
+@pytest.mark.parametrize("D,d,bits", [(128, 4, 8), (64, 2, 8), (128, 8, 8), (128, 8, 12), (64, 4, 10)])
+def test_an_infinite_key_leaves_infinities(D, d, bits):
+    """One infinite channel: its token is infinite in every transformed channel, with the signs of the transform's
+    row, at no finite distance from any centroid, so it belongs to centroid 0 of each table.  (What has no value is
+    NaN only where infinities of both signs meet.)"""
+    shape = synth.Shape(1, 2, 1, D, 320, d, d, bits, bits)
+    x, lam, cb0 = _problem(shape, "keys", 5)
+    c = 37
+    x[0, 0, 100, c] = np.inf
+    tr = Trainer(shape, x, lam, cb0)
+    _, errors = tr.train(1, -1.0)
+    cb, codes, _ = tr.state()
+    assert (codes[0, 0, 100] == 0).all()
+    signs = oracle.hadamard(D)[c].reshape(D // d, d)
+    first = cb[0, :, 0].astype(np.float64)                                 # [sub-spaces or 1, d]
+    if bits == 8:
+        np.testing.assert_array_equal(first, np.where(signs > 0, np.inf, -np.inf))
+    else:                                                                  # one table: all sub-spaces meet in it
+        mixed = (signs > 0).any(0) & (signs < 0).any(0)
+        np.testing.assert_array_equal(first[0], np.where(mixed, np.nan, np.where(signs[0] > 0, np.inf, -np.inf)))
+    assert np.isposinf(errors[0])
+    assert np.isfinite(cb[0, :, 1:].astype(np.float64)).all()
