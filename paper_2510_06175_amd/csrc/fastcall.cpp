@@ -29,6 +29,7 @@ decltype(&vecinfer_decode_step) decode_step;
 PyObject *find_stream;                   // binding._stream
 
 struct Refused {};                       // an argument that the interpreter's checks have to look at
+struct Raised {};                        // Python's error is set
 
 const at::Tensor &tensor(PyObject *o)
 {
@@ -77,14 +78,12 @@ void *address(PyObject *o)
     return p;
 }
 
-// The stream's handle, asked for after the checks as the interpreter's path does: without a GPU it raises.
+// The stream's handle, asked for after the checks as the interpreter's path does, and what that raises is raised: it may
+// be an interrupt, which a second attempt would not see.
 void *stream_of(PyObject *o)
 {
     PyObject *const r = PyObject_CallFunctionObjArgs(find_stream, o, nullptr);
-    if (!r) {
-        PyErr_Clear();
-        throw Refused();
-    }
+    if (!r) throw Raised();
     struct Release {
         PyObject *r;
         ~Release() { Py_DECREF(r); }
@@ -134,6 +133,8 @@ PyObject *guarded(F &&f)
 {
     try {
         return PyLong_FromLong(f());
+    } catch (const Raised &) {
+        return nullptr;
     } catch (...) {
         Py_RETURN_NONE;
     }

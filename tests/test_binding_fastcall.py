@@ -62,3 +62,24 @@ def test_same_outcome_and_result_on_the_gpu(change, monkeypatch):
     plain = run()
     assert native[0] == plain[0]
     assert all(torch.equal(a, b) for a, b in zip(native[1:], plain[1:]))
+
+
+@pytest.mark.gpu
+def test_an_interrupt_while_the_stream_is_asked_for_is_raised():
+    """Ctrl-C may arrive in the Python function that finds the stream: it must end the call, not vanish in it."""
+    L = vb.lib()
+    names = ("encode_keys", "encode_values", "append_kv", "decode_attention", "decode_attention_residual", "decode_step")
+    at = [ctypes.cast(getattr(L, "vecinfer_" + n), ctypes.c_void_p).value for n in names]
+
+    def interrupted(stream):
+        raise KeyboardInterrupt
+
+    t = {n: x.cuda() for n, x in step_args().items()}
+    vb._fast.bind(*at, interrupted)
+    try:
+        with pytest.raises(KeyboardInterrupt):
+            vb.vecinfer_decode_step(CFG, **t)
+    finally:
+        vb._fast.bind(*at, vb._stream)
+    vb.vecinfer_decode_step(CFG, **t)
+    torch.cuda.synchronize()
