@@ -14,6 +14,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/version.h>
 
+#include <exception>
 #include <initializer_list>
 
 #include "../../include/vecinfer.h"
@@ -116,14 +117,15 @@ struct Cfg {
     }
 };
 
+// f: a call of the library, which throws nothing.  (Where the interpreter is shutting down, PyEval_RestoreThread ends
+// a daemon thread by unwinding it: no destructor and no catch-all may stand in its way, or the process aborts.)
 template <typename F>
 int without_gil(F &&f)
 {
-    struct Save {
-        PyThreadState *state = PyEval_SaveThread();
-        ~Save() { PyEval_RestoreThread(state); }
-    } save;
-    return f();
+    PyThreadState *const state = PyEval_SaveThread();
+    const int rc = f();
+    PyEval_RestoreThread(state);
+    return rc;
 }
 
 // f() -> status; None for anything that is not as expected (also torch's own exceptions: wrapped tensors
@@ -135,9 +137,10 @@ PyObject *guarded(F &&f)
         return PyLong_FromLong(f());
     } catch (const Raised &) {
         return nullptr;
-    } catch (...) {
-        Py_RETURN_NONE;
+    } catch (const Refused &) {
+    } catch (const std::exception &) {
     }
+    Py_RETURN_NONE;
 }
 
 // encode(cfg, x, lambda or None (values), codebook, codes, pos0, stream)
