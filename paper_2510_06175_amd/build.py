@@ -49,8 +49,26 @@ def fastcall_command() -> list | None:
             "-ltorch_cpu", "-lc10"]
 
 
+def build_fastcall() -> None:
+    """Compile the Python module.  The library does without it: where its compiler or torch's headers are missing or do not
+    fit, a message says so and the calls go through ctypes."""
+    if os.path.exists(FASTCALL):
+        os.remove(FASTCALL)
+    why = "no Python headers"
+    try:
+        cmd = fastcall_command()
+        if cmd:
+            r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+            if r.returncode == 0:
+                return
+            why = r.stdout
+    except (ImportError, OSError) as e:        # no torch, no compiler
+        why = str(e)
+    print(f"{os.path.basename(FASTCALL)} is not built, calls go through ctypes: {why}", file=sys.stderr, flush=True)
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
-    """Compile every kernel source and link the shared library.  Always recompiles."""
+    """Compile every kernel source and link the shared library, then the Python module.  Always recompiles."""
     objs = []
     procs = []
     units = [(src, src, []) for src in SOURCES]
@@ -63,11 +81,6 @@ def build(verbose: bool = False, extra_flags=()) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
-    if os.path.exists(FASTCALL):
-        os.remove(FASTCALL)
-    cmd = fastcall_command()
-    if cmd:
-        procs.append(("fastcall.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, pr in procs:
         out, _ = pr.communicate()
         # the host pass warns that it does not know the packed-fp32 feature: harmless
@@ -78,6 +91,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
             print(out, flush=True)
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
+    build_fastcall()
     return LIB
 
 

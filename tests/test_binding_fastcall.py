@@ -30,6 +30,8 @@ def outcome(call):
                          ids=lambda c: "-".join(c) or "host-tensors")
 def test_refusals_are_the_interpreters(change, monkeypatch):
     vb.lib()
+    if vb._fast is None:
+        pytest.skip("the native module is not built: nothing to compare")
     with_native = outcome(lambda: vb.vecinfer_decode_step(CFG, **step_args(**change)))
     monkeypatch.setattr(vb, "_fast", None)
     assert with_native == outcome(lambda: vb.vecinfer_decode_step(CFG, **step_args(**change)))
