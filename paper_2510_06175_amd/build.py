@@ -9,7 +9,8 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvecinfer.so")
-FASTCALL = os.path.join(HERE, "_fastcall.so")       # the hot calls' argument checks, see csrc/fastcall.cpp
+# the hot calls' argument checks, see csrc/fastcall.cpp; named after the interpreter it is built for, so that no other loads it
+FASTCALL = os.path.join(HERE, "_fastcall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 SOURCES = ["api.hip", "merge.hip", "encode.hip", "calibrate.hip", "probe.hip", "decode_lut.hip", "decode_roles.hip"]
 # the matrix-core attention kernels, compiled once for the calls without a residual window and once for those with one
 MFMA_SOURCES = ["decode_mfma.hip", "decode_mfma_wide.hip", "decode_mfma_wide64.hip", "decode_mfma_tiled.hip"]
@@ -52,8 +53,9 @@ def fastcall_command() -> list | None:
 def build_fastcall() -> None:
     """Compile the Python module.  The library does without it: where its compiler or torch's headers are missing or do not
     fit, a message says so and the calls go through ctypes."""
-    if os.path.exists(FASTCALL):
-        os.remove(FASTCALL)
+    for old in {FASTCALL, os.path.join(HERE, "_fastcall.so")}:       # (what earlier builds made, any interpreter loads the latter)
+        if os.path.exists(old):
+            os.remove(old)
     why = "no Python headers"
     try:
         cmd = fastcall_command()
