@@ -336,7 +336,7 @@ int vecinfer_decode_attention_static(const vecinfer_cfg *cfg, const void *q_f16,
  * A sequence with no token in either part yields o = 0 and L = -inf.  Everything else, and the
  * workspace size, as for vecinfer_decode_attention.
  * Errors: as vecinfer_decode_attention, plus EINVAL for a NULL window, R < 0, R > r_cap,
- * N + R < 1, and EUNSUPPORTED for R > VECINFER_MAX_RESIDUAL.
+ * N + R < 1, and EUNSUPPORTED for R > VECINFER_MAX_RESIDUAL or r_cap >= 2^31.
  */
 int vecinfer_decode_attention_residual(const vecinfer_cfg *cfg, const void *q_f16, const float *lambda,
                                        const void *cb_k_f16, const void *cb_v_f16,

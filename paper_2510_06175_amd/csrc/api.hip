@@ -312,7 +312,7 @@ int decode_common(const vecinfer_cfg *cfg, const void *q_f16, const float *lambd
     if (N > 0 && (!k_idx || !v_idx)) return VECINFER_EINVAL;
     if (window) {
         if (!v_res || R < 0 || R > r_cap || N + R < 1) return VECINFER_EINVAL;
-        if (R > VECINFER_MAX_RESIDUAL) return VECINFER_EUNSUPPORTED;
+        if (R > VECINFER_MAX_RESIDUAL || r_cap > 0x7fffffffLL) return VECINFER_EUNSUPPORTED;
         if (!aligned(k_res, 16) || !aligned(v_res, 16)) return VECINFER_EINVAL;
     }
     if (num_splits < 0 || num_splits > VECINFER_MAX_SPLITS) return VECINFER_EINVAL;

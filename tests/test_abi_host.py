@@ -130,6 +130,9 @@ def test_decode_residual_argument_errors():
     assert res(N=1024, ki=None) == vb.EINVAL                    # but codes are needed when N > 0
     need = vb.vecinfer_decode_workspace_bytes(CFG, 1, 1024, 4)
     assert res(ws=FAKE, ws_bytes=need - 1) == vb.EWORKSPACE
+    # a window's row capacity is a 32-bit number, with a code cache and without
+    assert res(R=8, r_cap=1 << 31, ws=FAKE, ws_bytes=1 << 40) == vb.EUNSUPPORTED
+    assert res(N=0, ki=None, vi=None, R=8, r_cap=1 << 31, ws=FAKE, ws_bytes=1 << 40) == vb.EUNSUPPORTED
     assert vb.vecinfer_decode_workspace_bytes(CFG, 1, 0, 0) == vb.vecinfer_decode_workspace_bytes(CFG, 1, 1, 1) > 0
 
 
