@@ -326,3 +326,12 @@ def test_an_infinite_key_leaves_infinities(D, d, bits):
         np.testing.assert_array_equal(first[0], np.where(mixed, np.nan, np.where(signs[0] > 0, np.inf, -np.inf)))
     assert np.isposinf(errors[0])
     assert np.isfinite(cb[0, :, 1:].astype(np.float64)).all()
+    # the second iteration of a call, against a second call
+    tr.train(1, -1.0)
+    cb_one, codes_one, _ = tr.state()
+    tr.cb.copy_(dev(cb0))
+    tr.train(2, -1.0)
+    cb_two, codes_two, _ = tr.state()
+    np.testing.assert_array_equal(codes_two[0, 0, 100], codes_one[0, 0, 100])
+    for special in (np.isnan, np.isposinf, np.isneginf):
+        np.testing.assert_array_equal(special(cb_two), special(cb_one))
