@@ -242,9 +242,9 @@ int vecinfer_kmeans_train(const vecinfer_cfg *cfg, const void *x_f16, const floa
 /*
  * Number of sequence splits (grid axis "num_splits" of Sec. 3.3) the library picks for (B, N) when
  * num_splits = 0 and the workspace has room for them: the most that any of the decode calls takes.  For short
- * sequences they differ (one for vecinfer_decode_attention, more for vecinfer_decode_attention_residual,
- * whose merge runs in any case), and VECINFER_VARIANT_LUT, or a call with seq_lens, takes one more for
- * some batches.  Host-only; returns >= 1, or a negative code.
+ * sequences they differ (one for vecinfer_decode_attention, more for vecinfer_decode_attention_residual), and
+ * VECINFER_VARIANT_LUT, or a call with seq_lens, takes one more for some batches.  Host-only; returns >= 1, or
+ * a negative code.
  */
 int32_t vecinfer_decode_auto_splits(const vecinfer_cfg *cfg, int32_t B, int64_t N);
 

@@ -103,19 +103,20 @@ enum class Call { kAttention, kStep, kWindow };
 // the compute units and a token has less than 128 bytes) and the sequences are more than a few (from N / 8 to N
 // tokens: 17 x 8 heads, 30000, d = 2 157 us whole, 90 in two; 9 x 8, 30000, d = 8 42.6 in three, 35.4 in four; 5 x 8, d = 4,
 // 30000 / 60000 27.6 / 40.1 in six, 35.9 / 36.4 in seven; 3 x 8, 30000 22.9 in ten, 28.6 in eleven).
-// The lines below were measured when the merge was a launch of its own, 3 to 5 us (5 with more than four query heads per KV
-// head).  Merged by the last workgroup a split costs less (8 / 1 heads, d = 8, 400 tokens 17.6 us by these lines, 12.3 in more
-// splits), but the counts are what callers size and compare by and stay:
+// All lines below were measured when the merge was a launch of its own, 3 to 5 us (5 with more than four query heads per KV
+// head), and not again since the last workgroup merges, for which a split costs less: at some sizes more splits would
+// now be faster (8 / 1 heads, d = 8, 400 tokens 17.6 us by these lines, 12.3 in more splits).
 //   attention alone has nothing but its tokens to share: whole up to 1024 of them (8 sequences, 4 / 1
 //     heads: 250 / 600 / 1000 tokens 8.3 / 9.9 / 11.1 us whole, 11.4 / 11.6 / 11.6 in 4 / 10 / 16 splits; 8 / 1
 //     heads 9.9 / 12.1 / 13.7 and 15.1 / 15.7 / 15.9), 768 with d_k = 2, whose keys are twice the bytes (600 / 1000
 //     tokens, d = 2: 11.2 / 13.6 us whole, 11.8 / 12.0), and twice that where two is all there is room for (128
 //     sequences, 1100 / 1900 tokens: 12.1 / 14.7 us whole, 14.4 / 16.0 in two; d = 2 14.8 / 19.2 and 15.6 / 19.1);
 //   a step shares the search for its new token too, which pays sooner (step_whole);
-//   with a residual window the merge runs in any case (16 sequences at 1500 tokens: 17.8 us whole, 15.8 in
-//     two; up to 256 tokens nothing is gained: 200 tokens, 8 / 1 heads, d8b12, 17.7 us whole, 18.3 in four).
-// The merge reads 32 partials in one go, and every further 32 are another dependent round (about 2 us, 5
-// with more than four query heads per KV head), against a split's stream, which grows with N and the bytes
+//   with a residual window the merge launch ran in any case, so that splits paid sooner (16 sequences at 1500 tokens:
+//     17.8 us whole, 15.8 in two; up to 256 tokens nothing was gained: 200 tokens, 8 / 1 heads, d8b12, 17.7 us whole, 18.3
+//     in four).  A window call taken whole has no merge now.
+// The merge launch read 32 partials in one go (merge_arrived: 64, 32 with two head groups at D = 128), and every further 32
+// were another dependent round (about 2 us, 5 with more than four query heads per KV head), against a split's stream, which grows with N and the bytes
 // of a token's codes: more than 32, 64 and 128 splits pay from about 55000, 200000 and 500000 tokens on,
 // the first two sooner with 96 bytes or more.  One sequence, us per step in 32 / 64 / 128 / 256 splits:
 //   heads          57000 tokens       65536                  131072              262144             786432

@@ -9,9 +9,9 @@
 //   phase 2  search (encode_screen.h): a wavefront owns one sub-space at a time and a lane one
 //            token; the matrix cores shortlist, the exact fp32 distances decide.
 //   phase 3  the code bytes go out through LDS.
-// What bounds it: issue.  At 65536 x 8 tokens, d = 4, values, the kernel takes 269 us (287 for keys), with four wavefronts per
-// SIMD; with the butterflies through LDS shuffles and a division per channel 292 and 354, of which the vector ALU was
-// busy for 82 % and the matrix cores for 22 % (values).
+// What bounds it: issue.  At 65536 x 8 tokens, d = 4, values, the kernel takes 257 .. 269 us (274 .. 289 for keys), with four
+// wavefronts per SIMD; the vector ALU is busy for about 85 % of that, the matrix cores for 21.  With the butterflies through
+// LDS shuffles and a division per channel it took 292 and 354.
 #include "common.h"
 #include "encode_screen.h"
 #include "mfma_helpers.h"
