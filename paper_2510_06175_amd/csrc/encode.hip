@@ -27,8 +27,9 @@ constexpr int kEncTokens = 64;     // tokens per workgroup = lanes per wavefront
 // (kTransform) or just widened (values), as fp32 rows of x_s (row stride D + 4 floats).  A lane
 // owns 4 consecutive channels of one token; the first two butterfly stages run inside the lane,
 // the others across lanes on the vector ALU (DPP, row swaps): shuffles through LDS cost a trip per stage
-// that nothing covers, since all wavefronts are in this phase together (with divisions instead of tile_lambda's
-// reciprocals as well: 65536 x 8 keys and values, d = 4 539 us, now 498; 8 training iterations over 32768 x 8 keys 2207 / 1828).
+// that nothing covers, since all wavefronts are in this phase together (65536 x 8 keys and values, d = 4: shuffles and
+// divisions 539 us; divisions alone, instead of tile_lambda's reciprocals, 506, neither 486; 8 training iterations over
+// 32768 x 8 keys 2207, 1935 and 1804).
 // NCH < D: only channels ch0 .. ch0 + NCH - 1 are kept (row stride NCH + 4), for a workgroup that
 // searches a group of sub-spaces; values outside the window are then not even loaded.
 // The two halves are separate so that a kernel can request the next tile's rows before it searches
